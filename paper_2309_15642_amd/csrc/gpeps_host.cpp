@@ -387,11 +387,10 @@ gpeps_status build_layout(const gpeps_graph* graphs, int32_t n_graphs, const int
   }
   // BP's directed edges by falling degree of the sender: a sender with three legs costs D times one
   // with two, and the dear workgroups have to start first to share the CUs evenly
-  L.bp_order.resize((size_t)2 * L.NE);
-  for (size_t i = 0; i < L.bp_order.size(); ++i) L.bp_order[i] = (int32_t)i;
-  std::stable_sort(L.bp_order.begin(), L.bp_order.end(), [&](int32_t a, int32_t b) {
-    return L.edges[a >> 1].side[a & 1].deg > L.edges[b >> 1].side[b & 1].deg;
-  });
+  L.bp_order.reserve((size_t)2 * L.NE);
+  for (int deg = kMaxDeg; deg >= 1; --deg)
+    for (int i = 0; i < 2 * L.NE; ++i)
+      if (L.edges[i >> 1].side[i & 1].deg == deg) L.bp_order.push_back(i);
   const size_t slots = std::max(L.max_items, 1);
   size_t off = 0;
   auto take = [&](size_t bytes) {

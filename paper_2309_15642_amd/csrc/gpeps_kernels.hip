@@ -36,6 +36,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "gpeps_device.h"
 #include "gpeps_internal.h"
 
@@ -416,34 +418,36 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
 // ------------------------------------------------------------------ K2: Theta + Jacobi SVD + truncation
 
 // One workgroup of NT = 256 threads per item; NMAX = 2 * largest D handled
-// (32 for D <= 16, 64 for D <= 32).  Theta' lives in LDS as the matrix B whose
-// columns are orthogonalised: B = Theta' when Theta' has no more columns than
-// rows, else B = Theta'^H.  One-sided (Hestenes) Jacobi rotates column pairs
-// in a parallel tournament order (complex64: columns held in registers, see the
-// loop; complex128: circle method through LDS); squared column norms are tracked
-// and recomputed at the start of every sweep, so each rotation needs a single
-// reduction (the inner product).  A pair is rotated when its inner product
-// exceeds 2^-52 * mB relative to the column norms and also exceeds
+// (32 for D <= 16, 64 for D <= 32).  Theta' lives in LDS as the matrix B, the one of Theta' and
+// Theta'^H with fewer columns.  B P = Q R with the columns in an order P of falling size, and the
+// one-sided (Hestenes) Jacobi iteration runs on X = R^H, whose columns start nearly orthogonal and
+// graded: its orthogonalised columns are B's right singular vectors with rows permuted by P, scaled
+// by the singular values.  Squared column norms are tracked and recomputed at the start of every
+// sweep, so each rotation needs a single reduction (the inner product).  A pair is rotated when its
+// inner product exceeds 2^-52 * nB relative to the column norms and also exceeds
 // 2^-52 * eps^2 * ||B||_F^2 (eps = truncation cutoff): pairs below that are
 // made of columns far under the cutoff (rounding noise), whose rotation
 // cannot move a kept singular vector.  The sweep loop ends when a sweep
-// applies no rotation, or (complex64 path) when every rotation of the sweep
-// had |g|^2 <= 1e-8 al be (angles below 1e-4): by the quadratic convergence of
-// the sweeps the off-diagonal left is then O(1e-8) relative, under the 2^-24
-// rounding of the complex64 tensors the update writes.  The complex64 path also takes one Newton step, not
-// two, for the reciprocal square roots (unitarity to ~1e-13 per rotation), and runs the
-// iteration on X = R^H, R from a column-pivoted Cholesky factorisation of B^H B (below), whose
-// columns start nearly orthogonal and graded.
-// ACC (complex128 path) also accumulates the rotations W, which give the
-// other set of singular vectors directly; without it (complex64 path, cutoff
-// ~1e-6) they are recovered from the original Theta' as U = Theta' V / sigma
-// or V = Theta'^H U / sigma, accurate to ~2^-52 sigma_0 / sigma_k, well below
-// the complex64 storage rounding for every kept value.
+// applies no rotation, or when every rotation of the sweep was quiet: by the quadratic convergence
+// of the sweeps the off-diagonal left is then about the square of the quiet level, relative.
+//   complex64 (ACC = false): quiet at |g|^2 <= 1e-8 al be (angles below 1e-4; what is left, 1e-8,
+// is under the 2^-24 rounding of the complex64 tensors the update writes), one Newton step, not
+// two, for the reciprocal square roots (unitarity to ~1e-13 per rotation), R from a column-pivoted
+// Cholesky factorisation of B^H B, and the other set of singular vectors from the original Theta'
+// as U = Theta' V / sigma or V = Theta'^H U / sigma, accurate to ~2^-52 sigma_0 / sigma_k, well
+// below the complex64 storage rounding for every kept value (cutoff ~1e-6).
+//   complex128 (ACC = true, cutoffs down to 1e-12): quiet at |g|^2 <= 1e-16 al be, R from a
+// Householder QR of B with its columns sorted by norm, and the rotations accumulated in W, so that
+// the other set is Q W, accurate for every sigma.  D = 16, ten steps of the 127-qubit graph: 110 us
+// per launch and 5.3 sweeps (9.3 at most 17 without the QR, through LDS: 192 us).  A square B of at
+// most kSmallB columns takes Q = I, R = B: the QR and the reflectors (3.5 us at two columns) cost
+// more than the sweep they save.
 // BWD: the forward update (the same path and arithmetic, so the truncation rank and the
 // gauge of the new tensors are the forward ones bit for bit) that also keeps what the
 // reverse sweep needs: every singular triplet (bU, bV, bS) and float64 T matrices (t64).
-constexpr double kJacobiQuiet = 1e-12;     // (1e-6)^2: relative size of a "small" rotation
-constexpr double kJacobiQuietC64 = 1e-8;   // (1e-4)^2: the same for the complex64 path
+constexpr double kJacobiQuietC64 = 1e-8;    // (1e-4)^2: relative size of a quiet rotation, complex64
+constexpr int kSmallB = 8;                  // largest square B that skips the QR, complex128
+constexpr double kJacobiQuietC128 = 1e-16;  // (1e-8)^2: the same for the complex128 path
 
 template <typename CT, int NT, int NMAX, bool ACC_, bool BWD = false>
 __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd(DevState st, const int32_t* __restrict__ items, int first) {
@@ -454,7 +458,6 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
   constexpr int KPT = (DM * DM + NT - 1) / NT;  // (k, k') pairs per thread (4)
   constexpr int RPL = NMAX * NMAX / (2 * NT);  // rows per lane of a Jacobi column pair (upper bound)
   static_assert(2 * NT / NMAX <= 64 && RPL * (2 * NT / NMAX) >= NMAX, "Jacobi rows must fit RPL per lane");
-  constexpr bool PRE = !ACC;               // Cholesky preconditioning (complex64 path)
   constexpr int DS = DM + 1;               // padded row stride of the staging arena (no bank conflicts)
   // B: column-major B[col][row], column stride NMAX (a 16-lane group reading 16 consecutive rows
   // covers all 64 LDS banks once; lane groups that share an LDS cycle start on different row
@@ -468,7 +471,6 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
   __shared__ double lam_old[kMaxD];
   __shared__ double sig[NMAX];
   __shared__ int perm[NMAX];
-  __shared__ int sh_rot, sh_big;
   __shared__ int sh_chi;
   __shared__ double sh_norm;
   __shared__ double sh_floor;
@@ -499,6 +501,7 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
   const bool trans = n0 > m0;  // orthogonalise the shorter side
   const int mB = trans ? n0 : m0;
   const int nB = trans ? m0 : n0;
+  const bool small_sq = ACC && nB <= kSmallB && mB == nB;
   const double2* Rg = st.rbuf + rbuf_off(st, slot, 0, 0);  // 4 consecutive [D][D] blocks: i0, i1, j0, j1
 
   // stage the R factors of one end ([2][r][de], row stride DS) into an LDS region
@@ -587,7 +590,7 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
     sh_floor = f * st.trunc_rel * st.trunc_rel * 2.220446049250313e-16;
   }
 
-  // Preconditioning (complex64 path): R from a column-pivoted Cholesky factorisation of the
+  // Preconditioning, complex64 path: R from a column-pivoted Cholesky factorisation of the
   // Gram matrix, P^T B^H B P = R^H R, then the Jacobi iteration runs on X = R^H (nB x nB).  With
   // Q = B P R^-1 (orthonormal columns), B P = Q R and X = U_X S W^H gives B = (Q W) S (P U_X)^H,
   // so the orthogonalised columns of X are B's right singular vectors (rows permuted by P) and
@@ -595,8 +598,7 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
   // of B below ~1e-8 of its norm are not resolved, two orders under the truncation cutoff and
   // about the complex64 rounding of the stored tensors; the factorisation stops at a pivot below
   // 64 eps of the first (the remaining rows of R are zero).
-  int mJ = mB;
-  if (PRE) {
+  if constexpr (!ACC) {
     // G = B^H B on the FP64 matrix cores, 16 x 16 tiles over the waves (tile wv + q NW of the
     // tg x tg grid to wave wv; lane l holds rows i0 + l / 16 + 4 r, column j0 + l % 16 of each).
     constexpr int NW = NT / 64;
@@ -849,11 +851,121 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
       if (idx < nB * nB) B[c][rr] = xt[e];
     }
     __syncthreads();
-    mJ = nB;
+  } else {
+    // complex128 path: Householder QR of B, its columns in falling order of their norms.  Group c
+    // (LQ lanes) holds the column of position c in registers; one barrier per column: the owner of
+    // position j + 1 publishes its rows and their squared norm (below the diagonal) right after
+    // reflector j, and every group rebuilds reflector j + 1 from that copy, bit-identically.  The
+    // reflectors, scaled by sqrt(tau) (H = I - v v^H), are kept in the item's T buffer, which
+    // nothing else uses before the T matrices are written.
+    constexpr int LQ = NT / NMAX;
+    constexpr int RQ = NMAX / LQ;
+    __shared__ double2 vb[2][NMAX];
+    __shared__ double vn[2];
+    double2* const refl = reinterpret_cast<double2*>(st.tbuf) + rbuf_off(st, slot, 0, 0);  // [nB][mB]
+    if (small_sq) {
+      static_assert(kSmallB * kSmallB <= NT, "one entry per thread");
+      const int c = tid / nB, rr = tid - (tid / nB) * nB;
+      const bool in = tid < nB * nB;
+      const double2 t = B[in ? rr : 0][in ? c : 0];
+      __syncthreads();
+      if (in) B[c][rr] = cconj(t);
+      if (tid < nB) colid[tid] = tid;
+      __syncthreads();
+    } else {
+    const int qc = tid / LQ, ql = tid - (tid / LQ) * LQ;
+    {
+      double s2 = 0.0;
+      if (qc < nB)
+        for (int rr = ql; rr < mB; rr += LQ) s2 += cabs2(B[qc][rr]);
+      s2 = group_sum_dpp(s2, LQ);
+      if (ql == 0) nrm[qc] = qc < nB ? s2 : -1.0;
+    }
+    __syncthreads();
+    if (tid < nB) {
+      const double sv = nrm[tid];
+      int pos = 0;
+      for (int d = 0; d < nB; ++d) {
+        const double sd = nrm[d];
+        pos += (sd > sv) || (sd == sv && d < tid);
+      }
+      colid[pos] = tid;
+    }
+    __syncthreads();
+    double2 x[RQ];
+#pragma unroll
+    for (int u = 0; u < RQ; ++u) {
+      const int rr = ql + LQ * u;
+      x[u] = (qc < nB && rr < mB) ? B[colid[qc < nB ? qc : 0]][rr] : make_double2(0.0, 0.0);
+    }
+    auto publish = [&](int j) {  // rows and the norm below row j of the column of position j
+      double s2 = 0.0;
+#pragma unroll
+      for (int u = 0; u < RQ; ++u) {
+        const int rr = ql + LQ * u;
+        vb[j & 1][rr] = x[u];
+        if (rr > j) s2 += cabs2(x[u]);
+      }
+      s2 = group_sum_dpp(s2, LQ);
+      if (ql == 0) vn[j & 1] = s2;
+    };
+    if (qc == 0) publish(0);
+    __syncthreads();
+    for (int j = 0; j < nB; ++j) {
+      const double2 alpha = vb[j & 1][j];
+      const double s2 = vn[j & 1];
+      double2 v[RQ];
+#pragma unroll
+      for (int u = 0; u < RQ; ++u) v[u] = vb[j & 1][ql + LQ * u];
+      // reflector v = x - beta e_j, beta = -phase(x_j) ||x||, x = rows j.. of the column; an exactly
+      // zero lower part needs none
+      const bool any = s2 > 0.0;
+      const double aa2 = cabs2(alpha);
+      const double nu2 = any ? aa2 + s2 : 1.0;
+      const double nu = nu2 * rsq_nr(nu2);
+      const double2 ph = aa2 > 0.0 ? cscale(alpha, rsq_nr(aa2)) : make_double2(1.0, 0.0);
+      const double2 beta = any ? cscale(ph, -nu) : alpha;
+      const double2 v0 = csub(alpha, beta);
+      const double tau = any ? 2.0 * rcp_nr(cabs2(v0) + s2) : 0.0;
+#pragma unroll
+      for (int u = 0; u < RQ; ++u) {
+        const int rr = ql + LQ * u;
+        v[u] = rr == j ? v0 : rr > j ? v[u] : make_double2(0.0, 0.0);
+      }
+      if (qc > j && qc < nB) {
+        double wr = 0.0, wi = 0.0;
+#pragma unroll
+        for (int u = 0; u < RQ; ++u) {
+          const double2 t = cmulc(v[u], x[u]);
+          wr += t.x;
+          wi += t.y;
+        }
+        group_sum2_dpp(wr, wi, LQ);
+        const double2 f = make_double2(wr * tau, wi * tau);
+#pragma unroll
+        for (int u = 0; u < RQ; ++u) x[u] = csub(x[u], cmul(v[u], f));
+        if (qc == j + 1) publish(j + 1);
+      } else if (qc == j) {
+        const double rt = any ? tau * rsq_nr(tau) : 0.0;
+#pragma unroll
+        for (int u = 0; u < RQ; ++u) {
+          const int rr = ql + LQ * u;
+          if (rr < mB) refl[j * mB + rr] = cscale(v[u], rt);
+          if (rr == j) x[u] = beta;
+        }
+      }
+      __syncthreads();
+    }
+    // B <- R^H: X[c][r] = conj(R(c, r)), c <= r, from the registers of column r
+#pragma unroll
+    for (int u = 0; u < RQ; ++u) {
+      const int c = ql + LQ * u;
+      if (qc < nB && c < nB) B[c][qc] = c <= qc ? cconj(x[u]) : make_double2(0.0, 0.0);
+    }
+    __syncthreads();
+    }
   }
 
-  const int np = nB + (nB & 1);
-  const int npairs = np / 2;
   constexpr int LJ = 2 * NT / NMAX;  // lanes per column pair
   const int pair_id = tid / LJ;
   const int lane = tid - pair_id * LJ;
@@ -863,12 +975,11 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
   static_assert((RPL & (RPL - 1)) == 0 && RPL >= PW, "Jacobi row blocks");
   const int jsh = pair_id & (PW - 1);
   auto jrow = [&](int u) { return lane + LJ * ((u + jsh) & (RPL - 1)); };
-  const bool active = pair_id < npairs;
-  const double tol2 = (2.220446049250313e-16 * (double)mJ) * (2.220446049250313e-16 * (double)mJ);
+  const double tol2 = (2.220446049250313e-16 * (double)nB) * (2.220446049250313e-16 * (double)nB);
   int sweep = 0;
   bool converged = (nB < 2);
-  if constexpr (PRE) {
-    // Register-resident Jacobi (complex64 path, X = R^H: nB x nB).  The columns are padded to
+  {
+    // Register-resident Jacobi on X = R^H (nB x nB).  The columns are padded to
     // 2^K >= nB and paired as {c, c ^ m} for m = 1 .. 2^K - 1, a complete sweep in which every
     // round is a perfect matching.  The rounds run in blocks of equal highest bit hb of m: inside
     // a block the column of the pair with bit hb clear stays in the registers of its lane group
@@ -877,41 +988,21 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
     // order, consecutive rounds differ in one bit b of m', so every moving column passes to
     // group g ^ 2^b: a lane permutation (lane ^ LJ 2^b) inside a wave, an LDS store, barrier and
     // load across waves.  Between blocks (and at the end of every sweep) all columns are written
-    // to B and re-read under the next block's assignment.  The rotation arithmetic is that of
-    // the LDS path below.
+    // to B and re-read under the next block's assignment.  With ACC the columns of W travel with
+    // those of X.
+    //   The rotation of smaller angle (|theta| <= pi/4) with tan 2 theta = 2|g| / (be - al):
+    // h = (d^2 + 4|g|^2)^1/2, d = be - al, x = cos^2 theta = (1 + |d| / h) / 2, and
+    // c = x^1/2, s e^{i phi} = sign(d) g / (h x^1/2), so c^2 + |s|^2 = 1 exactly in exact
+    // arithmetic and |g| itself is never formed.
     constexpr int GW = 64 / LJ;  // lane groups per wave
     int K = 1;
     while ((1 << K) < nB) ++K;
     const bool gact = pair_id < (1 << (K - 1));
+    // a wave whose groups are all inactive takes part in the barriers only (uniform over the wave;
+    // at NMAX = 64 only the first steps have such waves, and the test costs the others 0.7 %)
+    const bool wact = NMAX == 64 || (__builtin_amdgcn_readfirstlane(tid) / LJ) < (1 << (K - 1));
     auto ins = [](int g, int hb, int bit) { return ((g >> hb) << (hb + 1)) | (bit << hb) | (g & ((1 << hb) - 1)); };
     auto xrow = [&](int u) { return lane + LJ * u; };
-    double2 xs[RPL], xm[RPL];  // stationary and moving column of the group
-    double ns = 0.0, nm = 0.0;  // their tracked squared norms
-    int cs_id = 0, cm_id = 0;   // their column indices
-    auto load_col = [&](double2 (&x)[RPL], int c) {
-#pragma unroll
-      for (int u = 0; u < RPL; ++u) {
-        const int rr = xrow(u);
-        const double2 t = B[c][rr];
-        x[u] = (gact && c < nB && rr < nB) ? t : make_double2(0.0, 0.0);
-      }
-    };
-    auto store_col = [&](const double2 (&x)[RPL], int c, double n2) {
-      if (gact && c < nB) {
-#pragma unroll
-        for (int u = 0; u < RPL; ++u) {
-          const int rr = xrow(u);
-          if (rr < nB) B[c][rr] = x[u];
-        }
-        if (lane == 0) nrm[c] = n2;
-      }
-    };
-    auto col_norm = [&](const double2 (&x)[RPL]) {
-      double s2 = 0.0;
-#pragma unroll
-      for (int u = 0; u < RPL; ++u) s2 += cabs2(x[u]);
-      return group_sum_dpp(s2, LJ);
-    };
     // per-sweep flags (any rotation, any rotation above the quiet level), three sets in
     // rotation so that a set is cleared neither while it is read nor after it is written
     __shared__ int sh_flag[3][2];
@@ -920,233 +1011,174 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
     // their tracked norms are zero too (store_col never writes them), which keeps the rotation
     // scalars of every pair finite
     for (int c = nB + tid; c < NMAX; c += NT) nrm[c] = 0.0;
-    bool rot = false, big = false;
     __syncthreads();
-    const double floor2 = sh_floor * sh_floor;
-    for (; sweep < st.max_sweeps && !converged; ++sweep) {
-      for (int hb = 0; hb < K; ++hb) {
-        cs_id = ins(pair_id, hb, 0);
-        cm_id = ins(pair_id, hb, 1);
-        load_col(xs, cs_id);
-        load_col(xm, cm_id);
-        if (hb == 0) {
-          ns = col_norm(xs);
-          nm = col_norm(xm);
-        } else {
-          ns = nrm[cs_id];
-          nm = nrm[cm_id];
+    // RB row blocks of LJ rows: a matrix of at most half the rows leaves the upper half of them out
+    auto sweeps = [&](auto row_blocks) {
+      constexpr int RB = decltype(row_blocks)::value;
+      double2 xs[RB], xm[RB];  // stationary and moving column of the group
+      double2 us[ACC ? RB : 1], um[ACC ? RB : 1];  // and the columns of W that go with them
+      double ns = 0.0, nm = 0.0;  // their tracked squared norms
+      int cs_id = 0, cm_id = 0;   // their column indices
+      auto load_col = [&](double2 (&x)[RB], double2 (&w)[ACC ? RB : 1], int c) {
+#pragma unroll
+        for (int u = 0; u < RB; ++u) {
+          const int rr = xrow(u);
+          const double2 t = B[c][rr];
+          x[u] = (gact && c < nB && rr < nB) ? t : make_double2(0.0, 0.0);
+          if constexpr (ACC) {
+            const double2 q = W[c][rr];
+            w[u] = (gact && c < nB && rr < nB) ? q : make_double2(0.0, 0.0);
+          }
         }
-        const int nt = 1 << hb;
-        // the moving column passes to group pair_id ^ 2^bb (lane ^ LJ 2^bb inside a wave)
-        auto move_intra = [&](auto tag) {
-          constexpr int OFF = decltype(tag)::value;
+      };
+      auto store_col = [&](const double2 (&x)[RB], const double2 (&w)[ACC ? RB : 1], int c, double n2) {
+        if (gact && c < nB) {
 #pragma unroll
-          for (int u = 0; u < RPL; ++u) lane_xor_pair<OFF>(xm[u].x, xm[u].y);
-          nm = lane_xor<OFF>(nm);
-        };
-        auto move_off = [&](int off) {
-          if (off == 4) move_intra(std::integral_constant<int, 4>());
-          else if (off == 8) move_intra(std::integral_constant<int, 8>());
-          else if (off == 16) move_intra(std::integral_constant<int, 16>());
-          else move_intra(std::integral_constant<int, 32>());
-        };
-        // one round: the rotation of the group's pair (stationary xs, moving xm).  Branch-free:
-        // a pair that is not rotated takes c = 1, s = 0 (f = 0), which leaves both columns and
-        // norms bit for bit.  Padding columns are exactly zero, so their pairs have g = 0 and are
-        // never rotated; h is kept away from zero so that every pair's scalars stay finite.
-        auto round = [&]() {
-          double2 g = cmulc(xs[0], xm[0]);
-#pragma unroll
-          for (int u = 1; u < RPL; ++u) g = cadd(g, cmulc(xs[u], xm[u]));
-          double gr = g.x, gi = g.y;
-          group_sum2_dpp(gr, gi, LJ);
-          const double al = ns, be = nm;
-          const double g2 = gr * gr + gi * gi;
-          const double ab = al * be;
-          const bool ok = (g2 > tol2 * ab) & (g2 > floor2);
-          const double d = be - al;
-          const double h2 = fmax(d * d + 4.0 * g2, 1e-300);
-          const double rh = rsq_nr1(h2);  // 1 / h
-          const double x = 0.5 + 0.5 * fabs(d) * rh;
-          const double rc = rsq_nr1(x);   // 1 / c
-          const double f = ok ? copysign(rh, d) * rc : 0.0;
-          const double cs = ok ? x * rc : 1.0;
-          const double2 sph = make_double2(gr * f, gi * f);  // s e^{i phi}
-          const double tg = g2 * f * rc;                      // t |g|
-#pragma unroll
-          for (int u = 0; u < RPL; ++u) {
-            const double2 bp = xs[u], bq = xm[u];
-            xs[u] = csub(cscale(bp, cs), cmulc(sph, bq));
-            xm[u] = cadd(cmul(sph, bp), cscale(bq, cs));
+          for (int u = 0; u < RB; ++u) {
+            const int rr = xrow(u);
+            if (rr < nB) {
+              B[c][rr] = x[u];
+              if constexpr (ACC) W[c][rr] = w[u];
+            }
           }
-          ns = al - tg;
-          nm = be + tg;
-          rot |= ok;
-          big |= ok & (g2 > kJacobiQuietC64 * ab);
-        };
-        // the moving column of this group in round t of the block
-        auto mid = [&](int t) { return ins(pair_id ^ (t ^ (t >> 1)), hb, 1); };
-        // groups of up to 8 rounds (4 when a lane holds 8 or more rows: straight-line groups
-        // that long take the compiler many minutes for little gain)
-        constexpr int UN = RPL >= 8 ? (GW < 4 ? GW : 4) : (GW < 8 ? GW : 8);
-        if (nt < UN) {
-          // short block (2^hb rounds, all moves inside a wave)
-          for (int t = 0; t < nt; ++t) {
-            round();
-            if (t + 1 < nt) move_off(LJ << __builtin_ctz(t + 1));
-          }
-        } else {
-          // rounds in groups of UN (nt is a multiple of UN): inside a group the bit that changes
-          // between consecutive rounds, ctz(k + 1), is a compile-time constant and every move is
-          // unconditional straight-line code; only the move after a group can cross waves
-          for (int t0 = 0; t0 < nt; t0 += UN) {
+          if (lane == 0) nrm[c] = n2;
+        }
+      };
+      auto col_norm = [&](const double2 (&x)[RB]) {
+        double s2 = 0.0;
 #pragma unroll
-            for (int k = 0; k < UN; ++k) {
-              round();
-              const int t = t0 + k;
-              if (k + 1 < UN) {
-                move_off(LJ << __builtin_ctz(k + 1));  // folds to one straight-line move
-              } else if (t + 1 < nt) {
+        for (int u = 0; u < RB; ++u) s2 += cabs2(x[u]);
+        return group_sum_dpp(s2, LJ);
+      };
+      bool rot = false, big = false;
+      const double floor2 = sh_floor * sh_floor;
+      for (; sweep < st.max_sweeps && !converged; ++sweep) {
+        for (int hb = 0; hb < K; ++hb) {
+          cs_id = ins(pair_id, hb, 0);
+          cm_id = ins(pair_id, hb, 1);
+          load_col(xs, us, cs_id);
+          load_col(xm, um, cm_id);
+          if (hb == 0) {
+            ns = col_norm(xs);
+            nm = col_norm(xm);
+          } else {
+            ns = nrm[cs_id];
+            nm = nrm[cm_id];
+          }
+          const int nt = 1 << hb;
+          // the moving column passes to group pair_id ^ 2^bb (lane ^ LJ 2^bb inside a wave)
+          auto move_intra = [&](auto tag) {
+            constexpr int OFF = decltype(tag)::value;
+#pragma unroll
+            for (int u = 0; u < RB; ++u) {
+              lane_xor_pair<OFF>(xm[u].x, xm[u].y);
+              if constexpr (ACC) lane_xor_pair<OFF>(um[u].x, um[u].y);
+            }
+            nm = lane_xor<OFF>(nm);
+          };
+          auto move_off = [&](int off) {
+            if (off == 4) move_intra(std::integral_constant<int, 4>());
+            else if (off == 8) move_intra(std::integral_constant<int, 8>());
+            else if (off == 16) move_intra(std::integral_constant<int, 16>());
+            else move_intra(std::integral_constant<int, 32>());
+          };
+          // one round: the rotation of the group's pair (stationary xs, moving xm).  Branch-free:
+          // a pair that is not rotated takes c = 1, s = 0 (f = 0), which leaves both columns and
+          // norms bit for bit.  Padding columns are exactly zero, so their pairs have g = 0 and are
+          // never rotated; h is kept away from zero so that every pair's scalars stay finite.
+          auto round = [&]() {
+            double2 g = cmulc(xs[0], xm[0]);
+#pragma unroll
+            for (int u = 1; u < RB; ++u) g = cadd(g, cmulc(xs[u], xm[u]));
+            double gr = g.x, gi = g.y;
+            group_sum2_dpp(gr, gi, LJ);
+            const double al = ns, be = nm;
+            const double g2 = gr * gr + gi * gi;
+            const double ab = al * be;
+            const bool ok = (g2 > tol2 * ab) & (g2 > floor2);
+            const double d = be - al;
+            const double h2 = fmax(d * d + 4.0 * g2, 1e-300);
+            const double rh = ACC ? rsq_nr(h2) : rsq_nr1(h2);  // 1 / h
+            const double x = 0.5 + 0.5 * fabs(d) * rh;
+            const double rc = ACC ? rsq_nr(x) : rsq_nr1(x);    // 1 / c
+            const double f = ok ? copysign(rh, d) * rc : 0.0;
+            const double cs = ok ? x * rc : 1.0;
+            const double2 sph = make_double2(gr * f, gi * f);  // s e^{i phi}
+            const double tg = g2 * f * rc;                      // t |g|
+#pragma unroll
+            for (int u = 0; u < RB; ++u) {
+              const double2 bp = xs[u], bq = xm[u];
+              xs[u] = csub(cscale(bp, cs), cmulc(sph, bq));
+              xm[u] = cadd(cmul(sph, bp), cscale(bq, cs));
+              if constexpr (ACC) {
+                const double2 wp = us[u], wq = um[u];
+                us[u] = csub(cscale(wp, cs), cmulc(sph, wq));
+                um[u] = cadd(cmul(sph, wp), cscale(wq, cs));
+              }
+            }
+            ns = al - tg;
+            nm = be + tg;
+            rot |= ok;
+            big |= ok & (g2 > (ACC ? kJacobiQuietC128 : kJacobiQuietC64) * ab);
+          };
+          // the moving column of this group in round t of the block
+          auto mid = [&](int t) { return ins(pair_id ^ (t ^ (t >> 1)), hb, 1); };
+          // groups of up to 8 rounds (4 when a lane holds 8 or more rows: straight-line groups
+          // that long take the compiler many minutes for little gain)
+          constexpr int UN = RB >= 8 ? (GW < 4 ? GW : 4) : (GW < 8 ? GW : 8);
+          if (nt < UN) {
+            // short block (2^hb rounds, all moves inside a wave)
+            if (wact) {
+              for (int t = 0; t < nt; ++t) {
+                round();
+                if (t + 1 < nt) move_off(LJ << __builtin_ctz(t + 1));
+              }
+            }
+          } else {
+            // rounds in groups of UN (nt is a multiple of UN): inside a group the bit that changes
+            // between consecutive rounds, ctz(k + 1), is a compile-time constant and every move is
+            // unconditional straight-line code; only the move after a group can cross waves
+            for (int t0 = 0; t0 < nt; t0 += UN) {
+              if (wact) {
+#pragma unroll
+                for (int k = 0; k < UN; ++k) {
+                  round();
+                  if (k + 1 < UN) move_off(LJ << __builtin_ctz(k + 1));  // folds to one straight-line move
+                }
+              }
+              const int t = t0 + UN - 1;
+              if (t + 1 < nt) {
                 const int bb = __builtin_ctz(t + 1);
                 if ((1 << bb) < GW) {
-                  move_off(LJ << bb);
+                  if (wact) move_off(LJ << bb);
                 } else {
-                  store_col(xm, mid(t), nm);
+                  store_col(xm, um, mid(t), nm);
                   __syncthreads();
-                  load_col(xm, mid(t + 1));
+                  load_col(xm, um, mid(t + 1));
                   nm = nrm[mid(t + 1)];
                 }
               }
             }
           }
+          cm_id = mid(nt - 1);
+          // end of the block: every column back to B (with its tracked norm)
+          store_col(xs, us, cs_id, ns);
+          store_col(xm, um, cm_id, nm);
+          if (hb + 1 == K) {
+            if (rot && lane == 0) sh_flag[sweep % 3][0] = 1;
+            if (big && lane == 0) sh_flag[sweep % 3][1] = 1;
+            if (tid < 2) sh_flag[(sweep + 1) % 3][tid] = 0;
+            rot = false;
+            big = false;
+          }
+          __syncthreads();
         }
-        cm_id = mid(nt - 1);
-        // end of the block: every column back to B (with its tracked norm)
-        store_col(xs, cs_id, ns);
-        store_col(xm, cm_id, nm);
-        if (hb + 1 == K) {
-          if (rot && lane == 0) sh_flag[sweep % 3][0] = 1;
-          if (big && lane == 0) sh_flag[sweep % 3][1] = 1;
-          if (tid < 2) sh_flag[(sweep + 1) % 3][tid] = 0;
-          rot = false;
-          big = false;
-        }
-        __syncthreads();
+        converged = (sh_flag[sweep % 3][0] == 0) || (sh_flag[sweep % 3][1] == 0);
       }
-      // complex64 path: a sweep whose rotations all had |g|^2 <= 1e-12 al be ends the iteration
-      converged = (sh_flag[sweep % 3][0] == 0) || (sh_flag[sweep % 3][1] == 0);
-    }
-  } else {
-  for (; sweep < st.max_sweeps && !converged; ++sweep) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int c = 2 * pair_id + h;
-      double s2 = 0.0;
-#pragma unroll
-      for (int u = 0; u < RPL; ++u) {
-        const int rr = jrow(u);
-        const double2 t = B[c][rr];
-        if (c < nB && rr < mJ) s2 += cabs2(t);
-      }
-      s2 = group_sum_dpp(s2, LJ);
-      if (lane == 0 && c < nB) nrm[c] = s2;
-    }
-    if (tid == 0) {
-      sh_rot = 0;
-      sh_big = 0;
-    }
-    __syncthreads();
-    const double floor2 = sh_floor * sh_floor;
-    // circle-method tournament: slot 0 fixed, the others advance by one each round
-    int pa = pair_id;
-    int pb = np - 1 - pair_id;
-    for (int round = 0; round < np - 1; ++round) {
-      const bool work = active && (pa < nB) && (pb < nB);
-      const int p = work ? (pa < pb ? pa : pb) : 0;
-      const int q = work ? (pa < pb ? pb : pa) : 0;
-      // every load of the round is issued before the first use
-      double2 bp[RPL], bq[RPL];
-#pragma unroll
-      for (int u = 0; u < RPL; ++u) {
-        const int rr = jrow(u);
-        const double2 a = B[p][rr], b = B[q][rr];
-        const bool ok = work && rr < mJ;
-        bp[u] = ok ? a : make_double2(0.0, 0.0);
-        bq[u] = ok ? b : make_double2(0.0, 0.0);
-      }
-      const double al = nrm[p], be = nrm[q];
-      double gr = 0.0, gi = 0.0;
-#pragma unroll
-      for (int u = 0; u < RPL; ++u) {
-        const double2 gg = cmulc(bp[u], bq[u]);
-        gr += gg.x;
-        gi += gg.y;
-      }
-      asm volatile("" ::"v"(al), "v"(be));  // keeps the norm loads beside the row loads
-      group_sum2_dpp(gr, gi, LJ);
-      if (work) {
-        const double g2 = gr * gr + gi * gi;
-        if (g2 > tol2 * al * be && g2 > floor2) {
-          double2 wp[ACC ? RPL : 1], wq[ACC ? RPL : 1];
-          if (ACC) {
-#pragma unroll
-            for (int u = 0; u < RPL; ++u) {
-              const int rr = jrow(u);
-              wp[u] = W[p][rr];
-              wq[u] = W[q][rr];
-            }
-          }
-          // The rotation of smaller angle (|theta| <= pi/4) with tan 2 theta = 2|g| / (be - al):
-          // h = (d^2 + 4|g|^2)^1/2, d = be - al, x = cos^2 theta = (1 + |d| / h) / 2, and
-          // c = x^1/2, s e^{i phi} = sign(d) g / (h x^1/2), so c^2 + |s|^2 = 1 exactly in exact
-          // arithmetic and |g| itself is never formed.  Two reciprocal square roots (two Newton
-          // steps each; one on the complex64 path) are the whole dependent chain.
-          const double d = be - al;
-          const double h2 = d * d + 4.0 * g2;
-          const double rh = PRE ? rsq_nr1(h2) : rsq_nr(h2);  // 1 / h
-          const double x = 0.5 + 0.5 * fabs(d) * rh;
-          const double rc = PRE ? rsq_nr1(x) : rsq_nr(x);    // 1 / c
-          const double cs = x * rc;
-          const double f = (d < 0.0 ? -rh : rh) * rc;
-          const double2 sph = make_double2(gr * f, gi * f);  // s e^{i phi}
-          const double tg = g2 * f * rc;                      // t |g| = sign(d) |g|^2 / (h c^2)
-          // b_p' = c b_p - s e^{-i phi} b_q ;  b_q' = s e^{i phi} b_p + c b_q
-#pragma unroll
-          for (int u = 0; u < RPL; ++u) {
-            const int rr = jrow(u);
-            if (rr < mJ) {
-              B[p][rr] = csub(cscale(bp[u], cs), cmulc(sph, bq[u]));
-              B[q][rr] = cadd(cmul(sph, bp[u]), cscale(bq[u], cs));
-            }
-          }
-          if (ACC) {
-#pragma unroll
-            for (int u = 0; u < RPL; ++u) {
-              const int rr = jrow(u);
-              if (rr < nB) {
-                W[p][rr] = csub(cscale(wp[u], cs), cmulc(sph, wq[u]));
-                W[q][rr] = cadd(cmul(sph, wp[u]), cscale(wq[u], cs));
-              }
-            }
-          }
-          if (lane == 0) {
-            nrm[p] = al - tg;
-            nrm[q] = be + tg;
-            sh_rot = 1;
-            if (g2 > kJacobiQuiet * al * be) sh_big = 1;
-          }
-        }
-      }
-      if (pair_id != 0) pa = (pa == np - 1) ? 1 : pa + 1;
-      pb = (pb == np - 1) ? 1 : pb + 1;
-      __syncthreads();
-    }
-    // complex64 path: a sweep whose rotations all had |g|^2 <= 1e-12 al be leaves
-    // off-diagonal terms of second order, O(n 1e-12) relative, far below the complex64 storage
-    // rounding, so it ends the iteration without a rotation-free check sweep
-    converged = (sh_rot == 0) || (PRE && sh_big == 0);
-    __syncthreads();
-  }
+    };
+    constexpr int kHalf = NMAX == 32 ? RPL / 2 : RPL;
+    if (kHalf < RPL && nB <= LJ * kHalf) sweeps(std::integral_constant<int, kHalf>());
+    else sweeps(std::integral_constant<int, RPL>());
   }
   if (tid == 0) {
     atomicAdd(reinterpret_cast<unsigned long long*>(st.stats) + 0, (unsigned long long)sweep);
@@ -1167,7 +1199,7 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
     for (int u = 0; u < RPL; ++u) {
       const int rr = jrow(u);
       const double2 t = B[c][rr];
-      if (c < nB && rr < mJ) s2 += cabs2(t);
+      if (c < nB && rr < nB) s2 += cabs2(t);
     }
     s2 = group_sum_dpp(s2, LJ);
     if (lane == 0 && c < nB) sig[c] = sqrt(s2);
@@ -1213,20 +1245,9 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
     double2* Vg = st.bV + (int64_t)slot * ld * ld;
     const double smax = sig[perm[0]];
     for (int k = tid; k < nB; k += NT) st.bS[(int64_t)slot * ld + k] = sig[perm[k]];
-    if (ACC) {
-      for (int idx = tid; idx < mB * nB; idx += NT) {
-        const int rr = idx / nB, k = idx - (idx / nB) * nB;
-        const double sv = sig[perm[k]];
-        const double2 bv = sv > 1e-13 * smax ? cscale(B[perm[k]][rr], 1.0 / sv) : make_double2(0.0, 0.0);
-        (trans ? Vg : Ug)[rr * ld + k] = bv;
-      }
-      for (int idx = tid; idx < nB * nB; idx += NT) {
-        const int rr = idx / nB, k = idx - (idx / nB) * nB;
-        (trans ? Ug : Vg)[rr * ld + k] = W[perm[k]][rr];
-      }
-    } else {
-      // preconditioned path: the Jacobi side is B's right singular vectors (rows permuted by the
-      // pivoting), i.e. V of Theta' when B = Theta', U when B = Theta'^H
+    {
+      // the Jacobi side is B's right singular vectors (rows permuted by the ordering), i.e. V of
+      // Theta' when B = Theta', U when B = Theta'^H
       for (int idx = tid; idx < nB * nB; idx += NT) {
         const int rr = idx / nB, k = idx - (idx / nB) * nB;
         const double sv = sig[perm[k]];
@@ -1234,6 +1255,64 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
         (trans ? Ug : Vg)[colid[rr] * ld + k] = bv;
       }
     }
+  }
+
+  // complex128 path: Q W, the left singular vectors of B, in registers: group kc (LC lanes) takes
+  // column kc of the sorted order (and, for the reverse sweep, kc + DM before it) and applies the
+  // reflectors, last one first.  Done before the T matrices take the reflectors' place.
+  constexpr int LC = NT / DM;
+  constexpr int RC = NMAX / LC;
+  const int kc = tid / LC, lc = tid - (tid / LC) * LC;
+  double2 qw[ACC ? RC : 1];
+  if constexpr (ACC) {
+    const double2* const refl = reinterpret_cast<const double2*>(st.tbuf) + rbuf_off(st, slot, 0, 0);
+    for (int batch = BWD ? 1 : 0; batch >= 0; --batch) {
+      const int k = kc + batch * DM;
+      const int col = perm[k < nB ? k : 0];
+#pragma unroll
+      for (int u = 0; u < RC; ++u) {
+        const int rr = lc + LC * u;
+        const double2 t = W[col][rr];
+        qw[u] = (k < nB && rr < nB) ? t : make_double2(0.0, 0.0);
+      }
+      double2 nv[RC];  // the next reflector, in flight
+      auto fetch = [&](int j) {
+#pragma unroll
+        for (int u = 0; u < RC; ++u) {
+          const int rr = lc + LC * u;
+          nv[u] = rr < mB ? refl[j * mB + rr] : make_double2(0.0, 0.0);
+        }
+      };
+      const int nr = small_sq ? 0 : nB;
+      if (nr) fetch(nr - 1);
+      for (int j = nr - 1; j >= 0; --j) {
+        double2 v[RC];
+#pragma unroll
+        for (int u = 0; u < RC; ++u) v[u] = nv[u];
+        if (j > 0) fetch(j - 1);
+        double wr = 0.0, wi = 0.0;
+#pragma unroll
+        for (int u = 0; u < RC; ++u) {
+          const double2 t = cmulc(v[u], qw[u]);
+          wr += t.x;
+          wi += t.y;
+        }
+        group_sum2_dpp(wr, wi, LC);
+        const double2 f = make_double2(wr, wi);
+#pragma unroll
+        for (int u = 0; u < RC; ++u) qw[u] = csub(qw[u], cmul(v[u], f));
+      }
+      if (BWD && k < nB) {
+        const int ld = 2 * D;
+        double2* Og = (trans ? st.bV : st.bU) + (int64_t)slot * ld * ld;
+#pragma unroll
+        for (int u = 0; u < RC; ++u) {
+          const int rr = lc + LC * u;
+          if (rr < mB) Og[rr * ld + k] = qw[u];
+        }
+      }
+    }
+    __syncthreads();  // every reflector has been read
   }
 
   CT* T = reinterpret_cast<CT*>(st.tbuf);
@@ -1258,20 +1337,16 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
   };
 
   if (ACC) {
-    // both vector sets are available: U / V from B and W, straight into the arena
-    double2 uv[2 * RPT];
+    // both vector sets into the arenas: B's right vectors from the orthogonalised columns (rows
+    // permuted by the ordering), its left ones from Q W
+    double2 uv[RPT];
 #pragma unroll
     for (int u = 0; u < RPT; ++u) {
       const int idx = tid + u * NT;
       uv[u] = make_double2(0.0, 0.0);
-      uv[RPT + u] = make_double2(0.0, 0.0);
-      if (idx < mB * chi) {
-        const int rr = idx / chi, kp = idx - (idx / chi) * chi;
-        uv[u] = cscale(B[perm[kp]][rr], 1.0 / sig[perm[kp]]);
-      }
       if (idx < nB * chi) {
         const int rr = idx / chi, kp = idx - (idx / chi) * chi;
-        uv[RPT + u] = W[perm[kp]][rr];
+        uv[u] = cscale(B[perm[kp]][rr], 1.0 / sig[perm[kp]]);
       }
     }
     __syncthreads();
@@ -1280,14 +1355,15 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
 #pragma unroll
     for (int u = 0; u < RPT; ++u) {
       const int idx = tid + u * NT;
-      if (idx < mB * chi) {
-        const int rr = idx / chi, kp = idx - (idx / chi) * chi;
-        (trans ? Vl : Ul)[rr * DS + kp] = uv[u];
-      }
       if (idx < nB * chi) {
         const int rr = idx / chi, kp = idx - (idx / chi) * chi;
-        (trans ? Ul : Vl)[rr * DS + kp] = uv[RPT + u];
+        (trans ? Ul : Vl)[colid[rr] * DS + kp] = uv[u];
       }
+    }
+#pragma unroll
+    for (int u = 0; u < RC; ++u) {
+      const int rr = lc + LC * u;
+      if (kc < chi && rr < mB) (trans ? Vl : Ul)[rr * DS + kc] = qw[u];
     }
     __syncthreads();
     stage_r(A1, 0, ri);
