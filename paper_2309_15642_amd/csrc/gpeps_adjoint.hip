@@ -109,52 +109,64 @@ __global__ __launch_bounds__(256) void k_seed_mean(DevState st) {
 
 // z_v = (rho00 - rho11)/(rho00 + rho11), rho_ss = sum_x |Gamma[s,x]|^2 W(x), W = prod_l lambda_l[x_l]^2.
 template <typename CT>
-__global__ __launch_bounds__(256) void k_adj_readout(DevState st) {
+__global__ __launch_bounds__(1024) void k_adj_readout(DevState st) {
+  constexpr int NT = 1024;  // one large tensor per workgroup: bound by the loads it has in flight
   const int v = blockIdx.x;
   const VertexInfo& V = st.verts[v];
-  const int D = st.D;
+  const int D = st.D, deg = V.deg;
   __shared__ double lw[kMaxDeg][kMaxD];
   __shared__ double acc[kMaxDeg][kMaxD];
-  __shared__ double red[256];
+  __shared__ double red0[NT / 64], red1[NT / 64];
   const int tid = threadIdx.x;
-  for (int idx = tid; idx < kMaxDeg * D; idx += blockDim.x) {
+  for (int idx = tid; idx < kMaxDeg * D; idx += NT) {
     const int l = idx / D, k = idx - (idx / D) * D;
     double w = 1.0;
-    if (l < V.deg) {
+    if (l < deg) {
       const double x = st.lam[(int64_t)V.leg[l] * D + k];
       w = x * x;
     }
     lw[l][k] = w;
-    acc[l][k] = 0.0;
   }
   __syncthreads();
-  int64_t ps = 1;
-  for (int l = 0; l < V.deg; ++l) ps *= D;
+  int ps = 1;
+  for (int l = 0; l < deg; ++l) ps *= D;
+  const int s0 = deg == 3 ? D * D : deg == 2 ? D : 1, s1 = deg == 3 ? D : 1;  // strides of legs 0 and 1
+  auto weight = [&](int i) {
+    double w = 1.0;
+    if (deg >= 1) w = lw[0][i / s0];
+    const int r = i - (i / s0) * s0;
+    if (deg >= 2) w *= lw[1][r / s1];
+    if (deg >= 3) w *= lw[2][r - (r / s1) * s1];
+    return w;
+  };
   const CT* gam = reinterpret_cast<const CT*>(st.gamma) + V.goff;
   double r0 = 0.0, r1 = 0.0;
-  for (int64_t i = tid; i < ps; i += blockDim.x) {
-    double w = 1.0;
-    int64_t rest = i;
-    for (int l = V.deg - 1; l >= 0; --l) {
-      w *= lw[l][(int)(rest % D)];
-      rest /= D;
-    }
+#pragma unroll 4
+  for (int i = tid; i < ps; i += NT) {
+    const double w = weight(i);
     r0 += cabs2(to_d2(gam[i])) * w;
     r1 += cabs2(to_d2(gam[i + ps])) * w;
   }
-  const double rho0 = block_sum<256>(r0, red);
-  const double rho1 = block_sum<256>(r1, red);
+  r0 = group_sum_dpp(r0, 64);
+  r1 = group_sum_dpp(r1, 64);
+  if ((tid & 63) == 0) {
+    red0[tid >> 6] = r0;
+    red1[tid >> 6] = r1;
+  }
+  __syncthreads();
+  double rho0 = 0.0, rho1 = 0.0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) {
+    rho0 += red0[w];
+    rho1 += red1[w];
+  }
   const double c = st.dldz[v];
   const double den = (rho0 + rho1) * (rho0 + rho1);
   const double d0 = c * 2.0 * rho1 / den, d1 = -c * 2.0 * rho0 / den;
   double2* gb = st.gbar + V.goff;
-  for (int64_t i = tid; i < ps; i += blockDim.x) {
-    double w = 1.0;
-    int64_t rest = i;
-    for (int l = V.deg - 1; l >= 0; --l) {
-      w *= lw[l][(int)(rest % D)];
-      rest /= D;
-    }
+#pragma unroll 4
+  for (int i = tid; i < ps; i += NT) {
+    const double w = weight(i);
     const double2 a = to_d2(gam[i]), b = to_d2(gam[i + ps]);
     gb[i] = cscale(a, 2.0 * d0 * w);
     gb[i + ps] = cscale(b, 2.0 * d1 * w);
@@ -163,31 +175,25 @@ __global__ __launch_bounds__(256) void k_adj_readout(DevState st) {
   // (d0 |G0|^2 + d1 |G1|^2) w.  The waves take the (l, k) bins in turn; lane j sums the bin's
   // elements j, j + 64, ... and a DPP wave sum adds the lanes, both in a fixed order, so the
   // gradient is bitwise reproducible.
-  {
-    const int inner = (int)(ps / D);
-    const int lane = tid & 63, wv = tid >> 6;
-    for (int bin = wv; bin < V.deg * D; bin += 4) {
-      const int l = bin / D, k = bin - (bin / D) * D;
-      int sl = 1;  // stride of leg l
-      for (int l2 = l + 1; l2 < V.deg; ++l2) sl *= D;
-      double sacc = 0.0;
+  const int inner = deg ? ps / D : 0;
+  const int lane = tid & 63;
+  for (int bin = tid >> 6; bin < deg * D; bin += NT / 64) {
+    const int l = bin / D, k = bin - (bin / D) * D;
+    const int sl = l == 0 ? s0 : l == 1 ? s1 : 1;  // stride of leg l
+    double sacc = 0.0;
+    if (lw[l][k] != 0.0) {  // the tensor is zero past a leg's active indices
+#pragma unroll 4
       for (int j = lane; j < inner; j += 64) {
         const int hi = j / sl, lo = j - (j / sl) * sl;  // digits above and below leg l
         const int i = (hi * D + k) * sl + lo;
-        double w = 1.0;
-        int rest = i;
-        for (int l2 = V.deg - 1; l2 >= 0; --l2) {
-          w *= lw[l2][rest % D];
-          rest /= D;
-        }
-        sacc += (d0 * cabs2(to_d2(gam[i])) + d1 * cabs2(to_d2(gam[i + ps]))) * w;
+        sacc += (d0 * cabs2(to_d2(gam[i])) + d1 * cabs2(to_d2(gam[i + ps]))) * weight(i);
       }
-      sacc = group_sum_dpp(sacc, 64);
-      if (lane == 0) acc[l][k] = sacc;
     }
+    sacc = group_sum_dpp(sacc, 64);
+    if (lane == 0) acc[l][k] = sacc;
   }
   __syncthreads();
-  for (int idx = tid; idx < V.deg * D; idx += blockDim.x) {
+  for (int idx = tid; idx < deg * D; idx += NT) {
     const int l = idx / D, k = idx - (idx / D) * D;
     const double lam = st.lam[(int64_t)V.leg[l] * D + k];
     if (lam > 0.0 && acc[l][k] != 0.0) atomicAdd(&st.lbar[(int64_t)V.leg[l] * D + k], acc[l][k] * 2.0 / lam);
@@ -975,7 +981,7 @@ static hipError_t adj_launch(int which, const DevState& st, const int32_t* items
       hipLaunchKernelGGL(k_adj_theta, dim3(st.n_inst), dim3(256), 0, stream, st, count);
       break;
     case 4:  // readout seed over all vertices
-      hipLaunchKernelGGL(k_adj_readout<CT>, dim3(st.NV), dim3(256), 0, stream, st);
+      hipLaunchKernelGGL(k_adj_readout<CT>, dim3(st.NV), dim3(1024), 0, stream, st);
       break;
     case 5:  // RX adjoint over `count` chunks starting at `first`; aux = pre-RX site tensors
       if (count <= 0) return hipSuccess;

@@ -57,7 +57,7 @@ struct Layout {
   std::vector<int32_t> rlist;               // per class: (slot * 2 + end), light ends stored first
   std::vector<int> rl_begin, rl_light, rl_heavy;
   std::vector<int64_t> chunks;             // RX chunk table
-  std::vector<int32_t> bp_order;           // directed edges (2 e + end) of BP, senders with most legs first
+  size_t bp_order = 0;                      // where rlist holds BP's directed edges (d_max <= 32)
   std::vector<int> inst_chunk_begin, inst_chunk_end;
   std::vector<int> inst_vert_begin, inst_vert_end;
   std::vector<int> inst_edge_begin;
@@ -71,7 +71,7 @@ struct Layout {
          off_gbar = 0, off_lbar = 0, off_thbar = 0, off_dldz = 0, off_bU = 0, off_bV = 0, off_bS = 0, off_t64 = 0,
          off_wsb = 0, off_ybuf = 0, off_ymode = 0, state_bytes = 0, state_slot = 0, off_z = 0, off_hist = 0, off_ctr = 0, off_chunks = 0,
          off_bp = 0, off_bpres = 0, off_ivb = 0, off_mean = 0, off_dldm = 0, off_big = 0, off_gpart = 0,
-         off_wbar = 0, off_rlist = 0, off_bporder = 0;
+         off_wbar = 0, off_rlist = 0;
   size_t total = 0;
 };
 
@@ -385,12 +385,14 @@ gpeps_status build_layout(const gpeps_graph* graphs, int32_t n_graphs, const int
       (pass == 0 ? L.rl_light : L.rl_heavy)[c] = n;
     }
   }
-  // BP's directed edges by falling degree of the sender: a sender with three legs costs D times one
-  // with two, and the dear workgroups have to start first to share the CUs evenly
-  L.bp_order.reserve((size_t)2 * L.NE);
-  for (int deg = kMaxDeg; deg >= 1; --deg)
-    for (int i = 0; i < 2 * L.NE; ++i)
-      if (L.edges[i >> 1].side[i & 1].deg == deg) L.bp_order.push_back(i);
+  // after them BP's directed edges (2 e + end) by falling degree of the sender: a sender with three
+  // legs costs D times one with two, and the dear workgroups have to start first to share the CUs
+  // evenly
+  L.bp_order = L.rlist.size();
+  if (D <= kMaxD)
+    for (int deg = kMaxDeg; deg >= 1; --deg)
+      for (int i = 0; i < 2 * L.NE; ++i)
+        if (L.edges[i >> 1].side[i & 1].deg == deg) L.rlist.push_back(i);
   const size_t slots = std::max(L.max_items, 1);
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -425,7 +427,6 @@ gpeps_status build_layout(const gpeps_graph* graphs, int32_t n_graphs, const int
   L.off_bp = take(D <= kMaxD ? (size_t)2 * 2 * L.NE * D * D * sizeof(double2) : 0);
   // scratch of the two-site SVD for bond dimensions above 32 (Theta' and one vector set per item)
   L.off_big = take(D > kMaxD ? slots * (size_t)big_scratch((int)D) * sizeof(double2) : 0);
-  L.off_bporder = take(L.bp_order.size() * sizeof(int32_t));
   L.off_bpres = take(sizeof(unsigned long long));
   L.off_chunks = take(L.chunks.size() * sizeof(int64_t));
   L.off_ivb = take(((size_t)n_instances + 1) * sizeof(int32_t));
@@ -847,7 +848,7 @@ gpeps_status gpeps_init(gpeps_ctx** out, const gpeps_graph* graphs, int32_t n_gr
   st.hist = reinterpret_cast<double*>(ws + L.off_hist);
   st.step_ctr = reinterpret_cast<int32_t*>(ws + L.off_ctr);
   st.bp_msg = reinterpret_cast<double2*>(ws + L.off_bp);
-  st.bp_order = reinterpret_cast<const int32_t*>(ws + L.off_bporder);
+  st.bp_order = c->d_rlist + L.bp_order;
   st.bp_res = reinterpret_cast<unsigned long long*>(ws + L.off_bpres);
   st.status = st.step_ctr + 1;
   st.chunks = reinterpret_cast<const int64_t*>(ws + L.off_chunks);
@@ -898,7 +899,6 @@ gpeps_status gpeps_init(gpeps_ctx** out, const gpeps_graph* graphs, int32_t n_gr
   if (e == hipSuccess) e = h2d(L.off_inst, both.data(), both.size() * sizeof(InstParam));
   if (e == hipSuccess) e = h2d(L.off_items, L.items.data(), L.items.size() * sizeof(int32_t));
   if (e == hipSuccess) e = h2d(L.off_rlist, L.rlist.data(), L.rlist.size() * sizeof(int32_t));
-  if (e == hipSuccess) e = h2d(L.off_bporder, L.bp_order.data(), L.bp_order.size() * sizeof(int32_t));
   if (e == hipSuccess) e = h2d(L.off_chunks, L.chunks.data(), L.chunks.size() * sizeof(int64_t));
   std::vector<int32_t> ivb(L.inst_vert_begin.begin(), L.inst_vert_begin.end());
   ivb.push_back(L.NV);
