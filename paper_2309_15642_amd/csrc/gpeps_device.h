@@ -209,6 +209,12 @@ __device__ __forceinline__ double rcp_nr(double x) {
   return r;
 }
 
+// One Newton step only (the estimate is good to 4.6e-8): relative error ~2e-15.
+__device__ __forceinline__ double rcp_nr1(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  return r * (2.0 - x * r);
+}
+
 // RZZ(theta_J) phase g(s,t) = exp(-i theta_J z_s z_t / 2), z_0 = +1, z_1 = -1.
 __device__ __forceinline__ double2 gate_phase(const InstParam& ip, int s, int t) {
   const double zz = (s == t) ? 1.0 : -1.0;

@@ -450,24 +450,28 @@ constexpr int kSmallB = 8;                  // largest square B that skips the Q
 constexpr double kJacobiQuietC128 = 1e-16;  // (1e-8)^2: the same for the complex128 path
 
 template <typename CT, int NT, int NMAX, bool ACC_, bool BWD = false>
-__global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd(DevState st, const int32_t* __restrict__ items, int first) {
+__global__ __launch_bounds__(NT, NMAX == 32 ? NT / 64 : ACC_ ? 1 : 2) void k_theta_svd(DevState st, const int32_t* __restrict__ items, int first) {
   constexpr bool ACC = ACC_;
   constexpr int DM = NMAX / 2;             // largest bond dimension handled
   constexpr int EPT = NMAX * NMAX / NT;    // Theta' entries per thread (16)
   constexpr int RPT = NMAX * DM / NT;      // singular-vector entries per thread (8)
-  constexpr int KPT = (DM * DM + NT - 1) / NT;  // (k, k') pairs per thread (4)
   constexpr int RPL = NMAX * NMAX / (2 * NT);  // rows per lane of a Jacobi column pair (upper bound)
   static_assert(2 * NT / NMAX <= 64 && RPL * (2 * NT / NMAX) >= NMAX, "Jacobi rows must fit RPL per lane");
   constexpr int DS = DM + 1;               // padded row stride of the staging arena (no bank conflicts)
-  // B: column-major B[col][row], column stride NMAX (a 16-lane group reading 16 consecutive rows
-  // covers all 64 LDS banks once; lane groups that share an LDS cycle start on different row
-  // blocks, below).  The same memory is the staging arena of 4 DM DS elements.
-  constexpr int kBsz = NMAX * NMAX > 4 * DM * DS ? NMAX * NMAX : 4 * DM * DS;
+  // B: column-major B[col][row].  A 16-lane LDS cycle covers all 64 banks once when it reads 16
+  // consecutive rows of a column (the Jacobi lane groups at NMAX = 32); the stride at NMAX = 64
+  // makes two rows of 8 consecutive columns conflict-free too (the lane groups there), and leaves
+  // the Gram products (one row of 16 columns) two-way conflicts instead of 16-way ones: the
+  // preconditioning phase 185 -> 160 k cycles.  (An odd stride at NMAX = 32 cost one instance 0.5 us
+  // a launch and 128 of them 1 %.)  The same memory is the staging arena of 4 DM DS elements.
+  constexpr int BST = NMAX == 32 ? NMAX : NMAX + 2;
+  constexpr int kBsz = NMAX * BST > 4 * DM * DS ? NMAX * BST : 4 * DM * DS;
   __shared__ double2 Bmem[kBsz];
   __shared__ double2 Wmem[ACC ? kBsz : 1];  // accumulated rotations W[col][row] (ACC only), also an arena
-  double2 (*const B)[NMAX] = reinterpret_cast<double2 (*)[NMAX]>(Bmem);
-  double2 (*const W)[NMAX] = reinterpret_cast<double2 (*)[NMAX]>(Wmem);
+  double2 (*const B)[BST] = reinterpret_cast<double2 (*)[BST]>(Bmem);
+  double2 (*const W)[BST] = reinterpret_cast<double2 (*)[BST]>(Wmem);
   __shared__ double nrm[NMAX];
+  __shared__ double scl[NMAX];  // squared scale of a column of B (and W) during the Jacobi sweeps
   __shared__ double lam_old[kMaxD];
   __shared__ double sig[NMAX];
   __shared__ int perm[NMAX];
@@ -984,25 +988,63 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
     // round is a perfect matching.  The rounds run in blocks of equal highest bit hb of m: inside
     // a block the column of the pair with bit hb clear stays in the registers of its lane group
     // g = c with bit hb deleted, and its partner (bit hb set) sits in group
-    // g = (c ^ m) with bit hb deleted.  With the low bits m' = m - 2^hb taken in Gray-code
-    // order, consecutive rounds differ in one bit b of m', so every moving column passes to
-    // group g ^ 2^b: a lane permutation (lane ^ LJ 2^b) inside a wave, an LDS store, barrier and
-    // load across waves.  Between blocks (and at the end of every sweep) all columns are written
-    // to B and re-read under the next block's assignment.  With ACC the columns of W travel with
+    // g = (c ^ m) with bit hb deleted.  Between rounds the moving columns change groups so that
+    // each visits every stationary one of its block once.  GW = 64 / LJ groups share a wave:
+    //   LJ = 16: the lanes of a group are consecutive (its sums are four DPP levels, the shortest
+    // chain: this size is bound by latency), and the low bits m' of m go through a Gray code,
+    // so that a column moves by lane ^ 16 or ^ 32 (v_permlane swaps);
+    //   LJ = 8, 4: the lanes of a group are spread over l / 16, the group index inside the wave is
+    // (blk, low), blk in lane bits 2 and 3, low in the upper bits of the lane's quad.  low walks
+    // through a Gray code (DPP quad permutation), blk rotates (DPP row_ror:4): one DPP instruction
+    // a word, 5.5 cycles of issue against 8.6 of a v_permlane swap, and the moves are most of the
+    // words.  In blocks of fewer than GW rounds blk moves by lane ^ 4.
+    // After GW rounds the columns pass to the wave whose index differs in one bit (Gray code)
+    // through LDS.  Between blocks (and at the end of every sweep) all columns are written to B
+    // and re-read under the next block's assignment.  With ACC the columns of W travel with
     // those of X.
     //   The rotation of smaller angle (|theta| <= pi/4) with tan 2 theta = 2|g| / (be - al):
-    // h = (d^2 + 4|g|^2)^1/2, d = be - al, x = cos^2 theta = (1 + |d| / h) / 2, and
-    // c = x^1/2, s e^{i phi} = sign(d) g / (h x^1/2), so c^2 + |s|^2 = 1 exactly in exact
-    // arithmetic and |g| itself is never formed.
-    constexpr int GW = 64 / LJ;  // lane groups per wave
+    // h = (d^2 + 4|g|^2)^1/2, d = be - al, x = cos^2 theta = (1 + |d| / h) / 2; |g| itself is never
+    // formed.
+    //   LJ = 16: c = x^1/2 and s e^{i phi} = sign(d) g / (h x^1/2), the shorter chain.
+    //   LJ = 8, 4 (more rows a lane, bound by issue): tan theta e^{i phi} = g F, F = sign(d) / (h x),
+    // and the columns carry a scale: the column is sqrt(ps) xs, a rotation is
+    // xs -= conj(g F) pm xm, xm += g F ps xs (g the inner product of the scaled columns) with both
+    // squared scales times x: 8 instead of 12 operations per complex pair of entries.  The scales
+    // are folded in at the start of a sweep and after the last one.  The inner products are summed
+    // with v_mfma_f64_4x4x4_4b_f64 against ones (lane l supplies A[l % 4][l / 16] and
+    // B[l / 16][l % 4] of block (l / 4) % 4 and receives D[l / 16][l % 4]).
+    //   32 instances at D = 32, per launch: 1188 us with the LJ = 16 forms at LJ = 8, 1186 with the
+    // sums on the matrix cores alone, 1164 with the scales alone, 1138 with both (101.9 k cycles a
+    // sweep of 63 rounds, two workgroups a CU).  At D = 16, one instance, the LJ = 8 forms took
+    // 87.7 us against 83.
+    constexpr int GW = 64 / LJ;                         // lane groups per wave
+    constexpr int LB = LJ == 16 ? 0 : LJ == 8 ? 1 : 2;  // bits of low
+    constexpr bool kSpread = LJ != 16;
+    static_assert(GW == 4 << LB, "lane groups");
+    const int wl = tid & 63;
+    const int jgrp = kSpread ? (tid >> 6) * GW + ((((wl >> 2) & 3) << LB) | ((wl & 3) >> (2 - LB))) : tid / LJ;
+    const int jlane = kSpread ? (wl & ((4 >> LB) - 1)) + (4 >> LB) * (wl >> 4) : tid & (LJ - 1);
+    const double own = ((wl >> 4) >> 1) == ((wl & 3) >> 1) ? 1.0 : 0.0;  // LJ = 8: the two groups of a block apart
     int K = 1;
     while ((1 << K) < nB) ++K;
-    const bool gact = pair_id < (1 << (K - 1));
+    const bool gact = jgrp < (1 << (K - 1));
     // a wave whose groups are all inactive takes part in the barriers only (uniform over the wave;
     // at NMAX = 64 only the first steps have such waves, and the test costs the others 0.7 %)
-    const bool wact = NMAX == 64 || (__builtin_amdgcn_readfirstlane(tid) / LJ) < (1 << (K - 1));
+    const bool wact = NMAX == 64 || (__builtin_amdgcn_readfirstlane(tid) >> 6) * GW < (1 << (K - 1));
     auto ins = [](int g, int hb, int bit) { return ((g >> hb) << (hb + 1)) | (bit << hb) | (g & ((1 << hb) - 1)); };
-    auto xrow = [&](int u) { return lane + LJ * u; };
+    auto xrow = [&](int u) { return jlane + LJ * u; };
+    auto group_total2 = [&](double& a, double& b) {
+      if constexpr (!kSpread) {
+        group_sum2_dpp(a, b, LJ);
+      } else {
+        if constexpr (LJ == 8) {
+          a = own * __builtin_amdgcn_mfma_f64_4x4x4f64(a, 1.0, 0.0, 0, 0, 0);  // sum over l / 16 of l % 4 = i, in D[i][j]
+          b = own * __builtin_amdgcn_mfma_f64_4x4x4f64(b, 1.0, 0.0, 0, 0, 0);
+        }
+        a = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, a, 0.0, 0, 0, 0);
+        b = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, b, 0.0, 0, 0, 0);
+      }
+    };
     // per-sweep flags (any rotation, any rotation above the quiet level), three sets in
     // rotation so that a set is cleared neither while it is read nor after it is written
     __shared__ int sh_flag[3][2];
@@ -1011,6 +1053,8 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
     // their tracked norms are zero too (store_col never writes them), which keeps the rotation
     // scalars of every pair finite
     for (int c = nB + tid; c < NMAX; c += NT) nrm[c] = 0.0;
+    if (kSpread)
+      for (int c = tid; c < NMAX; c += NT) scl[c] = 1.0;
     __syncthreads();
     // RB row blocks of LJ rows: a matrix of at most half the rows leaves the upper half of them out
     auto sweeps = [&](auto row_blocks) {
@@ -1018,6 +1062,7 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
       double2 xs[RB], xm[RB];  // stationary and moving column of the group
       double2 us[ACC ? RB : 1], um[ACC ? RB : 1];  // and the columns of W that go with them
       double ns = 0.0, nm = 0.0;  // their tracked squared norms
+      double ps = 1.0, pm = 1.0;  // their squared scales
       int cs_id = 0, cm_id = 0;   // their column indices
       auto load_col = [&](double2 (&x)[RB], double2 (&w)[ACC ? RB : 1], int c) {
 #pragma unroll
@@ -1031,7 +1076,7 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
           }
         }
       };
-      auto store_col = [&](const double2 (&x)[RB], const double2 (&w)[ACC ? RB : 1], int c, double n2) {
+      auto store_col = [&](const double2 (&x)[RB], const double2 (&w)[ACC ? RB : 1], int c, double n2, double p2) {
         if (gact && c < nB) {
 #pragma unroll
           for (int u = 0; u < RB; ++u) {
@@ -1041,49 +1086,84 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
               if constexpr (ACC) W[c][rr] = w[u];
             }
           }
-          if (lane == 0) nrm[c] = n2;
+          if (jlane == 0) {
+            nrm[c] = n2;
+            if (kSpread) scl[c] = p2;
+          }
         }
       };
-      auto col_norm = [&](const double2 (&x)[RB]) {
+      // the scale of a column folded in: its squared norm, with the scale back at 1
+      auto fold = [&](double2 (&x)[RB], double2 (&w)[ACC ? RB : 1], double& p2) {
+        if constexpr (kSpread) {
+          const double d = p2 * rsq_nr(p2);
+#pragma unroll
+          for (int u = 0; u < RB; ++u) {
+            x[u] = cscale(x[u], d);
+            if constexpr (ACC) w[u] = cscale(w[u], d);
+          }
+          p2 = 1.0;
+        }
         double s2 = 0.0;
 #pragma unroll
         for (int u = 0; u < RB; ++u) s2 += cabs2(x[u]);
-        return group_sum_dpp(s2, LJ);
+        return s2;
       };
       bool rot = false, big = false;
       const double floor2 = sh_floor * sh_floor;
       for (; sweep < st.max_sweeps && !converged; ++sweep) {
         for (int hb = 0; hb < K; ++hb) {
-          cs_id = ins(pair_id, hb, 0);
-          cm_id = ins(pair_id, hb, 1);
+          cs_id = ins(jgrp, hb, 0);
+          cm_id = ins(jgrp, hb, 1);
           load_col(xs, us, cs_id);
           load_col(xm, um, cm_id);
+          if (kSpread) {
+            ps = scl[cs_id];
+            pm = scl[cm_id];
+          }
           if (hb == 0) {
-            ns = col_norm(xs);
-            nm = col_norm(xm);
+            ns = fold(xs, us, ps);
+            nm = fold(xm, um, pm);
+            group_total2(ns, nm);
           } else {
             ns = nrm[cs_id];
             nm = nrm[cm_id];
           }
           const int nt = 1 << hb;
-          // the moving column passes to group pair_id ^ 2^bb (lane ^ LJ 2^bb inside a wave)
-          auto move_intra = [&](auto tag) {
-            constexpr int OFF = decltype(tag)::value;
+          // the moving column (with its norm and scale where the columns carry one) through one lane
+          // permutation
+          auto move = [&](auto perm2) {
 #pragma unroll
             for (int u = 0; u < RB; ++u) {
-              lane_xor_pair<OFF>(xm[u].x, xm[u].y);
-              if constexpr (ACC) lane_xor_pair<OFF>(um[u].x, um[u].y);
+              perm2(xm[u].x, xm[u].y);
+              if constexpr (ACC) perm2(um[u].x, um[u].y);
             }
-            nm = lane_xor<OFF>(nm);
+            if constexpr (kSpread) perm2(nm, pm);
           };
-          auto move_off = [&](int off) {
-            if (off == 4) move_intra(std::integral_constant<int, 4>());
-            else if (off == 8) move_intra(std::integral_constant<int, 8>());
-            else if (off == 16) move_intra(std::integral_constant<int, 16>());
-            else move_intra(std::integral_constant<int, 32>());
+          auto move_low = [&](int bit) {  // low ^ 2^bit
+            if (LB == 2 && bit == 0) move([](double& a, double& b) { a = dpp_d<0xB1>(a); b = dpp_d<0xB1>(b); });  // lane ^ 1
+            else move([](double& a, double& b) { a = dpp_d<0x4E>(a); b = dpp_d<0x4E>(b); });                      // lane ^ 2
+          };
+          auto move_xor = [&](int bit) {  // blocks of fewer than GW rounds, and LJ = 16: group ^ 2^bit
+            if constexpr (!kSpread) {
+              if (bit == 0) {
+                move([](double& a, double& b) { lane_xor_pair<16>(a, b); });
+                nm = lane_xor<16>(nm);
+              } else {
+                move([](double& a, double& b) { lane_xor_pair<32>(a, b); });
+                nm = lane_xor<32>(nm);
+              }
+            } else if (bit < LB) {
+              move_low(bit);
+            } else {
+              move([](double& a, double& b) { a = lane_xor<4>(a); b = lane_xor<4>(b); });
+            }
+          };
+          auto move_blk = [&](int sb) {
+            if constexpr (!kSpread) move_xor(sb & 1);  // bits 0, 1, 0
+            else move([](double& a, double& b) { a = dpp_d<0x124>(a); b = dpp_d<0x124>(b); });  // blk - 1 to blk
           };
           // one round: the rotation of the group's pair (stationary xs, moving xm).  Branch-free:
-          // a pair that is not rotated takes c = 1, s = 0 (f = 0), which leaves both columns and
+          // a pair that is not rotated takes F = 0, x = 1 (s = 0, c = 1), which leaves both columns and
           // norms bit for bit.  Padding columns are exactly zero, so their pairs have g = 0 and are
           // never rotated; h is kept away from zero so that every pair's scalars stay finite.
           auto round = [&]() {
@@ -1091,29 +1171,52 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
 #pragma unroll
             for (int u = 1; u < RB; ++u) g = cadd(g, cmulc(xs[u], xm[u]));
             double gr = g.x, gi = g.y;
-            group_sum2_dpp(gr, gi, LJ);
+            group_total2(gr, gi);
             const double al = ns, be = nm;
-            const double g2 = gr * gr + gi * gi;
+            const double g2 = kSpread ? (gr * gr + gi * gi) * (ps * pm) : gr * gr + gi * gi;
             const double ab = al * be;
             const bool ok = (g2 > tol2 * ab) & (g2 > floor2);
             const double d = be - al;
             const double h2 = fmax(d * d + 4.0 * g2, 1e-300);
             const double rh = ACC ? rsq_nr(h2) : rsq_nr1(h2);  // 1 / h
             const double x = 0.5 + 0.5 * fabs(d) * rh;
-            const double rc = ACC ? rsq_nr(x) : rsq_nr1(x);    // 1 / c
-            const double f = ok ? copysign(rh, d) * rc : 0.0;
-            const double cs = ok ? x * rc : 1.0;
-            const double2 sph = make_double2(gr * f, gi * f);  // s e^{i phi}
-            const double tg = g2 * f * rc;                      // t |g|
+            double tg;  // tan theta |g|
+            if constexpr (kSpread) {
+              const double rx = ACC ? rcp_nr(x) : rcp_nr1(x);  // 1 / x
+              const double F = ok ? copysign(rh, d) * rx : 0.0;
+              const double xx = ok ? x : 1.0;
+              tg = g2 * F;
+              const double fm = F * pm, fs = F * ps;
+              const double2 tm = make_double2(gr * fm, gi * fm), ts = make_double2(gr * fs, gi * fs);
+              auto turn = [&](double2& a, double2& b) {
+                const double2 a0 = a;
+                a.x = fma(-tm.x, b.x, fma(-tm.y, b.y, a.x));
+                a.y = fma(-tm.x, b.y, fma(tm.y, b.x, a.y));
+                b.x = fma(ts.x, a0.x, fma(-ts.y, a0.y, b.x));
+                b.y = fma(ts.x, a0.y, fma(ts.y, a0.x, b.y));
+              };
 #pragma unroll
-            for (int u = 0; u < RB; ++u) {
-              const double2 bp = xs[u], bq = xm[u];
-              xs[u] = csub(cscale(bp, cs), cmulc(sph, bq));
-              xm[u] = cadd(cmul(sph, bp), cscale(bq, cs));
-              if constexpr (ACC) {
-                const double2 wp = us[u], wq = um[u];
-                us[u] = csub(cscale(wp, cs), cmulc(sph, wq));
-                um[u] = cadd(cmul(sph, wp), cscale(wq, cs));
+              for (int u = 0; u < RB; ++u) {
+                turn(xs[u], xm[u]);
+                if constexpr (ACC) turn(us[u], um[u]);
+              }
+              ps *= xx;
+              pm *= xx;
+            } else {
+              const double rc = ACC ? rsq_nr(x) : rsq_nr1(x);  // 1 / c
+              const double f = ok ? copysign(rh, d) * rc : 0.0;
+              const double cs = ok ? x * rc : 1.0;
+              const double2 sph = make_double2(gr * f, gi * f);  // s e^{i phi}
+              tg = g2 * f * rc;
+              auto turn = [&](double2& a, double2& b) {
+                const double2 a0 = a, b0 = b;
+                a = csub(cscale(a0, cs), cmulc(sph, b0));
+                b = cadd(cmul(sph, a0), cscale(b0, cs));
+              };
+#pragma unroll
+              for (int u = 0; u < RB; ++u) {
+                turn(xs[u], xm[u]);
+                if constexpr (ACC) turn(us[u], um[u]);
               }
             }
             ns = al - tg;
@@ -1122,51 +1225,57 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
             big |= ok & (g2 > (ACC ? kJacobiQuietC128 : kJacobiQuietC64) * ab);
           };
           // the moving column of this group in round t of the block
-          auto mid = [&](int t) { return ins(pair_id ^ (t ^ (t >> 1)), hb, 1); };
-          // groups of up to 8 rounds (4 when a lane holds 8 or more rows: straight-line groups
-          // that long take the compiler many minutes for little gain)
-          constexpr int UN = RB >= 8 ? (GW < 4 ? GW : 4) : (GW < 8 ? GW : 8);
-          if (nt < UN) {
-            // short block (2^hb rounds, all moves inside a wave)
+          auto mid = [&](int t) {
+            if (!kSpread || nt < GW) return ins(jgrp ^ (t ^ (t >> 1)), hb, 1);
+            constexpr int ML = (1 << LB) - 1;  // low's Gray code ends at its last value, where the next one starts
+            const int T = t / GW, sb = (t >> LB) & 3, r = t & ML;
+            const int low = (jgrp & ML) ^ (r ^ (r >> 1)) ^ ((sb & 1) ? (ML ^ (ML >> 1)) : 0);
+            const int blk = (((jgrp >> LB) & 3) - (3 * T + sb)) & 3;
+            const int w = (jgrp / GW) ^ (T ^ (T >> 1));
+            return ins((w * 4 + blk) << LB | low, hb, 1);
+          };
+          if (nt < GW) {
             if (wact) {
               for (int t = 0; t < nt; ++t) {
                 round();
-                if (t + 1 < nt) move_off(LJ << __builtin_ctz(t + 1));
+                if (t + 1 < nt) move_xor(__builtin_ctz(t + 1));
               }
             }
           } else {
-            // rounds in groups of UN (nt is a multiple of UN): inside a group the bit that changes
-            // between consecutive rounds, ctz(k + 1), is a compile-time constant and every move is
-            // unconditional straight-line code; only the move after a group can cross waves
-            for (int t0 = 0; t0 < nt; t0 += UN) {
+            for (int t0 = 0; t0 < nt; t0 += GW) {
               if (wact) {
+                auto quarter = [&](int sb) {
 #pragma unroll
-                for (int k = 0; k < UN; ++k) {
-                  round();
-                  if (k + 1 < UN) move_off(LJ << __builtin_ctz(k + 1));  // folds to one straight-line move
+                  for (int r = 0; r < 1 << LB; ++r) {
+                    round();
+                    if (r + 1 < 1 << LB) move_low(__builtin_ctz(r + 1));
+                  }
+                  if (sb < 3) move_blk(sb);
+                };
+                if constexpr (RB >= 8) {  // straight-line code of that length takes the compiler many minutes
+#pragma unroll 1
+                  for (int sb = 0; sb < 4; ++sb) quarter(sb);
+                } else {
+#pragma unroll
+                  for (int sb = 0; sb < 4; ++sb) quarter(sb);
                 }
               }
-              const int t = t0 + UN - 1;
-              if (t + 1 < nt) {
-                const int bb = __builtin_ctz(t + 1);
-                if ((1 << bb) < GW) {
-                  if (wact) move_off(LJ << bb);
-                } else {
-                  store_col(xm, um, mid(t), nm);
-                  __syncthreads();
-                  load_col(xm, um, mid(t + 1));
-                  nm = nrm[mid(t + 1)];
-                }
+              if (t0 + GW < nt) {
+                store_col(xm, um, mid(t0 + GW - 1), nm, pm);
+                __syncthreads();
+                load_col(xm, um, mid(t0 + GW));
+                nm = nrm[mid(t0 + GW)];
+                if (kSpread) pm = scl[mid(t0 + GW)];
               }
             }
           }
           cm_id = mid(nt - 1);
-          // end of the block: every column back to B (with its tracked norm)
-          store_col(xs, us, cs_id, ns);
-          store_col(xm, um, cm_id, nm);
+          // end of the block: every column back to B (with its tracked norm and scale)
+          store_col(xs, us, cs_id, ns, ps);
+          store_col(xm, um, cm_id, nm, pm);
           if (hb + 1 == K) {
-            if (rot && lane == 0) sh_flag[sweep % 3][0] = 1;
-            if (big && lane == 0) sh_flag[sweep % 3][1] = 1;
+            if (rot && jlane == 0) sh_flag[sweep % 3][0] = 1;
+            if (big && jlane == 0) sh_flag[sweep % 3][1] = 1;
             if (tid < 2) sh_flag[(sweep + 1) % 3][tid] = 0;
             rot = false;
             big = false;
@@ -1190,16 +1299,25 @@ __global__ __launch_bounds__(NT, (NMAX == 64 && !ACC_) ? 2 : 1) void k_theta_svd
     }
   }
 
-  // singular values (column norms, two columns per pair group), stable descending order
+  // singular values (column norms, two columns per pair group, the scales folded in), stable
+  // descending order
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int c = 2 * pair_id + h;
+    const double d = LJ != 16 ? scl[c] * rsq_nr(scl[c]) : 1.0;
     double s2 = 0.0;
 #pragma unroll
     for (int u = 0; u < RPL; ++u) {
       const int rr = jrow(u);
-      const double2 t = B[c][rr];
-      if (c < nB && rr < nB) s2 += cabs2(t);
+      double2 t = B[c][rr];
+      if (c < nB && rr < nB) {
+        if constexpr (LJ != 16) {
+          t = cscale(t, d);
+          B[c][rr] = t;
+          if constexpr (ACC) W[c][rr] = cscale(W[c][rr], d);
+        }
+        s2 += cabs2(t);
+      }
     }
     s2 = group_sum_dpp(s2, LJ);
     if (lane == 0 && c < nB) sig[c] = sqrt(s2);
