@@ -389,10 +389,12 @@ gpeps_status build_layout(const gpeps_graph* graphs, int32_t n_graphs, const int
   // legs costs D times one with two, and the dear workgroups have to start first to share the CUs
   // evenly
   L.bp_order = L.rlist.size();
-  if (D <= kMaxD)
-    for (int deg = kMaxDeg; deg >= 1; --deg)
-      for (int i = 0; i < 2 * L.NE; ++i)
-        if (L.edges[i >> 1].side[i & 1].deg == deg) L.rlist.push_back(i);
+  if (D <= kMaxD) {
+    std::vector<int32_t> by_deg[kMaxDeg + 1];
+    for (int e = 0; e < L.NE; ++e)
+      for (int sd = 0; sd < 2; ++sd) by_deg[L.edges[e].side[sd].deg].push_back(2 * e + sd);
+    for (int deg = kMaxDeg; deg >= 1; --deg) L.rlist.insert(L.rlist.end(), by_deg[deg].begin(), by_deg[deg].end());
+  }
   const size_t slots = std::max(L.max_items, 1);
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -519,6 +521,19 @@ gpeps_status enqueue_edge_kernel(gpeps_ctx* c, int which, int first, int count, 
   HIP_TRY(c, launch_edge_kernel(which, c->c128, with_rows(c, c->st, first, count), c->d_items, first, count,
                                 c->blocks_per_slice, c->stream));
   return GPEPS_OK;
+}
+
+// Workgroup size of the Theta' + SVD kernel before any tuning.  Four waves per SVD give the shortest
+// chain (85 us for one instance at D = 16, one wave 150 us); one wave does the same with half the
+// float64 instructions and no barriers, and eight such workgroups fit a CU against five, so it wins
+// once the launches fill the chip: 127 qubits at D = 16, 20 steps, 256 / 64 threads: 16 instances
+// 12.9 / 15.7 ms, 32 (1728 items in the largest class) 21.7 / 20.6 ms, 128 72.7 / 63.5 ms; D = 12
+// x 32 19.6 / 17.8 ms.  At D <= 8 half of the four waves' work is gone already (64 instances at
+// D = 8 16.3 / 18.8 ms), and complex128 holds two matrices more (one wave a SIMD).  The choice
+// depends on the whole context, not on one launch: batched and plain mode give the same bits.
+int default_svd_threads(const gpeps_ctx* c) {
+  constexpr int kCus = 256;
+  return !c->c128 && c->D > 8 && c->D <= 16 && c->L.max_items >= 6 * kCus ? 64 : 256;
 }
 
 struct Timer {
@@ -883,7 +898,7 @@ gpeps_status gpeps_init(gpeps_ctx** out, const gpeps_graph* graphs, int32_t n_gr
   st.trunc_rel = cfg->trunc_rel;
   st.tune_rb = 2;
   st.tune_qr = 16;
-  st.tune_svd = 256;
+  st.tune_svd = default_svd_threads(c);
   // site tensors larger than the 256 MB last-level cache are streamed past the caches by the
   // re-absorb; a state that fits stays cached for the readout and the next gate (measured: a
   // 150 MiB state ran slower streamed, 620 and 665 MiB ones faster)
@@ -1348,7 +1363,7 @@ gpeps_status gpeps_autotune(gpeps_ctx* c, int32_t steps, int32_t* tiles_out) {
   double tot[kKinds];
   c->st.tune_qr = 16;
   c->st.tune_rb = 2;
-  c->st.tune_svd = 256;
+  c->st.tune_svd = default_svd_threads(c);
   drop_step_graph(c);
   gpeps_status s = timed_trial(c, steps, tot);  // warm-up (code objects, caches)
   double t_qr[2] = {0.0, 0.0}, t_rb[4] = {0.0, 0.0, 0.0, 0.0}, t_sv[2] = {0.0, 0.0};
@@ -1379,7 +1394,7 @@ gpeps_status gpeps_autotune(gpeps_ctx* c, int32_t steps, int32_t* tiles_out) {
   if (s != GPEPS_OK) {
     c->st.tune_qr = 16;
     c->st.tune_rb = 2;
-    c->st.tune_svd = 256;
+    c->st.tune_svd = default_svd_threads(c);
   }
   drop_step_graph(c);
   gpeps_status r = gpeps_reset(c);

@@ -450,7 +450,7 @@ constexpr int kSmallB = 8;                  // largest square B that skips the Q
 constexpr double kJacobiQuietC128 = 1e-16;  // (1e-8)^2: the same for the complex128 path
 
 template <typename CT, int NT, int NMAX, bool ACC_, bool BWD = false>
-__global__ __launch_bounds__(NT, NMAX == 32 ? NT / 64 : ACC_ ? 1 : 2) void k_theta_svd(DevState st, const int32_t* __restrict__ items, int first) {
+__global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : ACC_ ? 1 : 2) void k_theta_svd(DevState st, const int32_t* __restrict__ items, int first) {
   constexpr bool ACC = ACC_;
   constexpr int DM = NMAX / 2;             // largest bond dimension handled
   constexpr int EPT = NMAX * NMAX / NT;    // Theta' entries per thread (16)
@@ -1755,26 +1755,40 @@ __global__ __launch_bounds__(NT, NMAX == 32 ? NT / 64 : ACC_ ? 1 : 2) void k_the
   } else {
     // D <= 16: every product is one 16 x 16 tile per physical slice, so wave h (h = 0, 1) takes
     // slice h on the matrix cores (one wave takes both when the workgroup has one); the two
-    // slices meet in LDS, where every thread combines them for its (k, k') entry.
+    // slices meet in LDS, where every thread combines them for its (k, k') entry.  They meet in A0,
+    // once every wave has read what it holds (slices of their own would take 8.7 KB more: five
+    // workgroups a CU instead of eight).
     constexpr int NW = NT / 64;
     static_assert(DM <= 16, "one tile per slice");
     const int wv = tid >> 6, li = tid & 15, lk = (tid & 63) >> 4;
-    __shared__ double2 Xs[2][16][17];
-    cgemm_d4 cr, ci;
+    static_assert(DS == 17, "Xs[h][k][k'] is A0[h DM DS + k DS + k']");
+    double2 (*const Xs)[16][17] = reinterpret_cast<double2 (*)[16][17]>(A0);
+    constexpr int HW = NW == 1 ? 2 : 1;  // slices of a wave in the first product
+    cgemm_d4 cr, ci, c1r[HW], c1i[HW];
+    auto meet = [&]() {
+      __syncthreads();  // A0 has been read
+#pragma unroll
+      for (int q = 0; q < HW; ++q)
+        if (wv + q < 2) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) Xs[wv + q][lk + 4 * r][li] = make_double2(c1r[q][r], c1i[q][r]);
+        }
+      __syncthreads();
+    };
     if (!vside) {
       // Y_s = R_i^(s)H U_s;  T_j^(t) = lambda/sigma sum_s g(s,t) conj(Y_s);  Z_t = sum_s conj(g(s,t)) Y_s
-      for (int h = wv; h < 2; h += NW) {
+#pragma unroll
+      for (int q = 0; q < HW; ++q) {
+        const int h = wv + q;
         auto fa = [&](int k, int a) -> double2 {
           return (k < de && a < ri) ? cconj(A1[h * DM * DS + a * DS + k]) : make_double2(0.0, 0.0);
         };
         auto fb = [&](int a, int kp) -> double2 {
           return (a < ri && kp < chi) ? A0[(h * ri + a) * DS + kp] : make_double2(0.0, 0.0);
         };
-        cgemm_tile(0, 0, ri, fa, fb, cr, ci);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) Xs[h][lk + 4 * r][li] = make_double2(cr[r], ci[r]);
+        if (h < 2) cgemm_tile(0, 0, ri, fa, fb, c1r[q], c1i[q]);
       }
-      __syncthreads();
+      meet();
       for (int idx = tid; idx < 256; idx += NT) {
         const int k = idx >> 4, kp = idx & 15;
         if (k < de && kp < chi) {
@@ -1826,18 +1840,18 @@ __global__ __launch_bounds__(NT, NMAX == 32 ? NT / 64 : ACC_ ? 1 : 2) void k_the
       }
     } else {
       // X_t = R_j^(t)T V_t;  T_i^(s) = lambda/sigma sum_t g(s,t) X_t;  P_s = lambda sum_t g(s,t) X_t
-      for (int h = wv; h < 2; h += NW) {
+#pragma unroll
+      for (int q = 0; q < HW; ++q) {
+        const int h = wv + q;
         auto fa = [&](int k, int b) -> double2 {
           return (k < de && b < rj) ? A1[h * DM * DS + b * DS + k] : make_double2(0.0, 0.0);
         };
         auto fb = [&](int b, int kp) -> double2 {
           return (b < rj && kp < chi) ? A0[(h * rj + b) * DS + kp] : make_double2(0.0, 0.0);
         };
-        cgemm_tile(0, 0, rj, fa, fb, cr, ci);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) Xs[h][lk + 4 * r][li] = make_double2(cr[r], ci[r]);
+        if (h < 2) cgemm_tile(0, 0, rj, fa, fb, c1r[q], c1i[q]);
       }
-      __syncthreads();
+      meet();
       for (int idx = tid; idx < 256; idx += NT) {
         const int k = idx >> 4, kp = idx & 15;
         if (k < de && kp < chi) {
