@@ -10,10 +10,11 @@
 //     columns) lives in registers: 512 threads, 8 lanes per column pair, 16 rows per lane, the
 //     stationary and the moving column of every pair (128 VGPRs of data per lane);
 //   * one-sided (Hestenes) Jacobi with the pairing {c, c ^ m} of the D <= 32 complex64 kernel:
-//     blocks of rounds of equal highest bit hb of m, low bits in Gray-code order, so between
-//     rounds every moving column passes to the lane group g ^ 2^b (b the changed bit): a lane
-//     permutation inside a wave (lane ^ 8, 16, 32), an LDS exchange (64 columns, 128 KB) across
-//     waves; between blocks every column goes to its new owner through LDS (column ids < 64) and
+//     blocks of rounds of equal highest bit hb of m; the lanes of a group are spread over the wave
+//     and the moving columns pass between its eight groups by one DPP instruction a word, and
+//     across waves through an LDS exchange (64 columns, 130 KB); columns carry a scale, so a
+//     rotation takes 8 instead of 12 operations per pair of entries (as k_theta_svd at D = 32);
+//     between blocks every column goes to its new owner through LDS (column ids < 64) and
 //     the item's HBM scratch (ids >= 64);
 //   * B is first reduced by Householder QR with column pivoting, B P = Q R (columns in registers,
 //     4 lanes each; the pivot column goes through LDS every step), and the Jacobi iteration runs
@@ -53,30 +54,16 @@ __device__ __forceinline__ int ins_bit(int g, int hb, int bit) {
   return ((g >> hb) << (hb + 1)) | (bit << hb) | (g & ((1 << hb) - 1));
 }
 
-// The 16 rows of the moving column held by this lane, exchanged with lane ^ OFF.
-template <int OFF>
-__device__ __forceinline__ void move_col(double2 (&x)[kBRPL], double& n2) {
-#pragma unroll
-  for (int u = 0; u < kBRPL; ++u) {
-    const unsigned long long bx = (unsigned long long)__double_as_longlong(x[u].x);
-    const unsigned long long by = (unsigned long long)__double_as_longlong(x[u].y);
-    unsigned w0 = (unsigned)(bx & 0xffffffffull), w1 = (unsigned)(bx >> 32);
-    unsigned w2 = (unsigned)(by & 0xffffffffull), w3 = (unsigned)(by >> 32);
-    lane_xor2<OFF>(w0, w1);
-    lane_xor2<OFF>(w2, w3);
-    x[u] = make_double2(__longlong_as_double((long long)(((unsigned long long)w1 << 32) | w0)),
-                        __longlong_as_double((long long)(((unsigned long long)w3 << 32) | w2)));
-  }
-  n2 = lane_xor<OFF>(n2);
-}
-
 }  // namespace
 
 template <typename CT>
 __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __restrict__ items, int first) {
   constexpr bool C64 = sizeof(CT) == sizeof(float2);
-  __shared__ double2 X[kBGroups][kBN + 1];  // 129 KB: column exchange, then the kept vectors [k'][row]
+  // 130 KB: column exchange, then the kept vectors [k'][row].  With this stride the 8 lane groups of
+  // a wave, 2 rows each, cover all LDS banks once.
+  __shared__ double2 X[kBGroups][kBN + 2];
   __shared__ double nrmx[kBN];          // tracked squared norms by column id (exchanges)
+  __shared__ double sclx[kBN];          // squared scales of the columns, the same way
   __shared__ double sig[kBN];
   __shared__ int perm[kBN];
   __shared__ int colid_sh[kBN];  // original column of each pivot position
@@ -164,15 +151,18 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
   // Householder QR with column pivoting, B P = Q R (only R is kept).  Column c sits in the
   // registers of lanes 4c .. 4c + 3 (rows ql + 4u); pivoting is virtual (colid records the
   // order).  Every step: the pivot comes from the per-wave candidates of the previous step, its
-  // column's rows j.. go through LDS, every group builds the reflector from that copy
-  // (bit-identical in all groups) and applies it to its own column, then publishes the next
-  // candidate.  The key of a candidate is the squared norm with its 7 lowest mantissa bits
+  // owners build the reflector and put it in LDS (zero above row j), every other group applies it
+  // to its own column and publishes the next candidate.  Row blocks above row j are skipped (their
+  // test is uniform).  The key of a candidate is the squared norm with its 7 lowest mantissa bits
   // replaced by 127 - column (ties within 2^-45 relative go to the lowest column); a zero
-  // norm keeps key 0, a column that cannot be chosen has key -1.
+  // norm keeps key 0, a column that cannot be chosen has key -1.  Bound by issue and by the LDS reads
+  // of the reflector.  With every group rebuilding the reflector and a test per row, 17.0 k cycles a
+  // step at 128 columns.
   {
     constexpr int LQ = kBT / kBN;  // 4 lanes per column
     constexpr int RQ = kBN / LQ;   // 32 rows per lane
-    __shared__ double2 pcol[kBN];
+    __shared__ double2 pcol[kBN];  // the reflector v = x - beta e_j, zero above row j
+    __shared__ double sh_tau;      // I - tau v v^H; 0 when the column is zero below row j
     __shared__ double cand[2][kBT / 64];
     __shared__ int posof[kBN];
     const int qc = tid / LQ, ql = tid - (tid / LQ) * LQ, wv = tid >> 6;
@@ -208,66 +198,64 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
       if (!(best > 0.0)) break;  // the remaining columns are zero below row j
       const int P = 127 - (int)(__double_as_longlong(best) & 127ll);
       if (qc == P) {
+        double sb = 0.0;
 #pragma unroll
-        for (int u = 0; u < RQ; ++u) {
-          const int rr = ql + LQ * u;
-          if (rr >= j && rr < mB) pcol[rr] = x[u];
-        }
-        if (ql == 0) posof[P] = j;
-      }
-      __syncthreads();
-      // reflector I - tau v v^H, v = x - beta e_j, beta = -phase(x_j) ||x||, x = rows j.. of the pivot
-      const double2 alpha = pcol[j];
-      double sb = 0.0;
-#pragma unroll
-      for (int u = 0; u < RQ; ++u) {
-        const int rr = ql + LQ * u;
-        if (rr > j && rr < mB) sb += cabs2(pcol[rr]);
-      }
-      sb = group_sum_dpp(sb, LQ);
-      if (qc == P) {
+        for (int u = 0; u < RQ; ++u)
+          if (LQ * u + LQ > j) {
+            const int rr = ql + LQ * u;
+            pcol[rr] = rr >= j ? x[u] : make_double2(0.0, 0.0);
+            if (rr > j) sb += cabs2(x[u]);
+          }
+        sb = group_sum_dpp(sb, LQ);
+        wave_lds_sync();
+        const double2 alpha = pcol[j];
         used = true;
         jP = j;
         betaP = alpha;
+        double tau = 0.0;
+        if (sb > 0.0) {
+          // beta = -phase(x_j) ||x||
+          const double aa2 = cabs2(alpha);
+          const double nu2 = aa2 + sb;
+          const double nu = nu2 * rsq_nr(nu2);
+          const double2 ph = aa2 > 0.0 ? cscale(alpha, rsq_nr(aa2)) : make_double2(1.0, 0.0);
+          betaP = cscale(ph, -nu);
+          const double2 v0 = csub(alpha, betaP);
+          tau = 2.0 * rcp_nr(cabs2(v0) + sb);
+          wave_lds_sync();
+          if (ql == 0) pcol[j] = v0;
+        }
+        if (ql == 0) {
+          sh_tau = tau;
+          posof[P] = j;
+        }
       }
+      __syncthreads();
       double s2 = 0.0;
-      if (sb > 0.0) {
-        const double aa2 = cabs2(alpha);
-        const double nu2 = aa2 + sb;
-        const double nu = nu2 * rsq_nr(nu2);
-        const double2 ph = aa2 > 0.0 ? cscale(alpha, rsq_nr(aa2)) : make_double2(1.0, 0.0);
-        const double2 beta = cscale(ph, -nu);
-        const double2 v0 = csub(alpha, beta);
-        const double tau = 2.0 * rcp_nr(cabs2(v0) + sb);
-        if (qc == P) betaP = beta;
-        if (!used && qc < nB) {
+      if (!used && qc < nB) {
+        const double tau = sh_tau;
+        double2 f = make_double2(0.0, 0.0);
+        if (tau > 0.0) {
           double wr = 0.0, wi = 0.0;
 #pragma unroll
-          for (int u = 0; u < RQ; ++u) {
-            const int rr = ql + LQ * u;
-            if (rr >= j && rr < mB) {
-              const double2 g = cmulc(rr == j ? v0 : pcol[rr], x[u]);
-              wr += g.x;
-              wi += g.y;
+          for (int u = 0; u < RQ; ++u)
+            if (LQ * u + LQ > j) {
+              const double2 v = pcol[ql + LQ * u];
+              wr = fma(v.y, x[u].y, fma(v.x, x[u].x, wr));
+              wi = fma(-v.y, x[u].x, fma(v.x, x[u].y, wi));
             }
-          }
           group_sum2_dpp(wr, wi, LQ);
-          const double2 f = make_double2(wr * tau, wi * tau);
+          f = make_double2(wr * tau, wi * tau);
+        }
 #pragma unroll
-          for (int u = 0; u < RQ; ++u) {
+        for (int u = 0; u < RQ; ++u)
+          if (LQ * u + LQ > j) {
             const int rr = ql + LQ * u;
-            if (rr >= j && rr < mB) {
-              x[u] = csub(x[u], cmul(rr == j ? v0 : pcol[rr], f));
-              if (rr > j) s2 += cabs2(x[u]);
-            }
+            const double2 v = pcol[rr];
+            x[u].x = fma(-v.x, f.x, fma(v.y, f.y, x[u].x));
+            x[u].y = fma(-v.x, f.y, fma(-v.y, f.x, x[u].y));
+            if (rr > j) s2 += cabs2(x[u]);
           }
-        }
-      } else if (!used && qc < nB) {
-#pragma unroll
-        for (int u = 0; u < RQ; ++u) {
-          const int rr = ql + LQ * u;
-          if (rr > j && rr < mB) s2 += cabs2(x[u]);
-        }
       }
       publish(group_sum_dpp(s2, LQ), !used && qc < nB, (j + 1) & 1);
       __syncthreads();
@@ -301,21 +289,44 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
   }
   // the Jacobi matrix X = R^H (nB x nB): X[c][r] = conj(R(c, r)) = conj(Rs[r][c])
   auto x_at = [&](int c, int rr) -> double2 { return cconj(Rs[rr * kBN + c]); };
-  const int pair_id = tid / kBLJ;
-  const int lane = tid - pair_id * kBLJ;
+  // lane group and lane of the group: group index inside the wave (blk, low), blk in lane bits 2 and
+  // 3, low in lane bit 1; the lanes of a group are lane bits 0, 4 and 5
+  const int wl = tid & 63;
+  const int pair_id = (tid >> 6) * 8 + ((((wl >> 2) & 3) << 1) | ((wl >> 1) & 1));
+  const int lane = (wl & 1) + 2 * (wl >> 4);
+  const double own = ((wl >> 4) >> 1) == ((wl & 3) >> 1) ? 1.0 : 0.0;  // the two groups of a block apart
   auto xrow = [&](int u) { return lane + kBLJ * u; };
+  // sums over the lanes of a group, against ones on v_mfma_f64_4x4x4 (lane l supplies A[l % 4][l / 16]
+  // and B[l / 16][l % 4] of block (l / 4) % 4 and receives D[l / 16][l % 4])
+  auto total2 = [&](double& a, double& b) {
+    a = own * __builtin_amdgcn_mfma_f64_4x4x4f64(a, 1.0, 0.0, 0, 0, 0);
+    b = own * __builtin_amdgcn_mfma_f64_4x4x4f64(b, 1.0, 0.0, 0, 0, 0);
+    a = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, a, 0.0, 0, 0, 0);
+    b = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, b, 0.0, 0, 0, 0);
+  };
   int K = 1;
   while ((1 << K) < nB) ++K;
   const bool gact = pair_id < (1 << (K - 1));
   const double tol2 = (2.220446049250313e-16 * (double)nB) * (2.220446049250313e-16 * (double)nB);
   double2 xs[kBRPL], xm[kBRPL];  // stationary and moving column of the group
-  double ns = 0.0, nm = 0.0;
+  double ns = 0.0, nm = 0.0;  // their tracked squared norms
+  double ps = 1.0, pm = 1.0;  // their squared scales: the column is sqrt(ps) xs
   int cs_id = ins_bit(pair_id, 0, 0), cm_id = ins_bit(pair_id, 0, 1);
-  auto col_norm = [&](const double2 (&x)[kBRPL]) {
-    double s2 = 0.0;
+  // both scales folded into the columns, their squared norms to ns, nm
+  auto fold = [&]() {
+    const double ds = ps * rsq_nr(ps), dm = pm * rsq_nr(pm);
+    ns = 0.0;
+    nm = 0.0;
 #pragma unroll
-    for (int u = 0; u < kBRPL; ++u) s2 += cabs2(x[u]);
-    return group_sum_dpp(s2, kBLJ);
+    for (int u = 0; u < kBRPL; ++u) {
+      xs[u] = cscale(xs[u], ds);
+      xm[u] = cscale(xm[u], dm);
+      ns += cabs2(xs[u]);
+      nm += cabs2(xm[u]);
+    }
+    ps = 1.0;
+    pm = 1.0;
+    total2(ns, nm);
   };
   // initial assignment (block hb = 0): group g holds columns 2g and 2g + 1
 #pragma unroll
@@ -326,33 +337,52 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
   }
   const double floor2 = sh_floor * sh_floor;
 
-  // every column to its owner under block hb (ids < 64 through LDS, ids >= 64 through HBM)
-  auto redistribute = [&](int hb) {
-    auto put = [&](const double2 (&x)[kBRPL], int c, double n2) {
+  // Every column to its owner under block hb.  Within the blocks hb < 6 the ids under 64 stay with
+  // the first half of the groups and the others with the second half, so the halves take turns with
+  // the LDS buffer; into and out of block 6 (two of the seven times a sweep at 128 columns) the ids
+  // of 64 and more go through the item's HBM scratch.  All through the two buffers at once: 26 k
+  // cycles a time.
+  auto redistribute = [&](int hb, int from) {
+    const bool turns = hb < 6 && from < 6;
+    auto put = [&](const double2 (&x)[kBRPL], int c, double n2, double p2) {
       if (!gact || c >= nB) return;
-      double2* dst = c < kBGroups ? &X[c][0] : Og + (int64_t)(c - kBGroups) * kBN;
+      double2* dst = turns ? &X[c & (kBGroups - 1)][0] : c < kBGroups ? &X[c][0] : Og + (int64_t)(c - kBGroups) * kBN;
 #pragma unroll
       for (int u = 0; u < kBRPL; ++u) dst[xrow(u)] = x[u];
-      if (lane == 0) nrmx[c] = n2;
+      if (lane == 0) {
+        nrmx[c] = n2;
+        sclx[c] = p2;
+      }
     };
-    put(xs, cs_id, ns);
-    put(xm, cm_id, nm);
-    __syncthreads();
-    cs_id = ins_bit(pair_id, hb, 0);
-    cm_id = ins_bit(pair_id, hb, 1);
-    auto get = [&](double2 (&x)[kBRPL], int c, double& n2) {
+    auto get = [&](double2 (&x)[kBRPL], int c, double& n2, double& p2) {
       const bool ok = gact && c < nB;
-      const double2* src = c < kBGroups ? &X[c < kBGroups ? c : 0][0] : Og + (int64_t)(c - kBGroups) * kBN;
+      const double2* src = turns ? &X[c & (kBGroups - 1)][0]
+                                 : c < kBGroups ? &X[c][0] : Og + (int64_t)(c - kBGroups) * kBN;
 #pragma unroll
       for (int u = 0; u < kBRPL; ++u) {
         const double2 t = src[xrow(u)];
         x[u] = ok ? t : make_double2(0.0, 0.0);
       }
       n2 = ok ? nrmx[c] : 0.0;
+      p2 = ok ? sclx[c] : 1.0;
     };
-    get(xs, cs_id, ns);
-    get(xm, cm_id, nm);
-    __syncthreads();
+    const bool second = pair_id >= kBGroups / 2;
+    const int n_turns = turns && nB > kBGroups ? 2 : 1;
+    for (int turn = 0; turn < n_turns; ++turn) {
+      const bool mine = !turns || second == (turn == 1);
+      if (mine) {
+        put(xs, cs_id, ns, ps);
+        put(xm, cm_id, nm, pm);
+      }
+      __syncthreads();
+      if (mine) {
+        cs_id = ins_bit(pair_id, hb, 0);
+        cm_id = ins_bit(pair_id, hb, 1);
+        get(xs, cs_id, ns, ps);
+        get(xm, cm_id, nm, pm);
+      }
+      __syncthreads();
+    }
   };
 
   bool rot = false, big = false;
@@ -360,64 +390,91 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
   bool converged = nB < 2;
   for (; sweep < st.max_sweeps && !converged; ++sweep) {
     for (int hb = 0; hb < K; ++hb) {
-      if (hb == 0) {
-        ns = col_norm(xs);
-        nm = col_norm(xm);
-      }
+      if (hb == 0) fold();
       const int nt = 1 << hb;
-      for (int t = 0; t < nt; ++t) {
-        // rotation of the pair (stationary xs, moving xm); branch-free: a pair that is not
-        // rotated takes c = 1, s = 0, which leaves both columns and norms bit for bit
-        double2 g = cmulc(xs[0], xm[0]);
-#pragma unroll
-        for (int u = 1; u < kBRPL; ++u) g = cadd(g, cmulc(xs[u], xm[u]));
-        double gr = g.x, gi = g.y;
-        group_sum2_dpp(gr, gi, kBLJ);
+      // rotation of the pair (stationary xs, moving xm) by tan theta e^{i phi} = g F,
+      // F = sign(d) / (h x), x = cos^2 theta; branch-free: a pair that is not rotated takes F = 0 and
+      // x = 1, which leaves both columns and norms bit for bit
+      auto round = [&]() {
+        double gr, gi;
+        dot_rows<kBRPL>(xs, xm, gr, gi);
+        total2(gr, gi);
         const double al = ns, be = nm;
-        const double g2 = gr * gr + gi * gi;
-        const bool ok = gact & (cm_id < nB) & (g2 > tol2 * al * be) & (g2 > floor2);
+        const double g2 = (gr * gr + gi * gi) * (ps * pm);
+        const double ab = al * be;
+        // the columns of inactive groups and of ids past nB are exactly zero: g = 0
+        const bool ok = (g2 > tol2 * ab) & (g2 > floor2);
         const double d = be - al;
-        const double h2 = d * d + 4.0 * g2;
+        const double h2 = fmax(d * d + 4.0 * g2, 1e-300);
         const double rh = C64 ? rsq_nr1(h2) : rsq_nr(h2);  // 1 / h
-        const double xx = 0.5 + 0.5 * fabs(d) * rh;
-        const double rc = C64 ? rsq_nr1(xx) : rsq_nr(xx);  // 1 / c
-        const double f = (d < 0.0 ? -rh : rh) * rc;
-        const double cs = ok ? xx * rc : 1.0;
-        const double2 sph = ok ? make_double2(gr * f, gi * f) : make_double2(0.0, 0.0);
-        const double tg = ok ? g2 * f * rc : 0.0;
+        const double x = 0.5 + 0.5 * fabs(d) * rh;
+        const double rx = C64 ? rcp_nr1(x) : rcp_nr(x);    // 1 / x
+        const double F = ok ? copysign(rh, d) * rx : 0.0;
+        const double xx = ok ? x : 1.0;
+        const double tg = g2 * F;  // tan theta |g|
+        const double fm = F * pm, fs = F * ps;
+        const double2 tm = make_double2(gr * fm, gi * fm), ts = make_double2(gr * fs, gi * fs);
 #pragma unroll
         for (int u = 0; u < kBRPL; ++u) {
-          const double2 bp = xs[u], bq = xm[u];
-          xs[u] = csub(cscale(bp, cs), cmulc(sph, bq));
-          xm[u] = cadd(cmul(sph, bp), cscale(bq, cs));
+          const double2 a = xs[u], b = xm[u];
+          xs[u].x = fma(-tm.x, b.x, fma(-tm.y, b.y, a.x));
+          xs[u].y = fma(-tm.x, b.y, fma(tm.y, b.x, a.y));
+          xm[u].x = fma(ts.x, a.x, fma(-ts.y, a.y, b.x));
+          xm[u].y = fma(ts.x, a.y, fma(ts.y, a.x, b.y));
         }
+        ps *= xx;
+        pm *= xx;
         ns = al - tg;
         nm = be + tg;
         rot = rot || ok;
-        big = big || (ok && g2 > kQuietBigC64 * al * be);
-        if (t + 1 < nt) {
-          // the moving column passes to group pair_id ^ 2^bb
-          const int bb = __builtin_ctz(t + 1);
-          const int mp = (t + 1) ^ ((t + 1) >> 1);
-          if (bb == 0) {
-            move_col<kBLJ>(xm, nm);
-          } else if (bb == 1) {
-            move_col<2 * kBLJ>(xm, nm);
-          } else if (bb == 2) {
-            move_col<4 * kBLJ>(xm, nm);
-          } else {
+        big = big || (ok && g2 > kQuietBigC64 * ab);
+      };
+      auto move = [&](auto perm) {  // the moving column, its norm and scale, through a lane permutation
 #pragma unroll
-            for (int u = 0; u < kBRPL; ++u) X[pair_id][xrow(u)] = xm[u];
-            if (lane == 0) nrmx[pair_id] = nm;
-            __syncthreads();
-            const int src = pair_id ^ (1 << bb);
-#pragma unroll
-            for (int u = 0; u < kBRPL; ++u) xm[u] = X[src][xrow(u)];
-            nm = nrmx[src];
-            __syncthreads();
+        for (int u = 0; u < kBRPL; ++u) xm[u] = make_double2(perm(xm[u].x), perm(xm[u].y));
+        nm = perm(nm);
+        pm = perm(pm);
+      };
+      if (nt < 8) {
+        // fewer rounds than groups of a wave: group ^ 2^b, b the Gray-code bit
+        for (int t = 0; t < nt; ++t) {
+          round();
+          if (t + 1 < nt) {
+            if (__builtin_ctz(t + 1) == 0) move([](double v) { return dpp_d<0x4E>(v); });  // low: lane ^ 2
+            else move([](double v) { return lane_xor<4>(v); });                             // blk ^ 1
           }
-          cm_id = ins_bit(pair_id ^ mp, hb, 1);
         }
+        cm_id = ins_bit(pair_id ^ ((nt - 1) ^ ((nt - 1) >> 1)), hb, 1);
+      } else {
+        int T = 0;
+        for (;; ++T) {
+          // blk turns once more than it has to, so that every trip is the same straight line (a
+          // condition on the last one costs copies and spills of the whole column) and the columns
+          // end where they began
+#pragma unroll 1
+          for (int sb = 0; sb < 4; ++sb) {
+            round();
+            move([](double v) { return dpp_d<0x4E>(v); });  // low ^ 1
+            round();
+            move([](double v) { return dpp_d<0x124>(v); });  // blk - 1 to blk
+          }
+          if (8 * (T + 1) >= nt) break;
+          // to the wave whose index differs in the next Gray-code bit, same group inside the wave
+#pragma unroll
+          for (int u = 0; u < kBRPL; ++u) X[pair_id][xrow(u)] = xm[u];
+          if (lane == 0) {
+            nrmx[pair_id] = nm;
+            sclx[pair_id] = pm;
+          }
+          __syncthreads();
+          const int src = pair_id ^ (8 << __builtin_ctz(T + 1));
+#pragma unroll
+          for (int u = 0; u < kBRPL; ++u) xm[u] = X[src][xrow(u)];
+          nm = nrmx[src];
+          pm = sclx[src];
+          __syncthreads();
+        }
+        cm_id = ins_bit(pair_id ^ ((T ^ (T >> 1)) << 3), hb, 1);
       }
       if (hb + 1 == K) {
         if (rot && lane == 0) sh_flag[sweep % 3][0] = 1;
@@ -426,12 +483,13 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
         rot = false;
         big = false;
       }
-      if (hb + 1 < K) redistribute(hb + 1);
+      if (hb + 1 < K) redistribute(hb + 1, hb);
     }
     __syncthreads();
     converged = (sh_flag[sweep % 3][0] == 0) || (C64 && sh_flag[sweep % 3][1] == 0);
-    if (!converged) redistribute(0);
+    if (!converged) redistribute(0, K - 1);
   }
+  fold();
   if (tid == 0) {
     atomicAdd(reinterpret_cast<unsigned long long*>(st.stats) + 0, (unsigned long long)sweep);
     atomicAdd(reinterpret_cast<unsigned long long*>(st.stats) + 1, 1ull);
@@ -443,7 +501,7 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
   }
 
   // singular values (norms of the held columns), stable descending order, truncation
-  const double s_s = sqrt(col_norm(xs)), s_m = sqrt(col_norm(xm));
+  const double s_s = sqrt(ns), s_m = sqrt(nm);
   if (lane == 0 && gact) {
     if (cs_id < nB) sig[cs_id] = s_s;
     if (cm_id < nB) sig[cm_id] = s_m;

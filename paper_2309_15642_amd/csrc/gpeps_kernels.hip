@@ -1167,10 +1167,16 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
           // norms bit for bit.  Padding columns are exactly zero, so their pairs have g = 0 and are
           // never rotated; h is kept away from zero so that every pair's scalars stay finite.
           auto round = [&]() {
-            double2 g = cmulc(xs[0], xm[0]);
+            double gr, gi;
+            if constexpr (RB >= 4) {
+              dot_rows<RB>(xs, xm, gr, gi);
+            } else {  // the shorter chain
+              double2 g = cmulc(xs[0], xm[0]);
 #pragma unroll
-            for (int u = 1; u < RB; ++u) g = cadd(g, cmulc(xs[u], xm[u]));
-            double gr = g.x, gi = g.y;
+              for (int u = 1; u < RB; ++u) g = cadd(g, cmulc(xs[u], xm[u]));
+              gr = g.x;
+              gi = g.y;
+            }
             group_total2(gr, gi);
             const double al = ns, be = nm;
             const double g2 = kSpread ? (gr * gr + gi * gi) * (ps * pm) : gr * gr + gi * gi;
@@ -1230,7 +1236,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
             constexpr int ML = (1 << LB) - 1;  // low's Gray code ends at its last value, where the next one starts
             const int T = t / GW, sb = (t >> LB) & 3, r = t & ML;
             const int low = (jgrp & ML) ^ (r ^ (r >> 1)) ^ ((sb & 1) ? (ML ^ (ML >> 1)) : 0);
-            const int blk = (((jgrp >> LB) & 3) - (3 * T + sb)) & 3;
+            const int blk = (((jgrp >> LB) & 3) - sb) & 3;
             const int w = (jgrp / GW) ^ (T ^ (T >> 1));
             return ins((w * 4 + blk) << LB | low, hb, 1);
           };
@@ -1242,6 +1248,8 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
               }
             }
           } else {
+            // (spread lanes: blk turns once more than it has to, so that every trip is the same
+            // straight line and the columns end where they began the GW rounds)
             for (int t0 = 0; t0 < nt; t0 += GW) {
               if (wact) {
                 auto quarter = [&](int sb) {
@@ -1250,7 +1258,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
                     round();
                     if (r + 1 < 1 << LB) move_low(__builtin_ctz(r + 1));
                   }
-                  if (sb < 3) move_blk(sb);
+                  if (kSpread || sb < 3) move_blk(sb);
                 };
                 if constexpr (RB >= 8) {  // straight-line code of that length takes the compiler many minutes
 #pragma unroll 1
@@ -1261,7 +1269,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
                 }
               }
               if (t0 + GW < nt) {
-                store_col(xm, um, mid(t0 + GW - 1), nm, pm);
+                store_col(xm, um, mid(kSpread ? t0 : t0 + GW - 1), nm, pm);
                 __syncthreads();
                 load_col(xm, um, mid(t0 + GW));
                 nm = nrm[mid(t0 + GW)];
@@ -1269,7 +1277,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
               }
             }
           }
-          cm_id = mid(nt - 1);
+          cm_id = mid(kSpread && nt >= GW ? nt - GW : nt - 1);
           // end of the block: every column back to B (with its tracked norm and scale)
           store_col(xs, us, cs_id, ns, ps);
           store_col(xm, um, cm_id, nm, pm);
