@@ -12,8 +12,9 @@
 //       m[a, a'] = sum_{s, b, b', c, c'} A[s, a, b, c] conj(A[s, a', b', c']) M1[b, b'] M2[c, c']
 //     (a on the edge's leg, b and c on the sender's other legs, M1 and M2 the messages into the
 //     sender along them);
-//   * k_bp_norm: every new message divided by its trace; the largest Frobenius change of a message
-//     goes to a residual word;
+//     divided by its trace (above D = 16 in a launch of its own, k_bp_norm); with the last one the
+//     largest Frobenius
+//     change of a message goes to the residual word;
 //   * k_bp_readout: one workgroup per qubit and block of 16 rows, rho[s, s] with every leg closed
 //     by its incoming message; k_bp_z: <Z> = (rho_00 - rho_11) / (rho_00 + rho_11).
 // The work is 48 D^4 operations per directed edge of a sender with three legs, three dense
@@ -32,8 +33,10 @@ namespace gpeps {
 
 namespace {
 
-constexpr int kBpThreads = 512;
-constexpr int kBpWaves = kBpThreads / 64;
+// N: bound on D that sizes a kernel (8, 16 or 32).  Eight waves a workgroup from D = 9 on; four below,
+// where a wave already has two products of a phase at most and small workgroups share a CU.
+template <int N> constexpr int bp_threads() { return N == 8 ? 256 : 512; }
+template <int N> constexpr int bp_tiles() { return N == 32 ? 2 : 1; }  // 16-column tiles of a bond
 typedef double bp_d4 __attribute__((ext_vector_type(4)));
 
 // Geometry of one site tensor as seen by a BP contraction: leg 0 is `a`, legs 1 and 2 are b, c.
@@ -52,8 +55,8 @@ __device__ __forceinline__ int side_of(const DevState& st, int e, int64_t goff) 
 
 // Entry [k][kp] of a message weighted by sqrt(lambda) of its leg on both indices: zero past the
 // active n x n block; an absent leg (M null, n = 1) has the message [[1]].
-template <int NB>
-__device__ __forceinline__ double2 bp_wmsg(const double2* M, int D, int n, const double (&sl)[16 * NB], int k, int kp) {
+template <int N>
+__device__ __forceinline__ double2 bp_wmsg(const double2* M, int D, int n, const double (&sl)[N], int k, int kp) {
   if (k >= n || kp >= n) return make_double2(0.0, 0.0);
   if (!M) return make_double2(1.0, 0.0);
   return cscale(M[k * D + kp], sl[k] * sl[kp]);
@@ -69,18 +72,19 @@ __device__ __forceinline__ double2 bp_wmsg(const double2* M, int D, int n, const
 //   Y[b'][a] of every c' = sum_b W1[b][b'] X[a][b][c']  (one product per c', the waves in turn)
 //   m[a][a']            += sum_b' Y[b'][a] conj(G[a'][b'][c'])
 // Y is formed with b' on the rows, so the register that receives Y[4 r + l / 16][l % 16] is the
-// operand of k step r of the last product as it stands: only X goes through LDS (beside W1, which the caller has put there, [b][b'] with row stride
-// 16 NB + 1).  Lane l ends
-// with m[a0 + l / 16 + 4 r][16 t + l % 16], this wave's share of the sum, in (mr[t][r], mi[t][r]).
+// operand of k step r of the last product as it stands: only X goes through LDS (beside W1, which
+// the caller has put there, [b][b'] with row stride N + 1).  Lane l ends with m[a0 + l / 16 + 4 r][16 t + l % 16], this wave's share, in (mr[t][r], mi[t][r]).
 // Bound by the FP64 matrix cores at D = 32, where one workgroup fills a CU's LDS (131 KB) with two
 // waves per SIMD; at D <= 16 by the latency of the phases.  Every wave of the workgroup calls this.
-template <typename CT, int NB>
+template <typename CT, int N, int NB = bp_tiles<N>()>
 __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSite& g, const double2* W1,
-                                         const double2* __restrict__ M2, int D, const double (&sl)[3][16 * NB], int a0,
+                                         const double2* __restrict__ M2, int D, const double (&sl)[3][N], int a0,
                                          int s, double2* Xs, bp_d4 (&mr)[NB], bp_d4 (&mi)[NB]) {
-  constexpr int KS = 4 * NB;              // k steps of 4 over a bond
+  constexpr int kWaves = bp_threads<N>() / 64;
+  constexpr int KS = N / 4;               // k steps of 4 over a bond
+  constexpr int R4 = N < 16 ? N / 4 : 4;  // and over a tile of 16
   constexpr int PF = sizeof(CT) == sizeof(float2) ? NB : 1;
-  constexpr int CS = 16 * NB * 16 + 1;    // stride of c' in Xs[c'][b][a] (odd: writes free of bank conflicts)
+  constexpr int CS = N * 16 + 1;    // stride of c' in Xs[c'][b][a] (odd: writes free of bank conflicts)
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, li = l & 15, lk = l >> 4;
   const int na = g.dim[0], nb = g.dim[1], nc = g.dim[2];
   const CT* const gs = gam + g.base + s * g.pstride;
@@ -92,7 +96,7 @@ __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSit
   for (int j = 0; 16 * j < nc; ++j) {
     double2 w2[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) w2[ks] = bp_wmsg<NB>(M2, D, nc, sl[2], 4 * ks + lk, 16 * j + li);
+    for (int ks = 0; ks < KS; ++ks) w2[ks] = bp_wmsg<N>(M2, D, nc, sl[2], 4 * ks + lk, 16 * j + li);
     // X of this wave's b; the next b's elements are in flight while the products run
     CT nx[KS];
     auto fetch = [&](int b) {
@@ -103,11 +107,11 @@ __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSit
       }
     };
     if (wv < nb) fetch(wv);
-    for (int b = wv; b < nb; b += kBpWaves) {
+    for (int b = wv; b < nb; b += kWaves) {
       CT x[KS];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) x[ks] = nx[ks];
-      if (b + kBpWaves < nb) fetch(b + kBpWaves);
+      if (b + kWaves < nb) fetch(b + kWaves);
       bp_d4 xr = {0.0, 0.0, 0.0, 0.0}, xi = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
@@ -120,19 +124,20 @@ __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSit
         }
       }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) Xs[li * CS + b * 16 + lk + 4 * r] = make_double2(xr[r], xi[r]);
+      for (int r = 0; r < 4; ++r)
+        if (N >= 16 || li < N) Xs[li * CS + b * 16 + lk + 4 * r] = make_double2(xr[r], xi[r]);
     }
     __syncthreads();
     const int ncp = min(16, nc - 16 * j);
-    for (int cp = wv; cp < ncp; cp += kBpWaves) {
+    for (int cp = wv; cp < ncp; cp += kWaves) {
       // the elements of the last product (its first PF column tiles) ahead: they arrive while Y is
       // formed; complex128 has registers for one tile in flight
-      CT ga[PF][NB][4];
-      auto fetch_last = [&](int at, CT (&x)[NB][4]) {
+      CT ga[PF][NB][R4];
+      auto fetch_last = [&](int at, CT (&x)[NB][R4]) {
 #pragma unroll
         for (int t = 0; t < NB; ++t)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
+          for (int r = 0; r < R4; ++r) {
             const int a2 = 16 * at + li, b2 = 16 * t + 4 * r + lk;
             x[t][r] = (a2 < na && b2 < nb) ? gs[a2 * ta + b2 * tb + (16 * j + cp) * tc] : czero;
           }
@@ -152,7 +157,7 @@ __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSit
           const double2 x = b < nb ? Xs[cp * CS + b * 16 + li] : make_double2(0.0, 0.0);
 #pragma unroll
           for (int t = 0; t < NB; ++t) {
-            const double2 w = W1[b * (16 * NB + 1) + 16 * t + li];
+            const double2 w = N >= 16 || li < N ? W1[b * (N + 1) + 16 * t + li] : make_double2(0.0, 0.0);
             yr[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(w.x, x.x, yr[t], 0, 0, 0);
             yi[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(w.x, x.y, yi[t], 0, 0, 0);
             yr[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-w.y, x.y, yr[t], 0, 0, 0);
@@ -167,7 +172,7 @@ __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSit
 #pragma unroll
           for (int t = 0; t < NB; ++t)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < R4; ++r) {
               if (16 * t + 4 * r < nb) {
                 const double2 c = to_d2(ga[at % PF][t][r]);  // conjugated below
                 mr[at] = __builtin_amdgcn_mfma_f64_16x16x4f64(yr[t][r], c.x, mr[at], 0, 0, 0);
@@ -184,35 +189,38 @@ __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSit
 }
 
 // LDS of bp_block; the per-wave sums of bp_reduce use the same memory.
-template <int NB> constexpr int bp_lds() {
-  return 16 * (16 * NB * 16 + 1) > kBpWaves * NB * 4 * 64 ? 16 * (16 * NB * 16 + 1) : kBpWaves * NB * 4 * 64;
+template <int N> constexpr int bp_lds() {
+  constexpr int x = (N < 16 ? N : 16) * (N * 16 + 1), y = bp_threads<N>() * bp_tiles<N>() * 4;
+  return x > y ? x : y;
 }
 
-// Adds the waves' shares of m in a fixed order: entry q < NB * 256 of the 16 x 16 NB block is the
-// value of thread q (or q - 512), at register slot q / 64 = 4 t + r and lane q % 64.  put(i, j, v)
-// receives row i (0 .. 15) and column j (0 .. 16 NB - 1).
-template <int NB, class F>
+// Adds the waves' shares of m in a fixed order: entry q < NB * 256 of the 16 x 16 NB block sits at
+// register slot q / 64 = 4 t + r and lane q % 64.  put(i, j, v) receives row i (0 .. 15) and column j
+// (0 .. 16 NB - 1); a thread gets at most one entry.
+template <int N, class F, int NB = bp_tiles<N>()>
 __device__ __forceinline__ void bp_reduce(double2* lds, const bp_d4 (&mr)[NB], const bp_d4 (&mi)[NB], F put) {
+  constexpr int kWaves = bp_threads<N>() / 64;
+  static_assert(NB * 256 <= bp_threads<N>(), "one entry a thread");
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
   for (int t = 0; t < NB; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) lds[((wv * NB + t) * 4 + r) * 64 + l] = make_double2(mr[t][r], mi[t][r]);
   __syncthreads();
-  for (int q = threadIdx.x; q < NB * 256; q += kBpThreads) {
+  const int q = threadIdx.x;
+  if (q < NB * 256) {
     double2 v = lds[q];
 #pragma unroll
-    for (int w = 1; w < kBpWaves; ++w) v = cadd(v, lds[w * NB * 256 + q]);
+    for (int w = 1; w < kWaves; ++w) v = cadd(v, lds[w * NB * 256 + q]);
     const int t = q >> 8, r = (q >> 6) & 3, ll = q & 63;
     put((ll >> 4) + 4 * r, 16 * t + (ll & 15), v);
   }
 }
 
 // sqrt(lambda) of the three legs (1 for an absent one), then the weighted message along leg b.
-template <int NB>
+template <int N>
 __device__ __forceinline__ void bp_weights(const DevState& st, const BpSite& g, const double2* M1,
-                                           double (&sl)[3][16 * NB], double2* W1) {
-  constexpr int N = 16 * NB;
+                                           double (&sl)[3][N], double2* W1) {
 #pragma unroll
   for (int l = 0; l < 3; ++l)
     if (threadIdx.x < N) {
@@ -220,11 +228,17 @@ __device__ __forceinline__ void bp_weights(const DevState& st, const BpSite& g, 
       sl[l][k] = g.edge[l] >= 0 ? (k < st.D ? sqrt(st.lam[(int64_t)g.edge[l] * st.D + k]) : 0.0) : 1.0;
     }
   __syncthreads();
-  for (int i = threadIdx.x; i < N * N; i += kBpThreads) {
+  for (int i = threadIdx.x; i < N * N; i += bp_threads<N>()) {
     const int k = i / N, kp = i - (i / N) * N;
-    W1[k * (N + 1) + kp] = bp_wmsg<NB>(M1, st.D, g.dim[1], sl[1], k, kp);
+    W1[k * (N + 1) + kp] = bp_wmsg<N>(M1, st.D, g.dim[1], sl[1], k, kp);
   }
   __syncthreads();
+}
+
+// A non-negative residual folded into the residual word (such doubles order like their bit patterns).
+__device__ __forceinline__ void bp_record(const DevState& st, double dev2) {
+  const double r = sqrt(dev2);
+  atomicMax(st.bp_res, (unsigned long long)__double_as_longlong(isfinite(r) ? r : 0.0));
 }
 
 }  // namespace
@@ -242,15 +256,21 @@ __global__ void k_bp_init(DevState st) {
   if (slot == 0 && threadIdx.x == 0) *st.bp_res = 0ull;
 }
 
-// One parallel BP iteration: messages of buffer `src` -> buffer 1 - src, not yet normalised.
+// One parallel BP iteration: messages of buffer `src` -> buffer 1 - src.  Up to D = 16 a workgroup holds
+// its whole message and divides it by its trace; above, that is left to k_bp_norm.
+// Small bonds are bound by the launch: ten iterations and the readout of the 127-qubit graph take
+// 172 us at D = 2 in complex128 (226 with k_bp_norm at every D, 181 before the matrix cores), and
+// sixteen such instances at D = 3 470 us with kernels sized for D <= 8 (1129 with those for 16, 580).
 // Measured at D = 32 on the 288 directed edges of the 127-qubit graph: 185 us (5.4 GFLOP, 29 TFLOP/s)
 // with the senders of three legs first (bp_order), 307 us in edge order (some CUs got two of their
 // 150 us workgroups), 3860 us as vector dot products with one workgroup per directed edge.
-template <typename CT, int NB>
-__global__ __launch_bounds__(kBpThreads) void k_bp_update(DevState st, int src) {
-  __shared__ double2 Xs[bp_lds<NB>()];
-  __shared__ double2 W1[16 * NB * (16 * NB + 1)];
-  __shared__ double sl[3][16 * NB];
+template <typename CT, int N>
+__global__ __launch_bounds__(bp_threads<N>()) void k_bp_update(DevState st, int src, int record) {
+  constexpr int NB = bp_tiles<N>();
+  __shared__ double2 Xs[bp_lds<N>()];
+  __shared__ double2 W1[N * (N + 1)];
+  __shared__ double sl[3][N];
+  __shared__ double red[8];
   const int D = st.D;
   const int nab = (D + 15) >> 4;  // blocks of 16 rows
   const int ord = blockIdx.x / nab, a0 = 16 * (blockIdx.x - ord * nab);
@@ -277,7 +297,7 @@ __global__ __launch_bounds__(kBpThreads) void k_bp_update(DevState st, int src) 
   double2* out = st.bp_msg + (src ? 0 : nmsg) + (int64_t)slot * D * D;
   const double2* M1 = g.in[1] >= 0 ? msg + (int64_t)g.in[1] * D * D : nullptr;
   const double2* M2 = g.in[2] >= 0 ? msg + (int64_t)g.in[2] * D * D : nullptr;
-  bp_weights<NB>(st, g, M1, sl, W1);
+  bp_weights<N>(st, g, M1, sl, W1);
   bp_d4 mr[NB], mi[NB];
 #pragma unroll
   for (int t = 0; t < NB; ++t) {
@@ -286,16 +306,41 @@ __global__ __launch_bounds__(kBpThreads) void k_bp_update(DevState st, int src) 
   }
   if (a0 < g.dim[0]) {
     for (int s = 0; s < 2; ++s)
-      bp_block<CT, NB>(reinterpret_cast<const CT*>(st.gamma), g, W1, M2, D, sl, a0, s, Xs, mr, mi);
+      bp_block<CT, N>(reinterpret_cast<const CT*>(st.gamma), g, W1, M2, D, sl, a0, s, Xs, mr, mi);
   }
-  bp_reduce<NB>(Xs, mr, mi, [&](int i, int j, double2 v) {
+  int at = -1;  // this thread's entry of the message
+  double2 mine = make_double2(0.0, 0.0);
+  bool diag = false;
+  bp_reduce<N>(Xs, mr, mi, [&](int i, int j, double2 v) {
     const int a = a0 + i;
-    if (a < D && j < D)
-      out[a * D + j] = (a < g.dim[0] && j < g.dim[0]) ? cscale(v, sl[0][a] * sl[0][j]) : make_double2(0.0, 0.0);
+    if (a < D && j < D) {
+      at = a * D + j;
+      diag = a == j;
+      if (a < g.dim[0] && j < g.dim[0]) mine = cscale(v, sl[0][a] * sl[0][j]);
+    }
   });
+  if constexpr (N == 32) {
+    if (at >= 0) out[at] = mine;
+  } else {
+    const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6;  // the entries sit in the first four waves
+    const double t = group_sum(diag ? mine.x : 0.0, 64);
+    if (l == 0 && wv < 4) red[wv] = t;
+    __syncthreads();
+    const double tr = (red[0] + red[1]) + (red[2] + red[3]);
+    const bool good = isfinite(tr) && tr > 0.0;
+    const double2 v = cscale(mine, good ? 1.0 / tr : 0.0);
+    if (at >= 0) out[at] = v;
+    if (record) {
+      const double dv = group_sum(at >= 0 ? cabs2(csub(v, msg[(int64_t)slot * D * D + at])) : 0.0, 64);
+      if (l == 0 && wv < 4) red[4 + wv] = dv;
+      __syncthreads();
+      if (tid == 0) bp_record(st, (red[4] + red[5]) + (red[6] + red[7]));
+    }
+    if (tid == 0 && !good) flag_status(st.status, kStatusNonFinite);
+  }
 }
 
-// The new messages (buffer 1 - src) divided by their traces; with `record` the largest Frobenius
+// Above D = 16: the new messages (buffer 1 - src) divided by their traces; with `record` the largest Frobenius
 // change against buffer src is folded into the residual word.
 __global__ __launch_bounds__(256) void k_bp_norm(DevState st, int src, int record) {
   __shared__ double red[4];
@@ -322,11 +367,7 @@ __global__ __launch_bounds__(256) void k_bp_norm(DevState st, int src, int recor
   }
   if (tid == 0) {
     if (!good) flag_status(st.status, kStatusNonFinite);
-    if (record) {
-      const double r = sqrt((red[0] + red[1]) + (red[2] + red[3]));
-      // non-negative doubles order like their bit patterns
-      atomicMax(st.bp_res, (unsigned long long)__double_as_longlong(isfinite(r) ? r : 0.0));
-    }
+    if (record) bp_record(st, (red[0] + red[1]) + (red[2] + red[3]));
   }
 }
 
@@ -338,12 +379,14 @@ __device__ __forceinline__ int bp_vertex_slot(const DevState& st, const VertexIn
 // BP readout from the messages of buffer `buf`: rho[s, s] of the rows a0 .. a0 + 15 of the first leg
 // of a qubit, into the other buffer (free after the last iteration): two doubles per block of rows,
 // at the slot of the qubit's first leg.  Qubits without legs are left to k_bp_z.
-template <typename CT, int NB>
-__global__ __launch_bounds__(kBpThreads) void k_bp_readout(DevState st, int buf) {
-  __shared__ double2 Xs[bp_lds<NB>()];
-  __shared__ double2 W1[16 * NB * (16 * NB + 1)];
-  __shared__ double sl[3][16 * NB];
-  __shared__ double red[kBpWaves];
+template <typename CT, int N>
+__global__ __launch_bounds__(bp_threads<N>()) void k_bp_readout(DevState st, int buf) {
+  constexpr int NB = bp_tiles<N>();
+  constexpr int kWaves = bp_threads<N>() / 64;
+  __shared__ double2 Xs[bp_lds<N>()];
+  __shared__ double2 W1[N * (N + 1)];
+  __shared__ double sl[3][N];
+  __shared__ double red[kWaves];
   const int D = st.D;
   const int nab = (D + 15) >> 4;
   const int v = blockIdx.x / nab, ab = blockIdx.x - v * nab, a0 = 16 * ab;
@@ -370,7 +413,7 @@ __global__ __launch_bounds__(kBpThreads) void k_bp_readout(DevState st, int buf)
   const double2* M0 = msg + (int64_t)g.in[0] * D * D;
   const double2* M1 = g.in[1] >= 0 ? msg + (int64_t)g.in[1] * D * D : nullptr;
   const double2* M2 = g.in[2] >= 0 ? msg + (int64_t)g.in[2] * D * D : nullptr;
-  bp_weights<NB>(st, g, M1, sl, W1);
+  bp_weights<N>(st, g, M1, sl, W1);
   for (int s = 0; s < 2; ++s) {
     bp_d4 mr[NB], mi[NB];
 #pragma unroll
@@ -378,10 +421,10 @@ __global__ __launch_bounds__(kBpThreads) void k_bp_readout(DevState st, int buf)
       mr[t] = (bp_d4){0.0, 0.0, 0.0, 0.0};
       mi[t] = (bp_d4){0.0, 0.0, 0.0, 0.0};
     }
-    if (a0 < g.dim[0]) bp_block<CT, NB>(reinterpret_cast<const CT*>(st.gamma), g, W1, M2, D, sl, a0, s, Xs, mr, mi);
+    if (a0 < g.dim[0]) bp_block<CT, N>(reinterpret_cast<const CT*>(st.gamma), g, W1, M2, D, sl, a0, s, Xs, mr, mi);
     // rho[s, s] = sum_{a, a'} M0[a][a'] m[a][a'] (real: M0 and m are Hermitian)
     double acc = 0.0;
-    bp_reduce<NB>(Xs, mr, mi, [&](int i, int j, double2 m) {
+    bp_reduce<N>(Xs, mr, mi, [&](int i, int j, double2 m) {
       const int a = a0 + i;
       if (a < g.dim[0] && j < g.dim[0]) acc += cmul(M0[a * D + j], m).x * (sl[0][a] * sl[0][j]);
     });
@@ -390,7 +433,7 @@ __global__ __launch_bounds__(kBpThreads) void k_bp_readout(DevState st, int buf)
     __syncthreads();
     if (threadIdx.x == 0) {
       double r = 0.0;
-      for (int w = 0; w < kBpWaves; ++w) r += red[w];
+      for (int w = 0; w < kWaves; ++w) r += red[w];
       part[s] = r;
     }
     __syncthreads();
@@ -422,19 +465,20 @@ __global__ __launch_bounds__(256) void k_bp_z(DevState st, int buf) {
   st.z[v] = zv;
 }
 
-template <typename CT, int NB>
+template <typename CT, int N>
 void launch_bp_t(const DevState& st, int iters, hipStream_t stream) {
   const int slots = 2 * st.NE, nab = (st.D + 15) / 16;
+  constexpr int threads = bp_threads<N>();
   if (slots > 0) {
     hipLaunchKernelGGL(k_bp_init, dim3(slots), dim3(256), 0, stream, st);
     for (int it = 0; it < iters; ++it) {
-      hipLaunchKernelGGL((k_bp_update<CT, NB>), dim3(slots * nab), dim3(kBpThreads), 0, stream, st, it & 1);
-      hipLaunchKernelGGL(k_bp_norm, dim3(slots), dim3(256), 0, stream, st, it & 1, (int)(it == iters - 1));
+      const int last = it == iters - 1;
+      hipLaunchKernelGGL((k_bp_update<CT, N>), dim3(slots * nab), dim3(threads), 0, stream, st, it & 1, last);
+      if (N == 32) hipLaunchKernelGGL(k_bp_norm, dim3(slots), dim3(256), 0, stream, st, it & 1, last);
     }
   }
   if (st.NV > 0) {
-    if (slots > 0)
-      hipLaunchKernelGGL((k_bp_readout<CT, NB>), dim3(st.NV * nab), dim3(kBpThreads), 0, stream, st, iters & 1);
+    if (slots > 0) hipLaunchKernelGGL((k_bp_readout<CT, N>), dim3(st.NV * nab), dim3(threads), 0, stream, st, iters & 1);
     hipLaunchKernelGGL(k_bp_z<CT>, dim3((st.NV + 255) / 256), dim3(256), 0, stream, st, iters & 1);
   }
 }
@@ -476,12 +520,15 @@ hipError_t bp_scratch_address(void** ptr) {
 
 hipError_t launch_bp(bool c128, const DevState& st, int iters, hipStream_t stream) {
   if (st.D > kMaxD) return hipErrorInvalidValue;
-  if (st.D <= 16) {
-    if (c128) launch_bp_t<double2, 1>(st, iters, stream);
-    else launch_bp_t<float2, 1>(st, iters, stream);
+  if (st.D <= 8) {
+    if (c128) launch_bp_t<double2, 8>(st, iters, stream);
+    else launch_bp_t<float2, 8>(st, iters, stream);
+  } else if (st.D <= 16) {
+    if (c128) launch_bp_t<double2, 16>(st, iters, stream);
+    else launch_bp_t<float2, 16>(st, iters, stream);
   } else {
-    if (c128) launch_bp_t<double2, 2>(st, iters, stream);
-    else launch_bp_t<float2, 2>(st, iters, stream);
+    if (c128) launch_bp_t<double2, 32>(st, iters, stream);
+    else launch_bp_t<float2, 32>(st, iters, stream);
   }
   return hipGetLastError();
 }

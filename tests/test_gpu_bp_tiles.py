@@ -1,5 +1,5 @@
-"""Belief propagation at the bond dimensions where its 16 x 16 tiles end: one tile, one more column,
-two tiles, the smallest bonds; saturated bonds, senders with one, two and three legs.
+"""Belief propagation at the bond dimensions where its 16 x 16 tiles end: half a tile, one tile, one
+more column, two tiles, the smallest bonds; saturated bonds, senders with one, two and three legs.
 
 complex128 states against the BP oracle within 1e-10 (the parity of the complex128 path; the message
 products are float64 in both).
@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 TJ = -math.pi / 2
 
 
-@pytest.mark.parametrize("d", [1, 2, 5, 15, 16, 17, 20, 31, 32])
+@pytest.mark.parametrize("d", [1, 2, 5, 8, 9, 15, 16, 17, 20, 31, 32])
 def test_bp_tile_edges(d):
     import torch
     if not torch.cuda.is_available():
