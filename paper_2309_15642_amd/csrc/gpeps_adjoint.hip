@@ -365,52 +365,86 @@ struct Gemm {
   int ldc;
 };
 
+// This wave's number in its workgroup, the same on all its lanes.
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
+
 __device__ __forceinline__ int gemm_tiles(const Gemm& g) { return ((g.m + 15) >> 4) * ((g.n + 15) >> 4); }
 
-// 16 x 16 output tile `tile` of g, by one wave, on v_mfma_f64_16x16x4f64 (lane l holds A[l % 16][l / 16]
-// and B[l / 16][l % 16] and receives D[l / 16 + 4 r][l % 16]), four real products per complex one;
-// operands are read straight from memory.
-__device__ __forceinline__ void gemm_tile(const Gemm& g, int tile, bool accumulate) {
-  typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double adj_d4 __attribute__((ext_vector_type(4)));
+typedef double adj_d2 __attribute__((ext_vector_type(2)));
+// A descriptor's pointers come back from LDS, where the compiler loses that they are global ones:
+// said here, or every access is a flat one, which also waits on LDS.
+typedef __attribute__((address_space(1))) adj_d2 adj_mem;
+
+// Adds the 16 x 16 tile (ti, tj) of g's product to (cr, ci), by one wave, on v_mfma_f64_16x16x4f64 (lane l
+// holds A[l % 16][l / 16] and B[l / 16][l % 16] and receives D[l / 16 + 4 r][l % 16]), four real
+// products per complex one; operands are read straight from memory, those of the next four k steps
+// while the current ones are multiplied.  Indices past the end are clamped, so that no load waits for a
+// branch or a select: rows and columns past m and n are not stored, and the products past k are
+// zeroed in A when they are used.
+__device__ __forceinline__ void gemm_acc(const Gemm& g, int ti, int tj, adj_d4& cr, adj_d4& ci) {
   const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
-  const int tn = (g.n + 15) >> 4, ks = (g.k + 3) >> 2;
-  const int ti = tile / tn, tj = tile - (tile / tn) * tn;
-  const int i = 16 * ti + li, j = 16 * tj + li;
-  d4 cr = {0.0, 0.0, 0.0, 0.0}, ci = {0.0, 0.0, 0.0, 0.0};
+  const int K = __builtin_amdgcn_readfirstlane(g.k), ks = (K + 3) >> 2;
+  const int i = min(16 * ti + li, g.m - 1), j = min(16 * tj + li, g.n - 1);
+  const int sa = (g.opA & 1) ? g.lda : 1, sb = (g.opB & 1) ? 1 : g.ldb;  // strides of k
+  const double ca = (g.opA & 2) ? -1.0 : 1.0, cb = (g.opB & 2) ? -1.0 : 1.0;
+  const adj_mem* const A = (const adj_mem*)g.A + i * ((g.opA & 1) ? 1 : g.lda);
+  const adj_mem* const B = (const adj_mem*)g.B + j * ((g.opB & 1) ? g.ldb : 1);
+  adj_d4 er = {0.0, 0.0, 0.0, 0.0}, ei = {0.0, 0.0, 0.0, 0.0};
+  adj_d2 na[4], nb[4];
+  auto fetch = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int kk = min(4 * (s0 + u) + lk, K - 1);
+      na[u] = A[kk * sa];
+      nb[u] = B[kk * sb];
+    }
+  };
+  if (K <= 0) return;
+  fetch(0);
   for (int s0 = 0; s0 < ks; s0 += 4) {
     double2 a[4], b[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int kk = 4 * (s0 + u) + lk;
-      a[u] = make_double2(0.0, 0.0);
-      b[u] = make_double2(0.0, 0.0);
-      if (i < g.m && kk < g.k) {
-        a[u] = (g.opA & 1) ? g.A[kk * g.lda + i] : g.A[i * g.lda + kk];
-        if (g.opA & 2) a[u] = cconj(a[u]);
-      }
-      if (j < g.n && kk < g.k) {
-        b[u] = (g.opB & 1) ? g.B[j * g.ldb + kk] : g.B[kk * g.ldb + j];
-        if (g.opB & 2) b[u] = cconj(b[u]);
-      }
+      const double in = 4 * (s0 + u) + lk < K ? 1.0 : 0.0;
+      a[u] = make_double2(in * na[u].x, in * ca * na[u].y);
+      b[u] = make_double2(nb[u].x, cb * nb[u].y);
     }
+    if (s0 + 4 < ks) fetch(s0 + 4);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (s0 + u < ks) {
         cr = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, b[u].x, cr, 0, 0, 0);
-        cr = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[u].y, b[u].y, cr, 0, 0, 0);
         ci = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, b[u].y, ci, 0, 0, 0);
-        ci = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, b[u].x, ci, 0, 0, 0);
+        er = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[u].y, b[u].y, er, 0, 0, 0);
+        ei = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, b[u].x, ei, 0, 0, 0);
       }
     }
   }
+  cr += er;
+  ci += ei;
+}
+
+__device__ __forceinline__ void gemm_store(const Gemm& g, int ti, int tj, const adj_d4& cr, const adj_d4& ci,
+                                           bool accumulate) {
+  const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
+  adj_mem* const C = (adj_mem*)g.C;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int ii = 16 * ti + lk + 4 * r, jj = 16 * tj + li;
     if (ii < g.m && jj < g.n) {
-      const double2 v = make_double2(cr[r], ci[r]);
-      g.C[ii * g.ldc + jj] = accumulate ? cadd(g.C[ii * g.ldc + jj], v) : v;
+      const adj_d2 v = {cr[r], ci[r]};
+      C[ii * g.ldc + jj] = accumulate ? C[ii * g.ldc + jj] + v : v;
     }
   }
+}
+
+__device__ __forceinline__ void gemm_tile(const Gemm& g, int tile, bool accumulate) {
+  const int tn = (g.n + 15) >> 4;
+  const int ti = tile / tn, tj = tile - (tile / tn) * tn;
+  adj_d4 cr = {0.0, 0.0, 0.0, 0.0}, ci = {0.0, 0.0, 0.0, 0.0};
+  gemm_acc(g, ti, tj, cr, ci);
+  gemm_store(g, ti, tj, cr, ci, accumulate);
 }
 
 // NG mutually independent products: their output tiles are spread over the waves of the block
@@ -426,7 +460,7 @@ __device__ void bgemm_batch(const Gemm (&gs)[NG], Gemm* gd, bool accumulate) {
 #pragma unroll
   for (int i = 0; i < NG; ++i) tot += gemm_tiles(gs[i]);
   __syncthreads();
-  for (int tile = (int)(threadIdx.x >> 6); tile < tot; tile += (int)(blockDim.x >> 6)) {
+  for (int tile = wave_id(); tile < tot; tile += (int)(blockDim.x >> 6)) {
     int i = 0, t = tile;
     while (t >= gemm_tiles(gd[i])) {
       t -= gemm_tiles(gd[i]);
@@ -438,12 +472,29 @@ __device__ void bgemm_batch(const Gemm (&gs)[NG], Gemm* gd, bool accumulate) {
   __syncthreads();
 }
 
-__device__ void bgemm(int m, int n, int k, const double2* A, int lda, int opA, const double2* B, int ldb, int opB,
-                      double2* C, int ldc, bool accumulate) {
-  const Gemm g = {m, n, k, A, lda, opA, B, ldb, opB, C, ldc};
-  for (int tile = (int)(threadIdx.x >> 6); tile < gemm_tiles(g); tile += (int)(blockDim.x >> 6))
+__device__ void bgemm(const Gemm& g, bool accumulate) {
+  for (int tile = wave_id(); tile < gemm_tiles(g); tile += (int)(blockDim.x >> 6))
     gemm_tile(g, tile, accumulate);
   __syncthreads();
+}
+
+// C = g + h, two products into one output (g's).
+__device__ void bgemm_sum(const Gemm& g, const Gemm& h) {
+  const int tn = (g.n + 15) >> 4;
+  for (int tile = wave_id(); tile < gemm_tiles(g); tile += (int)(blockDim.x >> 6)) {
+    const int ti = tile / tn, tj = tile - (tile / tn) * tn;
+    adj_d4 cr = {0.0, 0.0, 0.0, 0.0}, ci = {0.0, 0.0, 0.0, 0.0};
+    gemm_acc(g, ti, tj, cr, ci);
+    gemm_acc(h, ti, tj, cr, ci);
+    gemm_store(g, ti, tj, cr, ci, false);
+  }
+  __syncthreads();
+}
+
+// x of the lane `lane` (the same on every lane).
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                          __builtin_amdgcn_readlane(__double2loint(x), lane));
 }
 
 // REC: the forward recovered one singular-vector set as Theta' v / sigma (complex64 path), which
@@ -454,14 +505,21 @@ __device__ void bgemm(int m, int n, int k, const double2* A, int lda, int opA, c
 // retained or not, and the result does not depend on how the forward resolved them.  Without
 // REC (both sets accumulated, complex128) every triplet above 1e-13 s_0 is retained and the
 // complement takes 1 / s_k.
-template <bool REC>
-__global__ __launch_bounds__(256) void k_adj_small(DevState st, const int32_t* __restrict__ items, int first,
-                                                   double2* __restrict__ ybuf) {
-  __shared__ double red[256];
-  __shared__ double Sv[2 * kMaxD], Sb[2 * kMaxD], Lb[kMaxD], lam[kMaxD];
+//
+// N bounds D (16 or 32).  One workgroup per edge and few edges a launch: bound by the latency of its
+// chain of small products, so the operands of the next k steps are in flight during the current ones,
+// eight waves share the tiles of a batch, and the eliminations run in registers.
+// Measured on the 48 edges of a class of the 127-qubit graph: MEASURED16 at D = 16, MEASURED32 at D = 32.
+constexpr int kSmallThreads = 512;
+
+template <bool REC, int N>
+__global__ __launch_bounds__(kSmallThreads) void k_adj_small(DevState st, const int32_t* __restrict__ items, int first,
+                                                             double2* __restrict__ ybuf) {
+  __shared__ double red[kSmallThreads];
+  __shared__ double Sv[2 * N], Sb[2 * N], Lb[N], lam[N], Lo[N];
   __shared__ int sh_rp;
-  __shared__ double Pt[kMaxD][kMaxD + 1];              // elementwise products, reduced by rows / columns
-  __shared__ double2 GZ[4][kMaxD][2 * kMaxD + 1];      // [G | Z] of the four QR backwards (Gauss-Jordan)
+  __shared__ double Pt[N][N + 1];      // elementwise products, reduced by rows / columns
+  __shared__ double2 Yt[4][N][N + 1];  // Y of the four QR backwards
   __shared__ Gemm gdesc[8];                            // descriptors of a batch of small products
   const int slot = blockIdx.x;
   const int e = items[first + slot];
@@ -510,13 +568,15 @@ __global__ __launch_bounds__(256) void k_adj_small(DevState st, const int32_t* _
                             {gate_dphase(ip, 1, 0), gate_dphase(ip, 1, 1)}};
 
   for (int k = tid; k < rr; k += blockDim.x) Sv[k] = st.bS[(int64_t)slot * NM + k];
-  for (int k = tid; k < kMaxD; k += blockDim.x) lam[k] = k < de ? lam_g[k] : 0.0;
-  if (tid == 0) {
-    int rp = 0;
-    const double s0 = st.bS[(int64_t)slot * NM];
+  for (int k = tid; k < N; k += blockDim.x) {
+    lam[k] = k < de ? lam_g[k] : 0.0;
+    Lo[k] = k < chi ? lbar_e[k] : 0.0;
+  }
+  if (tid < 64) {  // rr <= 2 N <= 64
     const double tau = REC ? kRecTau : 1e-13;
-    for (int k = 0; k < rr; ++k) rp += st.bS[(int64_t)slot * NM + k] > tau * s0;
-    sh_rp = rp > chi ? rp : chi;
+    const double s = tid < rr ? st.bS[(int64_t)slot * NM + tid] : 0.0;
+    const int rp = __popcll(__ballot(tid < rr && s > tau * lane_value(s, 0)));
+    if (tid == 0) sh_rp = rp > chi ? rp : chi;
   }
   __syncthreads();
   const int rp = sh_rp;
@@ -526,7 +586,7 @@ __global__ __launch_bounds__(256) void k_adj_small(DevState st, const int32_t* _
   double nrm2 = 0.0, ls = 0.0;
   for (int k = 0; k < chi; ++k) {
     nrm2 += Sv[k] * Sv[k];
-    ls += lbar_e[k] * Sv[k];
+    ls += Lo[k] * Sv[k];
   }
   const double nrm = sqrt(nrm2);
   // P[k][k'] = sum_w Re conj(TB_w[k][k']) T64_w[k][k'] in parallel, then its column sums give
@@ -542,7 +602,7 @@ __global__ __launch_bounds__(256) void k_adj_small(DevState st, const int32_t* _
   for (int kp = tid; kp < rr; kp += blockDim.x) {
     double sb = 0.0;
     if (kp < chi) {
-      sb = lbar_e[kp] / nrm - Sv[kp] * ls / (nrm2 * nrm);
+      sb = Lo[kp] / nrm - Sv[kp] * ls / (nrm2 * nrm);
       double t = 0.0;
       for (int k = 0; k < de; ++k) t += Pt[k][kp];
       sb -= t / Sv[kp];
@@ -648,9 +708,8 @@ __global__ __launch_bounds__(256) void k_adj_small(DevState st, const int32_t* _
   }
   __syncthreads();
   // M1 += U In ;  Theta'-bar = M1 V^H + U Vp^H
-  bgemm(m0, rp, rp, U, NM, 0, In, NM, 0, M1, NM, true);
-  bgemm(m0, n0, rp, M1, NM, 0, V, NM, 3, Thb, NM, false);
-  bgemm(m0, n0, rp, U, NM, 0, Vp, NM, 3, Thb, NM, true);
+  bgemm({m0, rp, rp, U, NM, 0, In, NM, 0, M1, NM}, true);
+  bgemm_sum({m0, n0, rp, M1, NM, 0, V, NM, 3, Thb, NM}, {m0, n0, rp, U, NM, 0, Vp, NM, 3, Thb, NM});
 
   // ---- Theta' backward: H_st = Thb_st conj(R_j^(t))  [ri x de]
   {
@@ -705,9 +764,9 @@ __global__ __launch_bounds__(256) void k_adj_small(DevState st, const int32_t* _
   // ---- QR backward of the four (end, slice) blocks, solved together.  A block that was not
   // reduced (M <= D_e, R = A) has A-bar = R-bar.  For the others G = R^H R and Z = R^H R-bar
   // (one batch of products; G in the H region, finished with above), then
-  // Y = (G + delta I)^-1 Z by Gauss-Jordan elimination of [G + delta I | Z] in LDS (Hermitian
-  // positive definite: no pivoting), one wave per block and one lane per column, so the four
-  // run side by side with no workgroup barrier.
+  // Y = (G + delta I)^-1 Z by Gauss-Jordan elimination of [G + delta I | Z] (Hermitian positive
+  // definite: no pivoting), one wave per block and one lane per column with the column in
+  // registers, so the four run side by side with no workgroup barrier.
   bool redw[4];
 #pragma unroll
   for (int w = 0; w < 4; ++w) redw[w] = Ms[w >> 1] > de;
@@ -733,38 +792,46 @@ __global__ __launch_bounds__(256) void k_adj_small(DevState st, const int32_t* _
     bgemm_batch(gs, gdesc, false);
   }
   {
-    // wave w solves system w; lane c owns column c of [G | Z] (G: c < de, Z: kMaxD <= c < kMaxD + de)
+    // wave w solves system w; lane c owns column c of [G | Z] (G: c < de, Z: N <= c < N + de).  Before
+    // step p, x[i] is row (p + i) % N: the pivot row is always x[0] and each step moves the rows up
+    // by one, so that one copy of the step serves all (rows from de on stay zero).
     const int wq = tid >> 6, lc = tid & 63;
     if (wq < 4 && redw[wq]) {
-      const bool gcol = lc < de, zcol = lc >= kMaxD && lc < kMaxD + de;
-      for (int a = 0; a < de; ++a) {
-        if (gcol) GZ[wq][a][lc] = H[wq * q + a * D + lc];
-        if (zcol) GZ[wq][a][lc] = Yout[wq * q + a * D + lc - kMaxD];
+      const bool gcol = lc < de, zcol = lc >= N && lc < N + de;
+      const double2* src = gcol ? H + wq * q + lc : Yout + wq * q + (zcol ? lc - N : 0);
+      double2 x[N];
+      double dmax = 0.0;
+#pragma unroll
+      for (int a = 0; a < N; ++a) {
+        x[a] = a < de ? src[a * D] : make_double2(0.0, 0.0);
+        if (!gcol && !zcol) x[a] = make_double2(0.0, 0.0);
+        if (gcol && a == lc) dmax = x[a].x;
       }
-      wave_lds_sync();
-      double dmax = gcol ? GZ[wq][lc][lc].x : 0.0;
       dmax = wave_max(dmax);
-      if (gcol) GZ[wq][lc][lc].x += 1e-13 * (dmax > 0.0 ? dmax : 1.0);
-      wave_lds_sync();
+      const double delta = 1e-13 * (dmax > 0.0 ? dmax : 1.0);
+#pragma unroll
+      for (int a = 0; a < N; ++a)
+        if (gcol && a == lc) x[a].x += delta;
       for (int p = 0; p < de; ++p) {
-        // scale row p (columns > p of G and all of Z) by 1 / G[p][p] (real: Hermitian), then
-        // eliminate column p from the other rows; column p itself is not written in this step
-        const double ip = 1.0 / GZ[wq][p][p].x;
-        const bool act = (lc > p && lc < de) || zcol;
-        if (act) {
-          const double2 rpc = cscale(GZ[wq][p][lc], ip);
-          GZ[wq][p][lc] = rpc;
-          for (int a = 0; a < de; ++a)
-            if (a != p) GZ[wq][a][lc] = csub(GZ[wq][a][lc], cmul(GZ[wq][a][p], rpc));
+        // scale the pivot row by 1 / G[p][p] (real: Hermitian), then eliminate column p from the others
+        const double ip = 1.0 / lane_value(x[0].x, p);
+        const double2 rpc = cscale(x[0], ip);
+#pragma unroll
+        for (int i = 1; i < N; ++i) {
+          const double2 f = make_double2(lane_value(x[i].x, p), lane_value(x[i].y, p));
+          x[i - 1] = csub(x[i], cmul(f, rpc));
         }
-        wave_lds_sync();
+        x[N - 1] = rpc;
       }
-      // Hermitian part of Y
+      // Hermitian part of Y; row a ended at x[N - de + a]
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (zcol && i >= N - de) Yt[wq][i - (N - de)][lc - N] = x[i];
+      wave_lds_sync();
       if (zcol) {
-        const int b = lc - kMaxD;
+        const int b = lc - N;
         for (int a = 0; a < de; ++a) {
-          const double2 x = GZ[wq][a][kMaxD + b], y = GZ[wq][b][kMaxD + a];
-          double2 h = cscale(cadd(x, cconj(y)), 0.5);
+          double2 h = cscale(cadd(Yt[wq][a][b], cconj(Yt[wq][b][a])), 0.5);
           if (a == b) h.y = 0.0;
           Yout[wq * q + a * D + b] = h;
         }
@@ -776,7 +843,7 @@ __global__ __launch_bounds__(256) void k_adj_small(DevState st, const int32_t* _
 
   // ---- pre-gate lambda_e adjoint and dL/dtheta_J
   for (int k = tid; k < D; k += blockDim.x) lbar_e[k] = k < de ? Lb[k] : 0.0;
-  const double tot = block_sum<256>(thj, red);
+  const double tot = block_sum<kSmallThreads>(thj, red);
   // one item per edge in a launch: the edge's own accumulator, summed per instance at the end
   if (tid == 0) st.gpart[e] += tot;
 }
@@ -955,8 +1022,11 @@ static hipError_t adj_launch(int which, const DevState& st, const int32_t* items
       break;
     case 2:
       if (count <= 0) return hipSuccess;
-      hipLaunchKernelGGL((k_adj_small<std::is_same<CT, float2>::value>), dim3(count), dim3(256), 0, stream, st,
-                         items, first, (double2*)aux);
+      {
+        constexpr bool kRec = std::is_same<CT, float2>::value;
+        const auto kern = st.D <= 16 ? k_adj_small<kRec, 16> : k_adj_small<kRec, 32>;
+        hipLaunchKernelGGL(kern, dim3(count), dim3(kSmallThreads), 0, stream, st, items, first, (double2*)aux);
+      }
       break;
     case 3:
       if (count <= 0) return hipSuccess;

@@ -88,7 +88,10 @@ __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSit
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, li = l & 15, lk = l >> 4;
   const int na = g.dim[0], nb = g.dim[1], nc = g.dim[2];
   const CT* const gs = gam + g.base + s * g.pstride;
-  const CT czero = from_d2<CT>(make_double2(0.0, 0.0));
+  // loads are at a valid offset in any case and zeroed when they are used: a choice between the
+  // element and a zero becomes a flat load through the stack, and a select at the load waits for it
+  auto at = [&](bool v, int off) -> CT { return gs[v ? off : 0]; };
+  auto pick = [](bool v, const CT& x) { return v ? to_d2(x) : make_double2(0.0, 0.0); };
   const int ta = g.st[0], tb = g.st[1], tc = g.st[2];  // (a tensor has at most 2^16 elements)
   const int kb = (nb + 3) >> 2, kc = (nc + 3) >> 2;
   const bool av = a0 + li < na;
@@ -103,7 +106,7 @@ __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSit
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         const int c = 4 * ks + lk;
-        nx[ks] = (av && c < nc) ? gs[arow + b * tb + c * tc] : czero;
+        nx[ks] = at(av && c < nc, arow + b * tb + c * tc);
       }
     };
     if (wv < nb) fetch(wv);
@@ -116,7 +119,7 @@ __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSit
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         if (ks < kc) {
-          const double2 a = to_d2(x[ks]);
+          const double2 a = pick(av && 4 * ks + lk < nc, x[ks]);
           xr = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, w2[ks].x, xr, 0, 0, 0);
           xi = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, w2[ks].y, xi, 0, 0, 0);
           xr = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, w2[ks].y, xr, 0, 0, 0);
@@ -133,13 +136,13 @@ __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSit
       // the elements of the last product (its first PF column tiles) ahead: they arrive while Y is
       // formed; complex128 has registers for one tile in flight
       CT ga[PF][NB][R4];
-      auto fetch_last = [&](int at, CT (&x)[NB][R4]) {
+      auto fetch_last = [&](int ta2, CT (&x)[NB][R4]) {
 #pragma unroll
         for (int t = 0; t < NB; ++t)
 #pragma unroll
           for (int r = 0; r < R4; ++r) {
-            const int a2 = 16 * at + li, b2 = 16 * t + 4 * r + lk;
-            x[t][r] = (a2 < na && b2 < nb) ? gs[a2 * ta + b2 * tb + (16 * j + cp) * tc] : czero;
+            const int a2 = 16 * ta2 + li, b2 = 16 * t + 4 * r + lk;
+            x[t][r] = at(a2 < na && b2 < nb, a2 * ta + b2 * tb + (16 * j + cp) * tc);
           }
       };
 #pragma unroll
@@ -174,7 +177,7 @@ __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSit
 #pragma unroll
             for (int r = 0; r < R4; ++r) {
               if (16 * t + 4 * r < nb) {
-                const double2 c = to_d2(ga[at % PF][t][r]);  // conjugated below
+                const double2 c = pick(16 * at + li < na && 16 * t + 4 * r + lk < nb, ga[at % PF][t][r]);  // conjugated below
                 mr[at] = __builtin_amdgcn_mfma_f64_16x16x4f64(yr[t][r], c.x, mr[at], 0, 0, 0);
                 mi[at] = __builtin_amdgcn_mfma_f64_16x16x4f64(yi[t][r], c.x, mi[at], 0, 0, 0);
                 mr[at] = __builtin_amdgcn_mfma_f64_16x16x4f64(yi[t][r], c.y, mr[at], 0, 0, 0);
