@@ -109,19 +109,17 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
     const int wv = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
     const int tm = (m0 + 15) >> 4, tn = (n0 + 15) >> 4;
     auto fa = [&](int i, int k) -> double2 {
-      if (i >= m0 || k >= de) return make_double2(0.0, 0.0);
       const int s = i / ri, a = i - (i / ri) * ri;
       return cscale(Rg[(int64_t)s * D * D + a * D + k], lam_old[k]);
     };
     auto fb = [&](int k, int j) -> double2 {
-      if (j >= n0 || k >= de) return make_double2(0.0, 0.0);
       const int t = j / rj, b = j - (j / rj) * rj;
       return Rg[(int64_t)(2 + t) * D * D + b * D + k];
     };
     for (int tile = wv; tile < tm * tn; tile += kBT / 64) {
       const int ti = tile / tn, tj = tile - (tile / tn) * tn;
       cgemm_d4 cr, ci;
-      cgemm_tile(16 * ti, 16 * tj, de, fa, fb, cr, ci);
+      cgemm_tile<true>(16 * ti, 16 * tj, m0, n0, de, fa, fb, cr, ci);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = 16 * ti + lk + 4 * r, col = 16 * tj + li;
@@ -567,17 +565,15 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
     const int wv = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
     const int tm = (mO + 15) >> 4, tn = (chi + 15) >> 4;
     auto fa = [&](int i, int q) -> double2 {
-      if (i >= mO || q >= nB) return make_double2(0.0, 0.0);
       return trans ? cconj(Tg[q * kBN + i]) : Tg[i * kBN + q];
     };
     auto fb = [&](int q, int j) -> double2 {
-      if (q >= nB || j >= chi) return make_double2(0.0, 0.0);
       return X[j][q];
     };
     for (int tile = wv; tile < tm * tn; tile += kBT / 64) {
       const int ti = tile / tn, tj = tile - (tile / tn) * tn;
       cgemm_d4 cr, ci;
-      cgemm_tile(16 * ti, 16 * tj, nB, fa, fb, cr, ci);
+      cgemm_tile<true>(16 * ti, 16 * tj, mO, chi, nB, fa, fb, cr, ci);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int rr = 16 * ti + lk + 4 * r, kp = 16 * tj + li;
@@ -590,8 +586,16 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
   }
   __syncthreads();
   // U[(s,a)][k'] and V[(t,b)][k'] wherever they are
-  auto Uv = [&](int row, int kp) -> double2 { return trans ? X[kp][row] : Og[row * kMaxDBig + kp]; };
-  auto Vv = [&](int row, int kp) -> double2 { return trans ? Og[row * kMaxDBig + kp] : X[kp][row]; };
+  // (said to be global, or the choice becomes a flat load, which waits for LDS and memory alike)
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  const __attribute__((address_space(1))) d2* const Om = (const __attribute__((address_space(1))) d2*)Og;
+  auto from_x = [&](int row, int kp) -> double2 { return X[kp][row]; };
+  auto from_o = [&](int row, int kp) -> double2 {
+    const d2 v = Om[row * kMaxDBig + kp];
+    return make_double2(v.x, v.y);
+  };
+  auto Uv = [&](int row, int kp) -> double2 { return trans ? from_x(row, kp) : from_o(row, kp); };
+  auto Vv = [&](int row, int kp) -> double2 { return trans ? from_o(row, kp) : from_x(row, kp); };
 
   CT* T = reinterpret_cast<CT*>(st.tbuf);
   for (int idx = tid; idx < 4 * de * (D - chi); idx += kBT) {
@@ -619,19 +623,19 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
         const double2* RJ = h ? RJ1 : RJ0;
         const double2* RI = h ? RI1 : RI0;
         auto fjx = [&](int k, int b) -> double2 {
-          return (k < de && b < rj) ? RJ[b * D + k] : make_double2(0.0, 0.0);
+          return RJ[b * D + k];
         };
         auto fjv = [&](int b, int kp) -> double2 {
-          return (b < rj && kp < chi) ? Vv(h * rj + b, kp) : make_double2(0.0, 0.0);
+          return Vv(h * rj + b, kp);
         };
         auto fix = [&](int k, int a) -> double2 {
-          return (k < de && a < ri) ? RI[a * D + k] : make_double2(0.0, 0.0);
+          return RI[a * D + k];
         };
         auto fiu = [&](int a, int kp) -> double2 {
-          return (a < ri && kp < chi) ? cconj(Uv(h * ri + a, kp)) : make_double2(0.0, 0.0);
+          return cconj(Uv(h * ri + a, kp));
         };
-        cgemm_tile(16 * ti, 16 * tj, rj, fjx, fjv, xr[h], xi[h]);
-        cgemm_tile(16 * ti, 16 * tj, ri, fix, fiu, yr[h], yi[h]);
+        cgemm_tile<true>(16 * ti, 16 * tj, de, chi, rj, fjx, fjv, xr[h], xi[h]);
+        cgemm_tile<true>(16 * ti, 16 * tj, de, chi, ri, fix, fiu, yr[h], yi[h]);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {

@@ -326,31 +326,49 @@ __host__ __device__ inline int row_grid(const DevState& st, int count, int bps) 
 
 // One 16 x 16 tile of a complex product C[i][j] = sum_k A(i, k) B(k, j), by one wave on
 // v_mfma_f64_16x16x4f64 (lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] of each k step
-// of 4 and receives C[l / 16 + 4 r][l % 16]), four real products per complex one.  fa(i, k) and
-// fb(k, j) return the operands (zero past the matrix); the tile's rows start at i0, its columns
-// at j0, K is the inner dimension.  Lane l ends with C[i0 + l / 16 + 4 r][j0 + l % 16] in
-// (cr[r], ci[r]).  Every lane of the wave must be active.
+// of 4 and receives C[l / 16 + 4 r][l % 16]), four real products per complex one.  C is M x N, K the
+// inner dimension; the tile's rows start at i0, its columns at j0.  fa(i, k) and fb(k, j) return the
+// operands: they are asked for valid entries only (indices clamped) and zeroed past the end when
+// they are used, so the loads of 16 k steps are all in flight at once; a bounds test around each
+// made them wait for one another.  Lane l ends with C[i0 + l / 16 + 4 r][j0 + l % 16], zero past the
+// matrix, in (cr[r], ci[r]).  Every lane of the wave must be active.  AHEAD: the operands of the next
+// 16 k steps load during the products (for operands in global memory and K > 16).
 typedef double cgemm_d4 __attribute__((ext_vector_type(4)));
-template <class FA, class FB>
-__device__ __forceinline__ void cgemm_tile(int i0, int j0, int K, FA fa, FB fb, cgemm_d4& cr, cgemm_d4& ci) {
+template <bool AHEAD = false, class FA, class FB>
+__device__ __forceinline__ void cgemm_tile(int i0, int j0, int M, int N, int K, FA fa, FB fb, cgemm_d4& cr,
+                                           cgemm_d4& ci) {
   const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
+  const bool vi = i0 + li < M, vj = j0 + li < N;
+  const int i = vi ? i0 + li : 0, j = vj ? j0 + li : 0;
   cr = (cgemm_d4){0.0, 0.0, 0.0, 0.0};
   ci = (cgemm_d4){0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    double2 a[4], b[4];
+  double2 a[4], b[4];
+  auto fetch = [&](int k0) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int k = k0 + 4 * u + lk;
-      a[u] = fa(i0 + li, k);
-      b[u] = fb(k, j0 + li);
+      const int k = min(k0 + 4 * u + lk, K - 1);
+      a[u] = fa(i, k);
+      b[u] = fb(k, j);
     }
+  };
+  if (AHEAD) fetch(0);
+  for (int k0 = 0; k0 < K; k0 += 16) {
+    if (!AHEAD) fetch(k0);
+    double2 x[4], y[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool vk = k0 + 4 * u + lk < K;
+      x[u] = vk && vi ? a[u] : make_double2(0.0, 0.0);
+      y[u] = vk && vj ? b[u] : make_double2(0.0, 0.0);
+    }
+    if (AHEAD && k0 + 16 < K) fetch(k0 + 16);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (k0 + 4 * u < K) {
-        cr = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, b[u].x, cr, 0, 0, 0);
-        cr = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[u].y, b[u].y, cr, 0, 0, 0);
-        ci = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, b[u].y, ci, 0, 0, 0);
-        ci = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, b[u].x, ci, 0, 0, 0);
+        cr = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u].x, y[u].x, cr, 0, 0, 0);
+        cr = __builtin_amdgcn_mfma_f64_16x16x4f64(-x[u].y, y[u].y, cr, 0, 0, 0);
+        ci = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u].x, y[u].y, ci, 0, 0, 0);
+        ci = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u].y, y[u].x, ci, 0, 0, 0);
       }
     }
   }

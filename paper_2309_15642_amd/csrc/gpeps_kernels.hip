@@ -510,11 +510,19 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
 
   // stage the R factors of one end ([2][r][de], row stride DS) into an LDS region
   auto stage_r = [&](double2* dst, int side, int rows) {
-    for (int idx = tid; idx < 2 * rows * de; idx += NT) {
-      const int sl = idx / (rows * de);
-      const int rem = idx - sl * rows * de;
-      const int rr = rem / de, k = rem - (rem / de) * de;
-      dst[sl * DM * DS + rr * DS + k] = Rg[(int64_t)(side * 2 + sl) * D * D + rr * D + k];
+    constexpr int PT = 2 * DM * DM / NT;  // entries a thread, all in flight
+    double2 v[PT];
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+      const int idx = tid + q * NT;
+      const int sl = idx / (DM * DM), rr = (idx / DM) % DM, k = idx % DM;
+      v[q] = Rg[(side * 2 + sl) * D * D + min(rr, rows - 1) * D + min(k, de - 1)];
+    }
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+      const int idx = tid + q * NT;
+      const int sl = idx / (DM * DM), rr = (idx / DM) % DM, k = idx % DM;
+      if (rr < rows && k < de) dst[sl * DM * DS + rr * DS + k] = v[q];
     }
   };
 
@@ -542,11 +550,19 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
       const double2* Ra = Rg + (int64_t)s * D * D + a * D;
       const double2* Rb = Rg + (int64_t)(2 + t) * D * D + b * D;
       double2 x[KS], y[KS];
+      double w[KS];
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) {  // valid entries only: the loads do not wait for one another
+        const int k = min(4 * kk + lk, de - 1);
+        x[kk] = Ra[k];
+        y[kk] = Rb[k];
+        w[kk] = lam_e[k];
+      }
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
         const int k = 4 * kk + lk;
-        x[kk] = (rv && k < de) ? cscale(Ra[k], lam_e[k]) : make_double2(0.0, 0.0);
-        y[kk] = (cv && k < de) ? Rb[k] : make_double2(0.0, 0.0);
+        x[kk] = (rv && k < de) ? cscale(x[kk], w[kk]) : make_double2(0.0, 0.0);
+        y[kk] = (cv && k < de) ? y[kk] : make_double2(0.0, 0.0);
       }
       // The registers x, y serve C = X Y (A = X, B = Y) and C^T = Y^T X^T (A = Y^T, B = X^T)
       // alike; the orientation is chosen so that the 16 lanes sharing an output register
@@ -612,15 +628,15 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
     cgemm_d4 sr[TPW], si[TPW];
     {
       auto fa = [&](int i, int k) -> double2 {
-        return (i < nB && k < mB) ? cconj(B[i][k]) : make_double2(0.0, 0.0);
+        return cconj(B[i][k]);
       };
       auto fb = [&](int k, int jj) -> double2 {
-        return (k < mB && jj < nB) ? B[jj][k] : make_double2(0.0, 0.0);
+        return B[jj][k];
       };
 #pragma unroll
       for (int q = 0; q < TPW; ++q) {
         const int tile = wv + q * NW;
-        if (tile < tg * tg) cgemm_tile(16 * (tile / tg), 16 * (tile - (tile / tg) * tg), mB, fa, fb, sr[q], si[q]);
+        if (tile < tg * tg) cgemm_tile(16 * (tile / tg), 16 * (tile - (tile / tg) * tg), nB, nB, mB, fa, fb, sr[q], si[q]);
       }
     }
     auto tile_ij = [&](int q, int& ti, int& tj) {
@@ -1578,12 +1594,12 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
   #pragma unroll
         for (int h = 0; h < 2; ++h) {
           auto fa = [&](int k, int a) -> double2 {
-            return (k < de && a < ri) ? cconj(A1[h * DM * DS + a * DS + k]) : make_double2(0.0, 0.0);
+            return cconj(A1[h * DM * DS + a * DS + k]);
           };
           auto fb = [&](int a, int kp) -> double2 {
-            return (a < ri && kp < chi) ? A0[(h * ri + a) * DS + kp] : make_double2(0.0, 0.0);
+            return A0[(h * ri + a) * DS + kp];
           };
-          cgemm_tile(16 * ti, 16 * tj, ri, fa, fb, ar[h], ai[h]);
+          cgemm_tile(16 * ti, 16 * tj, de, chi, ri, fa, fb, ar[h], ai[h]);
         }
   #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -1620,12 +1636,12 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
   #pragma unroll
         for (int h = 0; h < 2; ++h) {
           auto fa = [&](int b, int k) -> double2 {
-            return (b < rj && k < de) ? cscale(cconj(A1[h * DM * DS + b * DS + k]), lam_old[k]) : make_double2(0.0, 0.0);
+            return cscale(cconj(A1[h * DM * DS + b * DS + k]), lam_old[k]);
           };
           auto fb = [&](int k, int kp) -> double2 {
-            return (k < de && kp < chi) ? A0[h * DM * DS + k * DS + kp] : make_double2(0.0, 0.0);
+            return A0[h * DM * DS + k * DS + kp];
           };
-          cgemm_tile(16 * ti, 16 * tj, de, fa, fb, ar[h], ai[h]);
+          cgemm_tile(16 * ti, 16 * tj, rj, chi, de, fa, fb, ar[h], ai[h]);
         }
       }
       __syncthreads();
@@ -1646,12 +1662,12 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
   #pragma unroll
         for (int h = 0; h < 2; ++h) {
           auto fa = [&](int k, int b) -> double2 {
-            return (k < de && b < rj) ? A1[h * DM * DS + b * DS + k] : make_double2(0.0, 0.0);
+            return A1[h * DM * DS + b * DS + k];
           };
           auto fb = [&](int b, int kp) -> double2 {
-            return (b < rj && kp < chi) ? A0[(h * rj + b) * DS + kp] : make_double2(0.0, 0.0);
+            return A0[(h * rj + b) * DS + kp];
           };
-          cgemm_tile(16 * ti, 16 * tj, rj, fa, fb, ar[h], ai[h]);
+          cgemm_tile(16 * ti, 16 * tj, de, chi, rj, fa, fb, ar[h], ai[h]);
         }
   #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -1671,12 +1687,12 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
   #pragma unroll
         for (int h = 0; h < 2; ++h) {
           auto fa = [&](int k, int b) -> double2 {
-            return (k < de && b < rj) ? A1[h * DM * DS + b * DS + k] : make_double2(0.0, 0.0);
+            return A1[h * DM * DS + b * DS + k];
           };
           auto fb = [&](int b, int kp) -> double2 {
-            return (b < rj && kp < chi) ? A0[(h * rj + b) * DS + kp] : make_double2(0.0, 0.0);
+            return A0[(h * rj + b) * DS + kp];
           };
-          cgemm_tile(16 * ti, 16 * tj, rj, fa, fb, ar[h], ai[h]);
+          cgemm_tile(16 * ti, 16 * tj, de, chi, rj, fa, fb, ar[h], ai[h]);
         }
   #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -1715,12 +1731,12 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
   #pragma unroll
         for (int h = 0; h < 2; ++h) {
           auto fa = [&](int a, int k) -> double2 {
-            return (a < ri && k < de) ? A1[h * DM * DS + a * DS + k] : make_double2(0.0, 0.0);
+            return A1[h * DM * DS + a * DS + k];
           };
           auto fb = [&](int k, int kp) -> double2 {
-            return (k < de && kp < chi) ? A0[h * DM * DS + k * DS + kp] : make_double2(0.0, 0.0);
+            return A0[h * DM * DS + k * DS + kp];
           };
-          cgemm_tile(16 * ti, 16 * tj, de, fa, fb, ar[h], ai[h]);
+          cgemm_tile(16 * ti, 16 * tj, ri, chi, de, fa, fb, ar[h], ai[h]);
         }
       }
       __syncthreads();
@@ -1741,12 +1757,12 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
   #pragma unroll
         for (int h = 0; h < 2; ++h) {
           auto fa = [&](int k, int a) -> double2 {
-            return (k < de && a < ri) ? A1[h * DM * DS + a * DS + k] : make_double2(0.0, 0.0);
+            return A1[h * DM * DS + a * DS + k];
           };
           auto fb = [&](int a, int kp) -> double2 {
-            return (a < ri && kp < chi) ? cconj(A0[(h * ri + a) * DS + kp]) : make_double2(0.0, 0.0);
+            return cconj(A0[(h * ri + a) * DS + kp]);
           };
-          cgemm_tile(16 * ti, 16 * tj, ri, fa, fb, ar[h], ai[h]);
+          cgemm_tile(16 * ti, 16 * tj, de, chi, ri, fa, fb, ar[h], ai[h]);
         }
   #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -1789,12 +1805,12 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
       for (int q = 0; q < HW; ++q) {
         const int h = wv + q;
         auto fa = [&](int k, int a) -> double2 {
-          return (k < de && a < ri) ? cconj(A1[h * DM * DS + a * DS + k]) : make_double2(0.0, 0.0);
+          return cconj(A1[h * DM * DS + a * DS + k]);
         };
         auto fb = [&](int a, int kp) -> double2 {
-          return (a < ri && kp < chi) ? A0[(h * ri + a) * DS + kp] : make_double2(0.0, 0.0);
+          return A0[(h * ri + a) * DS + kp];
         };
-        if (h < 2) cgemm_tile(0, 0, ri, fa, fb, c1r[q], c1i[q]);
+        if (h < 2) cgemm_tile(0, 0, de, chi, ri, fa, fb, c1r[q], c1i[q]);
       }
       meet();
       for (int idx = tid; idx < 256; idx += NT) {
@@ -1814,12 +1830,12 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
       // X_t = R_j^(t)T V_t (each wave on its own slice: no barrier between the two)
       for (int h = wv; h < 2; h += NW) {
         auto fa = [&](int b, int k) -> double2 {
-          return (b < rj && k < de) ? cscale(cconj(A1[h * DM * DS + b * DS + k]), lam_old[k]) : make_double2(0.0, 0.0);
+          return cscale(cconj(A1[h * DM * DS + b * DS + k]), lam_old[k]);
         };
         auto fb = [&](int k, int kp) -> double2 {
-          return (k < de && kp < chi) ? A0[h * DM * DS + k * DS + kp] : make_double2(0.0, 0.0);
+          return A0[h * DM * DS + k * DS + kp];
         };
-        cgemm_tile(0, 0, de, fa, fb, cr, ci);
+        cgemm_tile(0, 0, rj, chi, de, fa, fb, cr, ci);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const double is = li < chi ? 1.0 / sig[perm[li]] : 0.0;
@@ -1827,10 +1843,10 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
         }
         wave_lds_sync();
         auto fc = [&](int k, int b) -> double2 {
-          return (k < de && b < rj) ? A1[h * DM * DS + b * DS + k] : make_double2(0.0, 0.0);
+          return A1[h * DM * DS + b * DS + k];
         };
-        auto fd = [&](int b, int kp) -> double2 { return b < rj ? Xs[h][b][kp] : make_double2(0.0, 0.0); };
-        cgemm_tile(0, 0, rj, fc, fd, cr, ci);
+        auto fd = [&](int b, int kp) -> double2 { return Xs[h][b][kp]; };
+        cgemm_tile(0, 0, de, chi, rj, fc, fd, cr, ci);
         wave_lds_sync();
 #pragma unroll
         for (int r = 0; r < 4; ++r) Xs[h][lk + 4 * r][li] = make_double2(cr[r], ci[r]);
@@ -1852,12 +1868,12 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
       for (int q = 0; q < HW; ++q) {
         const int h = wv + q;
         auto fa = [&](int k, int b) -> double2 {
-          return (k < de && b < rj) ? A1[h * DM * DS + b * DS + k] : make_double2(0.0, 0.0);
+          return A1[h * DM * DS + b * DS + k];
         };
         auto fb = [&](int b, int kp) -> double2 {
-          return (b < rj && kp < chi) ? A0[(h * rj + b) * DS + kp] : make_double2(0.0, 0.0);
+          return A0[(h * rj + b) * DS + kp];
         };
-        if (h < 2) cgemm_tile(0, 0, rj, fa, fb, c1r[q], c1i[q]);
+        if (h < 2) cgemm_tile(0, 0, de, chi, rj, fa, fb, c1r[q], c1i[q]);
       }
       meet();
       for (int idx = tid; idx < 256; idx += NT) {
@@ -1878,12 +1894,12 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
       // U_s[a][k'] = 1/sigma sum_k R_i^(s)[a,k] P_s[k][k'], then Y_s = R_i^(s)T conj(U_s)
       for (int h = wv; h < 2; h += NW) {
         auto fa = [&](int a, int k) -> double2 {
-          return (a < ri && k < de) ? A1[h * DM * DS + a * DS + k] : make_double2(0.0, 0.0);
+          return A1[h * DM * DS + a * DS + k];
         };
         auto fb = [&](int k, int kp) -> double2 {
-          return (k < de && kp < chi) ? A0[h * DM * DS + k * DS + kp] : make_double2(0.0, 0.0);
+          return A0[h * DM * DS + k * DS + kp];
         };
-        cgemm_tile(0, 0, de, fa, fb, cr, ci);
+        cgemm_tile(0, 0, ri, chi, de, fa, fb, cr, ci);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const double is = li < chi ? 1.0 / sig[perm[li]] : 0.0;
@@ -1891,10 +1907,10 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
         }
         wave_lds_sync();
         auto fc = [&](int k, int a) -> double2 {
-          return (k < de && a < ri) ? A1[h * DM * DS + a * DS + k] : make_double2(0.0, 0.0);
+          return A1[h * DM * DS + a * DS + k];
         };
-        auto fd = [&](int a, int kp) -> double2 { return a < ri ? cconj(Xs[h][a][kp]) : make_double2(0.0, 0.0); };
-        cgemm_tile(0, 0, ri, fc, fd, cr, ci);
+        auto fd = [&](int a, int kp) -> double2 { return cconj(Xs[h][a][kp]); };
+        cgemm_tile(0, 0, de, chi, ri, fc, fd, cr, ci);
         wave_lds_sync();
 #pragma unroll
         for (int r = 0; r < 4; ++r) Xs[h][lk + 4 * r][li] = make_double2(cr[r], ci[r]);
