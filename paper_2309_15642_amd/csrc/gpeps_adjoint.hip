@@ -259,7 +259,7 @@ __global__ __launch_bounds__(256) void k_adj_tbar(DevState st, const int32_t* __
   const int M = d1 * d2;
   const CT* gam = reinterpret_cast<const CT*>(st.gamma);
   const int64_t base = S.goff + p * S.pstride;
-  const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6, li = l & 15, lk = l >> 4;
+  const int tid = threadIdx.x, l = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), li = l & 15, lk = l >> 4;
   const int ta_n = (de + 15) >> 4, tb_n = (chi + 15) >> 4;
   d4 cr[NT16][NT16], ci[NT16][NT16];
 #pragma unroll
@@ -270,22 +270,37 @@ __global__ __launch_bounds__(256) void k_adj_tbar(DevState st, const int32_t* __
       ci[ta][tb] = (d4){0.0, 0.0, 0.0, 0.0};
     }
   const int ksteps = (M + 3) >> 2;
+  // (rows and columns past the end are clamped, the loads do not wait for one another, and the
+  // next batch loads during the products; the clamped rows are zeroed in Gamma when they are used,
+  // clamped columns are not stored)
+  CT na[UNR][NT16];
+  double2 nb[UNR][NT16];
+  auto fetch = [&](int ks0) {
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      const int m = min(4 * (ks0 + 4 * u) + lk, M - 1);
+      const int o1 = m / d2, o2 = m - (m / d2) * d2;
+      const int64_t ro = base + (int64_t)o1 * S.so[0] + (int64_t)o2 * S.so[1];
+#pragma unroll
+      for (int t = 0; t < NT16; ++t) {
+        if (t < ta_n) na[u][t] = gam[ro + (int64_t)min(16 * t + li, de - 1) * S.sq];
+        if (t < tb_n) nb[u][t] = st.gbar[ro + (int64_t)min(16 * t + li, chi - 1) * S.sq];
+      }
+    }
+  };
+  fetch(wv);
   for (int ks0 = wv; ks0 < ksteps; ks0 += 4 * UNR) {
     double2 ga[UNR][NT16], gb[UNR][NT16];
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
-      const int m = 4 * (ks0 + 4 * u) + lk;
-      const bool mv = m < M;
-      const int mc = mv ? m : 0;
-      const int o1 = mc / d2, o2 = mc - (mc / d2) * d2;
-      const int64_t ro = base + (int64_t)o1 * S.so[0] + (int64_t)o2 * S.so[1];
+      const bool mv = 4 * (ks0 + 4 * u) + lk < M;
 #pragma unroll
       for (int t = 0; t < NT16; ++t) {
-        const int c = 16 * t + li;
-        ga[u][t] = (mv && c < de) ? to_d2(gam[ro + (int64_t)c * S.sq]) : make_double2(0.0, 0.0);
-        gb[u][t] = (mv && c < chi) ? st.gbar[ro + (int64_t)c * S.sq] : make_double2(0.0, 0.0);
+        ga[u][t] = mv && t < ta_n ? to_d2(na[u][t]) : make_double2(0.0, 0.0);
+        gb[u][t] = mv && t < tb_n ? nb[u][t] : make_double2(0.0, 0.0);
       }
     }
+    if (ks0 + 4 * UNR < ksteps) fetch(ks0 + 4 * UNR);
 #pragma unroll
     for (int u = 0; u < UNR; ++u)
 #pragma unroll

@@ -2089,27 +2089,29 @@ __global__ __launch_bounds__(256) void k_reabsorb_mfma(DevState st, const int32_
   const int nt = (ncol + 15) >> 4;           // column tiles of 16
   float2* gam = reinterpret_cast<float2*>(st.gamma);
   const float2* T = reinterpret_cast<const float2*>(st.tbuf) + rbuf_off(st, slot, side, p);
-  const int64_t base = S.goff + p * S.pstride;
-  const int rstride = d2 > 1 ? S.so[1] : S.so[0];
-  const bool bond_major = S.sq == 1 || rstride != 1;  // C = Gamma T (else C^T = T^T Gamma^T)
-  const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // (strides in registers: read through S they would be loaded again after every store)
+  const int64_t base = S.goff + p * S.pstride, so0 = S.so[0], so1 = S.so[1], sq = S.sq;
+  const int64_t rstride = d2 > 1 ? so1 : so0;
+  const bool bond_major = sq == 1 || rstride != 1;  // C = Gamma T (else C^T = T^T Gamma^T)
+  const int l = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int li = l & 15, lk = l >> 4;
 
   // T[4 kk + lk][16 t + li]: the same registers serve as B (first form) or A (second form)
+  // (indices past the end are clamped and the entries zeroed afterwards: with a test around each
+  // load the loads wait for one another.  Whole steps and tiles past the end load nothing.)
   float tr[KK][NT], ti[KK][NT];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const int k = 4 * kk + lk, c = 16 * t + li;
       float2 v = make_float2(0.f, 0.f);
-      if (k < de && c < ncol) v = T[k * D + c];
+      if (kk < ks && t < nt) v = T[min(4 * kk + lk, de - 1) * D + min(16 * t + li, ncol - 1)];
       tr[kk][t] = v.x;
       ti[kk][t] = v.y;
     }
   auto row_off = [&](int m) -> int64_t {
     const int o1 = m / d2, o2 = m - (m / d2) * d2;
-    return base + (int64_t)o1 * S.so[0] + (int64_t)o2 * S.so[1];
+    return base + o1 * so0 + o2 * so1;
   };
   // every tile's rows are loaded before the first product (memory-level parallelism); a tile
   // past the last row loads nothing and is skipped below
@@ -2117,15 +2119,29 @@ __global__ __launch_bounds__(256) void k_reabsorb_mfma(DevState st, const int32_
 #pragma unroll
   for (int tile = 0; tile < TPW; ++tile) {
     const int row0 = rb * RB + (wave * TPW + tile) * 16;
-    const int m = row0 + li;
-    const int64_t ro = m < M ? row_off(m) : 0;
+    const int64_t ro = row_off(min(row0 + li, M - 1));
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      const int k = 4 * kk + lk;
       float2 v = make_float2(0.f, 0.f);
-      if (m < M && k < de) v = ld_c64(&gam[ro + (int64_t)k * S.sq], STREAM);
+      if (row0 < M && kk < ks) v = ld_c64(&gam[ro + min(4 * kk + lk, de - 1) * sq], STREAM);
       gr[tile][kk] = v.x;
       gi[tile][kk] = v.y;
+    }
+  }
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    const bool kv = 4 * kk + lk < de;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const bool v = kv && 16 * t + li < ncol;
+      tr[kk][t] = v ? tr[kk][t] : 0.f;
+      ti[kk][t] = v ? ti[kk][t] : 0.f;
+    }
+#pragma unroll
+    for (int tile = 0; tile < TPW; ++tile) {
+      const bool v = kv && rb * RB + (wave * TPW + tile) * 16 + li < M;
+      gr[tile][kk] = v ? gr[tile][kk] : 0.f;
+      gi[tile][kk] = v ? gi[tile][kk] : 0.f;
     }
   }
 #pragma unroll
@@ -2169,14 +2185,14 @@ __global__ __launch_bounds__(256) void k_reabsorb_mfma(DevState st, const int32_
       ci[t] = q3[t] - q1[t] - q2[t];
     }
     // the rows of this tile were read into registers above; write the new rows.  A lane's rows
-    // are m0, m0 + 1, ... (first form) or the single row m0 (second form): one division, then
+    // are m0, m0 + 1, ... (first form) or m0 four times (second form): one division, then
     // the other-leg indices (o1, o2) step forward.
     const int m0 = bond_major ? row0 + 4 * lk : row0 + li;
     int o1 = m0 / d2, o2 = m0 - (m0 / d2) * d2;
     int64_t roff[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      roff[r] = base + (int64_t)o1 * S.so[0] + (int64_t)o2 * S.so[1];
+      roff[r] = base + o1 * so0 + o2 * so1;
       if (bond_major && ++o2 == d2) {
         o2 = 0;
         ++o1;
@@ -2190,7 +2206,7 @@ __global__ __launch_bounds__(256) void k_reabsorb_mfma(DevState st, const int32_
           const int m = bond_major ? m0 + r : m0;
           const int kp = bond_major ? 16 * t + li : 16 * t + 4 * lk + r;
           if (m < M && kp < ncol)
-            st_c64(&gam[roff[bond_major ? r : 0] + (int64_t)kp * S.sq], make_float2(cr[t][r], ci[t][r]), STREAM);
+            st_c64(&gam[roff[r] + kp * sq], make_float2(cr[t][r], ci[t][r]), STREAM);
         }
       }
     }
