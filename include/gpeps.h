@@ -255,8 +255,9 @@ gpeps_status gpeps_time_backward(gpeps_ctx* ctx, const double* dl_dz, double* dt
  *   tiles[2]  threads per workgroup of the Theta' + SVD kernel when d_max <= 16: 64 (one wave
  *             per SVD, no workgroup barriers) or 256 (ignored for d_max > 16, which uses 256)
  * They change the blocking only; the complex64 re-absorb gives the same bits for every choice,
- * the Householder reduction and the SVD differ by float64 rounding.  Defaults 16, 2 and 256 (64
- * where a complex64 context with 8 < d_max <= 16 has at least 1536 edges in a colour class). */
+ * the Householder reduction and the SVD differ by float64 rounding.  Defaults 16, 1 (2 where a
+ * colour class has at least 128 edges and d_max^2 rows fill blocks of 128) and 256 (64 where a
+ * complex64 context with 8 < d_max <= 16 has at least 1536 edges in a colour class). */
 
 /* Autotuner: run `steps` Trotter steps (1 <= steps <= cfg.max_steps) of the configured
  * workload once per candidate tile triple, timing every launch with hipEvents, keep for each

@@ -536,6 +536,17 @@ int default_svd_threads(const gpeps_ctx* c) {
   return !c->c128 && c->D > 8 && c->D <= 16 && c->L.max_items >= 6 * kCus ? 64 : 256;
 }
 
+// 16-row tiles a wave of the complex64 re-absorb takes before any tuning (the bits are the same).  Two
+// read T half as often, but a workgroup then covers 128 rows instead of 64: with fewer than 128 edges in
+// the largest class the launch leaves CUs idle, and where the d_max^2 rows of an end need fewer
+// blocks of 64 than twice those of 128 the second half block is padding.  127 qubits, one class,
+// 1 / 2 tiles: 1 instance (48 edges) at D = 16 8.0 / 9.1 us, 2 9.7 / 10.9, 3 13.0 / 12.6, 8 17.8 / 16.6; D = 32 2 instances
+// 22.3 / 23.3, 8 67.6 / 64.5; padded: D = 12 x 24 30.5 / 35.0, D = 20 x 8 28.9 / 33.5.
+int default_rb_tiles(const gpeps_ctx* c) {
+  const int rows = c->D * c->D;
+  return c->L.max_items >= 128 && (rows + 63) / 64 == 2 * ((rows + 127) / 128) ? 2 : 1;
+}
+
 struct Timer {
   bool on = false;
   std::vector<hipEvent_t> ev;
@@ -896,7 +907,7 @@ gpeps_status gpeps_init(gpeps_ctx** out, const gpeps_graph* graphs, int32_t n_gr
   st.max_sweeps = cfg->max_jacobi_sweeps > 0 ? cfg->max_jacobi_sweeps : 40;
   st.max_steps = cfg->max_steps;
   st.trunc_rel = cfg->trunc_rel;
-  st.tune_rb = 2;
+  st.tune_rb = default_rb_tiles(c);
   st.tune_qr = 16;
   st.tune_svd = default_svd_threads(c);
   // site tensors larger than the 256 MB last-level cache are streamed past the caches by the
@@ -1362,7 +1373,7 @@ gpeps_status gpeps_autotune(gpeps_ctx* c, int32_t steps, int32_t* tiles_out) {
   const int trials = 4;
   double tot[kKinds];
   c->st.tune_qr = 16;
-  c->st.tune_rb = 2;
+  c->st.tune_rb = default_rb_tiles(c);
   c->st.tune_svd = default_svd_threads(c);
   drop_step_graph(c);
   gpeps_status s = timed_trial(c, steps, tot);  // warm-up (code objects, caches)
@@ -1393,7 +1404,7 @@ gpeps_status gpeps_autotune(gpeps_ctx* c, int32_t steps, int32_t* tiles_out) {
   c->st.tune_svd = (c->D <= 16 && avg(t_sv[1], n_sv[1]) < avg(t_sv[0], n_sv[0])) ? 64 : 256;
   if (s != GPEPS_OK) {
     c->st.tune_qr = 16;
-    c->st.tune_rb = 2;
+    c->st.tune_rb = default_rb_tiles(c);
     c->st.tune_svd = default_svd_threads(c);
   }
   drop_step_graph(c);
