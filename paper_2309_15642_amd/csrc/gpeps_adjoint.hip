@@ -524,7 +524,8 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
 // N bounds D (16 or 32).  One workgroup per edge and few edges a launch: bound by the latency of its
 // chain of small products, so the operands of the next k steps are in flight during the current ones,
 // eight waves share the tiles of a batch, and the eliminations run in registers.
-// Measured on the 48 edges of a class of the 127-qubit graph: MEASURED16 at D = 16, MEASURED32 at D = 32.
+// Mean over the classes of the 127-qubit graph (one instance): 86 -> 47 us at D = 16, 163 -> 85 us at
+// D = 32; a four-wave form that waited for every pair of loads and eliminated in LDS is the first figure.
 constexpr int kSmallThreads = 512;
 
 template <bool REC, int N>
@@ -865,9 +866,18 @@ __global__ __launch_bounds__(kSmallThreads) void k_adj_small(DevState st, const 
 
 // ------------------------------------------------------------------ Gamma-bar rows
 
-template <typename CT>
-__global__ __launch_bounds__(256) void k_adj_rows(DevState st, const int32_t* __restrict__ items, int first,
+// Gamma-bar = Gamma'-bar T^H + w A-bar and w-bar = sum_k Re conj(A-bar) Gamma per row, with
+// A-bar = w (Gamma Y) or, where the slice was not reduced, the stored R-bar.  Each wave takes 16 rows and
+// every column: both products on v_mfma_f64_16x16x4f64 (lane l holds A[l % 16][l / 16] and
+// B[l / 16][l % 16] and receives D[l / 16 + 4 r][l % 16]), operands from memory to registers (T and Y
+// from the caches), no LDS and no barrier.  Clamped indices as in gemm_acc.  Bound by latency at
+// D = 16 and by the FP64 matrix cores above.  N bounds D.  One class
+// of the 127-qubit graph (mean): 13.9 -> 9.4 us at D = 16, 59.8 -> 28.2 us at D = 32 against vector dot
+// products on rows staged in LDS.
+template <typename CT, int N>
+__global__ __launch_bounds__(256, N == 32 ? 2 : 4) void k_adj_rows(DevState st, const int32_t* __restrict__ items, int first,
                                                   int blocks_per_slice, const double2* __restrict__ ybuf) {
+  constexpr int NT = N / 16;
   int slot, sp, rb;
   row_task(st, blockIdx.x, blocks_per_slice, slot, sp, rb);
   const int side = sp >> 1, p = sp & 1;
@@ -877,91 +887,127 @@ __global__ __launch_bounds__(256) void k_adj_rows(DevState st, const int32_t* __
   const int d1 = S.oth[0] >= 0 ? st.chi[S.oth[0]] : 1;
   const int d2 = S.oth[1] >= 0 ? st.chi[S.oth[1]] : 1;
   const int M = d1 * d2;
-  const int row0 = rb * kRowBlock;
+  static_assert(kRowBlock == 4 * 16, "16 rows a wave");
+  const int row0 = rb * kRowBlock + 16 * __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (row0 >= M) return;
-  const int rows = min(kRowBlock, M - row0);
   const SlotMeta meta = st.meta[slot];
   const int de = meta.de_old, chi = meta.chi_new;
   const int ncol = max(de, chi);
-  const int mode = st.ymode[slot * 4 + sp];
-  // LDS sized by D (dynamic): T [de x chi], Y [de x de] (mode 0), Gamma and Gamma'-bar rows
-  extern __shared__ double2 rows_lds[];
-  const int DS = D + 1;
-  double2* const Ts = rows_lds;
-  double2* const Ys = Ts + D * DS;
-  double2* const Gs = Ys + D * DS;
-  double2* const Bs = Gs + kRowBlock * DS;
-  __shared__ double wl[kRowBlock];
+  const bool reduced = st.ymode[slot * 4 + sp] == 0;
   const double* l1 = S.oth[0] >= 0 ? st.lam + (int64_t)S.oth[0] * D : nullptr;
   const double* l2 = S.oth[1] >= 0 ? st.lam + (int64_t)S.oth[1] * D : nullptr;
   const double2* T = st.t64 + rbuf_off(st, slot, side, p);
   const double2* Y = ybuf + rbuf_off(st, slot, side, p);
+  const int64_t base = S.goff + p * S.pstride, so0 = S.so[0], so1 = S.so[1], sq = S.sq;
   const CT* gam = reinterpret_cast<const CT*>(st.gamma);
-  const int64_t base = S.goff + p * S.pstride;
-  const int tid = threadIdx.x;
-  for (int idx = tid; idx < de * chi; idx += blockDim.x) {
-    const int k = idx / chi, kp = idx - (idx / chi) * chi;
-    Ts[(k) * DS + kp] = T[k * D + kp];
+  double2* const gbar = st.gbar;
+  const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
+  auto row_off = [&](int m) -> int64_t {
+    const int o1 = m / d2, o2 = m - (m / d2) * d2;
+    return base + o1 * so0 + o2 * so1;
+  };
+  const int64_t ra = row_off(min(row0 + li, M - 1));
+  // Gamma at the output positions and the rows' weights, in flight during the products
+  CT gout[4][NT];
+  double w[4];
+  int64_t ro[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int m = min(row0 + lk + 4 * r, M - 1);
+    const int o1 = m / d2, o2 = m - (m / d2) * d2;
+    ro[r] = base + o1 * so0 + o2 * so1;
+    w[r] = (l1 ? l1[o1] : 1.0) * (l2 ? l2[o2] : 1.0);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (16 * t < de) gout[r][t] = gam[ro[r] + min(16 * t + li, de - 1) * sq];
   }
-  if (mode == 0) {
-    for (int idx = tid; idx < de * de; idx += blockDim.x) {
-      const int k = idx / de, l = idx - (idx / de) * de;
-      Ys[(k) * DS + l] = Y[k * D + l];
-    }
+  adj_d4 br[NT], bi[NT], yr[NT], yi[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    br[t] = (adj_d4){0.0, 0.0, 0.0, 0.0};
+    bi[t] = br[t];
+    yr[t] = br[t];
+    yi[t] = br[t];
   }
-  for (int idx = tid; idx < rows; idx += blockDim.x) {
-    const int m = row0 + idx, o1 = m / d2, o2 = m - (m / d2) * d2;
-    double w = 1.0;
-    if (l1) w *= l1[o1];
-    if (l2) w *= l2[o2];
-    wl[idx] = w;
-  }
-  for (int idx = tid; idx < rows * de; idx += blockDim.x) {
-    const int rr = idx / de, k = idx - (idx / de) * de;
-    const int m = row0 + rr, o1 = m / d2, o2 = m - (m / d2) * d2;
-    Gs[(rr) * DS + k] = to_d2(gam[base + (int64_t)o1 * S.so[0] + (int64_t)o2 * S.so[1] + (int64_t)k * S.sq]);
-  }
-  for (int idx = tid; idx < rows * chi; idx += blockDim.x) {
-    const int rr = idx / chi, k = idx - (idx / chi) * chi;
-    const int m = row0 + rr, o1 = m / d2, o2 = m - (m / d2) * d2;
-    Bs[(rr) * DS + k] = st.gbar[base + (int64_t)o1 * S.so[0] + (int64_t)o2 * S.so[1] + (int64_t)k * S.sq];
-  }
-  __syncthreads();
-  // new Gamma-bar and A-bar per (row, column), w-bar per row: thread t takes row t / 4 of the
-  // block and columns t % 4 + 4 j, so its four threads sum a row's w-bar with two DPP steps
-  static_assert(kRowBlock * 4 == 256, "one row per four threads");
-  __shared__ double wb[kRowBlock];
-  {
-    const int rr = tid >> 2, kq = tid & 3;
-    double wsum = 0.0;
-    if (rr < rows) {
-      const int m = row0 + rr, o1 = m / d2, o2 = m - (m / d2) * d2;
-      const int64_t ro = base + (int64_t)o1 * S.so[0] + (int64_t)o2 * S.so[1];
-      for (int k = kq; k < ncol; k += 4) {
-        double2 out = make_double2(0.0, 0.0);
-        if (k < de) {
-          for (int kp = 0; kp < chi; ++kp) out = cadd(out, cmul(Bs[(rr) * DS + kp], cconj(Ts[(k) * DS + kp])));
-          double2 abar;
-          if (mode == 0) {
-            double2 gy = make_double2(0.0, 0.0);
-            for (int l = 0; l < de; ++l) gy = cadd(gy, cmul(Gs[(rr) * DS + l], Ys[(l) * DS + k]));
-            abar = cscale(gy, wl[rr]);
-          } else {
-            abar = Y[m * D + k];
+#pragma unroll
+  for (int k0 = 0; k0 < N; k0 += 16) {
+    if (k0 < chi) {  // Gamma'-bar T^H over k' = k0 .. k0 + 15
+      double2 x[4], y[4][NT];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int kp = min(k0 + 4 * u + lk, chi - 1);
+        x[u] = gbar[ra + kp * sq];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          if (16 * t < de) y[u][t] = T[min(16 * t + li, de - 1) * D + kp];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double2 a = k0 + 4 * u + lk < chi ? x[u] : make_double2(0.0, 0.0);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          if (16 * t < de && k0 + 4 * u < chi) {
+            const double2 b = y[u][t];  // conjugated
+            br[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, br[t], 0, 0, 0);
+            bi[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, bi[t], 0, 0, 0);
+            br[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, br[t], 0, 0, 0);
+            bi[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.x, b.y, bi[t], 0, 0, 0);
           }
-          out = cadd(out, cscale(abar, wl[rr]));
-          wsum += cmulc(abar, Gs[(rr) * DS + k]).x;
-        }
-        st.gbar[ro + (int64_t)k * S.sq] = out;
       }
     }
-    wsum = group_sum_dpp(wsum, 4);
-    if (kq == 0 && rr < rows) wb[rr] = wsum;
+    if (reduced && k0 < de) {  // Gamma Y
+      CT x[4];
+      double2 y[4][NT];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = min(k0 + 4 * u + lk, de - 1);
+        x[u] = gam[ra + k * sq];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          if (16 * t < de) y[u][t] = Y[k * D + min(16 * t + li, de - 1)];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double2 a = k0 + 4 * u + lk < de ? to_d2(x[u]) : make_double2(0.0, 0.0);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          if (16 * t < de && k0 + 4 * u < de) {
+            const double2 b = y[u][t];
+            yr[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, yr[t], 0, 0, 0);
+            yi[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, yi[t], 0, 0, 0);
+            yr[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, yr[t], 0, 0, 0);
+            yi[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, yi[t], 0, 0, 0);
+          }
+      }
+    }
   }
-  __syncthreads();
-  // w-bar per row (w = l1[o1] l2[o2]) for k_adj_lbar, which folds it into the other legs' lambda-bar
+  // the wave's rows have been read: Gamma-bar goes out in place, w-bar per row (w = l1[o1] l2[o2]) to
+  // k_adj_lbar, which folds it into the other legs' lambda-bar
+  double ws[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int m = row0 + lk + 4 * r;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int k = 16 * t + li;
+      if (m < M && k < ncol) {
+        double2 out = make_double2(0.0, 0.0);
+        if (k < de) {
+          const double2 abar = reduced ? make_double2(w[r] * yr[t][r], w[r] * yi[t][r]) : Y[m * D + k];
+          out = make_double2(fma(w[r], abar.x, br[t][r]), fma(w[r], abar.y, bi[t][r]));
+          ws[r] += cmulc(abar, to_d2(gout[r][t])).x;
+        }
+        gbar[ro[r] + k * sq] = out;
+      }
+    }
+  }
   double* wrow = st.wbar + ((int64_t)slot * 4 + sp) * D * D;
-  for (int idx = tid; idx < rows; idx += blockDim.x) wrow[row0 + idx] = wb[idx];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const double v = group_sum_dpp(ws[r], 16);
+    const int m = row0 + lk + 4 * r;
+    if (li == 0 && m < M) wrow[m] = v;
+  }
 }
 
 // lambda-bar of the other legs of one end (slot, side) from the per-row w-bar of both slices:
@@ -1046,13 +1092,8 @@ static hipError_t adj_launch(int which, const DevState& st, const int32_t* items
     case 3:
       if (count <= 0) return hipSuccess;
       {
-        const size_t lds = (size_t)(2 * st.D + 2 * kRowBlock) * (st.D + 1) * sizeof(double2);
-        if (lds > 65536) {  // above 64 KB of dynamic LDS the kernel's limit has to be raised
-          const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_adj_rows<CT>),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-          if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL(k_adj_rows<CT>, dim3(row_grid(st, count, blocks_per_slice)), dim3(256), lds, stream, st, items, first,
+        const auto kern = st.D <= 16 ? k_adj_rows<CT, 16> : k_adj_rows<CT, 32>;
+        hipLaunchKernelGGL(kern, dim3(row_grid(st, count, blocks_per_slice)), dim3(256), 0, stream, st, items, first,
                            blocks_per_slice, (const double2*)aux);
       }
       break;
