@@ -907,6 +907,12 @@ gpeps_status gpeps_init(gpeps_ctx** out, const gpeps_graph* graphs, int32_t n_gr
   st.max_sweeps = cfg->max_jacobi_sweeps > 0 ? cfg->max_jacobi_sweeps : 40;
   st.max_steps = cfg->max_steps;
   st.trunc_rel = cfg->trunc_rel;
+  // rows of an end over four workgroups (complex64, d_max > 32): pays while the ends of a class leave
+  // CUs idle and some end has rows to share (absorb of one class of 127 qubits, whole / split: one
+  // instance at D = 64 147 / 104 us, D = 33 58 / 53; four at D = 33 94 / 150; ring, two legs a
+  // vertex, 11.8 / 14.4)
+  st.gram_split = c->D > kMaxD && L.max_items <= 64 &&
+                  std::any_of(L.verts.begin(), L.verts.end(), [](const VertexInfo& v) { return v.deg == kMaxDeg; });
   st.tune_rb = default_rb_tiles(c);
   st.tune_qr = 16;
   st.tune_svd = default_svd_threads(c);

@@ -68,8 +68,9 @@ __host__ __device__ inline int64_t adj_scratch(int D) { return (int64_t)48 * D *
 
 // Per-item HBM scratch of k_svd_big (d_max > 32), in double2 entries: Theta' [128][128], the
 // pivoted R factor [128][128], and [128][64] for the column exchange and then the recovered
-// singular-vector set.
-__host__ __device__ inline int64_t big_scratch(int /*D*/) {
+// singular-vector set.  Before it runs, the partial Gram matrices of the item's four (end, slice)
+// blocks (complex64) take the same memory.
+__host__ __device__ constexpr int64_t big_scratch(int /*D*/) {
   return (int64_t)2 * (2 * kMaxDBig) * (2 * kMaxDBig) + (int64_t)2 * kMaxDBig * kMaxDBig;
 }
 
@@ -128,6 +129,7 @@ struct DevState {
   int32_t NE;
   int32_t max_sweeps;
   int32_t max_steps;
+  int32_t gram_split;     // complex64 absorb above D = 32: rows of an end over several workgroups
   int32_t tune_rb;        // complex64 re-absorb: 16-row tiles per wave (1, 2 or 4); autotuned
   int32_t tune_qr;        // QR reduction: rows per lane per chunk (8 or 16); autotuned
   int32_t tune_svd;       // SVD workgroup size for bonds up to 16 (64 or 256); autotuned

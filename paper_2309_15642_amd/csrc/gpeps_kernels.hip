@@ -187,14 +187,26 @@ __global__ __launch_bounds__(256) void k_absorb_qr(DevState st, const int32_t* _
 // directions of A below ~1e-7 of its norm are not resolved, about the complex64 rounding of the
 // stored tensors, and a Cholesky pivot below 1e-13 of its column's squared norm is taken as
 // zero (that row of R is zero), which keeps exact zeros exact.
-template <int NC>
+//
+// Above D = 32 the rows of an end go to kGramSplit workgroups where the whole context has few edges
+// (st.gram_split): an end with three legs has up to 4096 rows, the few such ends of a class leave most
+// CUs idle, and one CU's FP64 matrix cores need 250 us for one.  The first launch (kGramPart) leaves
+// the partial Gram matrices in the scratch of the SVD that follows, the second (kGramEnd) adds them in a
+// fixed order and factorises.  One 127-qubit instance at D = 64: 479 -> 217 + 85 us in the largest
+// class, 147 -> 104 us in the mean.
+constexpr int kGramWhole = 0, kGramPart = 1, kGramEnd = 2;
+constexpr int kGramSplit = 4;
+
+template <int NC, int MODE = kGramWhole>
 __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState st, const int32_t* __restrict__ items, int first) {
   typedef double d4 __attribute__((ext_vector_type(4)));
   constexpr int NT16 = NC / 16;                 // column tiles of 16
   constexpr int NTILE = NT16 * (NT16 + 1) / 2;  // tiles on and above the diagonal
   constexpr int UNR = NT16 >= 4 ? 2 : 4 / NT16;  // row steps (of 4 rows) per load batch in flight
   int slot, side, p;
-  end_task(st, blockIdx.x, slot, side, p);
+  constexpr int SP = MODE == kGramPart ? kGramSplit : 1;
+  const int split = MODE == kGramPart ? (int)blockIdx.x % kGramSplit : 0;
+  end_task(st, blockIdx.x / SP, slot, side, p);
   const int e = items[first + slot];
   const EdgeInfo& E = st.edges[e];
   const SideGeom G = side_geom(st, E.side[side]);
@@ -206,7 +218,8 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
   const int tid = threadIdx.x;
 
   if (M <= n) {  // no reduction: R = A (M x n)
-    for (int idx = tid; idx < M * n; idx += blockDim.x) {
+    if (MODE == kGramEnd) return;
+    for (int idx = tid + split * 256; idx < M * n; idx += 256 * SP) {
       const int m = idx / n, k = idx - (idx / n) * n;
       R[m * D + k] = cscale(to_d2(gam[G.addr(p, m, k)]), G.env(m));
     }
@@ -218,13 +231,16 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
   // while it writes G.
   constexpr int PART = NTILE * 4 * 64;
   constexpr int GSZ = NC * (NC + 1);
-  __shared__ double2 lds[PART + (GSZ > PART ? GSZ : PART)];
+  static_assert(MODE == kGramWhole || 4 * kGramSplit * PART <= big_scratch(NC), "partial sums in st.big");
+  __shared__ double2 lds[PART + (GSZ > PART && MODE != kGramPart ? GSZ : PART)];
   __shared__ double dg[NC];           // squared column norms (diagonal of G)
   __shared__ double envs[2][NC];      // lambda weights of the other two legs (1 for a missing leg)
   double2* part0 = lds;
   double2* part1 = lds + PART;
   auto Gs = [&](int i, int j) -> double2& { return lds[PART + i * (NC + 1) + j]; };
 
+  double2* const gpar = MODE == kGramWhole ? nullptr
+                                           : st.big + (int64_t)slot * big_scratch(D) + (side * 2 + p) * kGramSplit * PART;
   if (tid < NC) {
     envs[0][tid] = (G.l1 && tid < G.d1) ? G.l1[tid] : 1.0;
     envs[1][tid] = (G.l2 && tid < G.d2) ? G.l2[tid] : 1.0;
@@ -232,12 +248,14 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
   __syncthreads();
 
   const int l = tid & 63, wv = tid >> 6, li = l & 15, lk = l >> 4;
+  if constexpr (MODE != kGramEnd) {
   d4 gr[NTILE], gi[NTILE];
 #pragma unroll
   for (int t = 0; t < NTILE; ++t) {
     gr[t] = (d4){0.0, 0.0, 0.0, 0.0};
     gi[t] = (d4){0.0, 0.0, 0.0, 0.0};
   }
+  constexpr int WS = 4 * SP;  // waves that share the rows
   // Software pipelined: the complex64 elements of the next batch of rows (4 ks + l / 16, columns
   // 16 t + l % 16) are in flight while the products of the current batch run.  A row past the
   // end gets weight 0 (its load is clamped to the last row).
@@ -248,7 +266,7 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
   auto fetch = [&](int ks0) {
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
-      const int m = 4 * (ks0 + 4 * u) + lk;
+      const int m = 4 * (ks0 + WS * u) + lk;
       const bool mv = m < M;
       const int mc = mv ? m : M - 1;
       const int o1 = mc / G.d2, o2 = mc - (mc / G.d2) * G.d2;
@@ -262,8 +280,9 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
       }
     }
   };
-  fetch(wv);
-  for (int ks0 = wv; ks0 < ksteps; ks0 += 4 * UNR) {
+  const int w0 = split * 4 + wv;
+  fetch(w0);
+  for (int ks0 = w0; ks0 < ksteps; ks0 += WS * UNR) {
     float2 x[UNR][NT16];
     double w[UNR];
 #pragma unroll
@@ -272,7 +291,7 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
 #pragma unroll
       for (int t = 0; t < NT16; ++t) x[u][t] = nx[u][t];
     }
-    if (ks0 + 4 * UNR < ksteps) fetch(ks0 + 4 * UNR);
+    if (ks0 + WS * UNR < ksteps) fetch(ks0 + WS * UNR);
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
       double2 a[NT16];
@@ -337,11 +356,31 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
           const double2 v = make_double2(gr[tile][r] + q.x, gi[tile][r] + q.y);
           // off the diagonal tiles k < k' always; a diagonal tile is stored whole (its lower
           // half holds X[k'][k] for the antisymmetrisation below)
-          Gs(16 * ta + lk + 4 * r, 16 * tb + li) = v;
+          if constexpr (MODE == kGramPart) gpar[split * PART + (tile * 4 + r) * 64 + l] = v;
+          else Gs(16 * ta + lk + 4 * r, 16 * tb + li) = v;
         }
         ++tile;
       }
   }
+  } else {
+    int tile = 0;
+#pragma unroll
+    for (int ta = 0; ta < NT16; ++ta)
+#pragma unroll
+      for (int tb = ta; tb < NT16; ++tb) {
+        if ((tile & 3) == wv) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            double2 v = gpar[(tile * 4 + r) * 64 + l];
+#pragma unroll
+            for (int q = 1; q < kGramSplit; ++q) v = cadd(v, gpar[q * PART + (tile * 4 + r) * 64 + l]);
+            Gs(16 * ta + lk + 4 * r, 16 * tb + li) = v;
+          }
+        }
+        ++tile;
+      }
+  }
+  if constexpr (MODE == kGramPart) return;
   __syncthreads();
   // Im G on the diagonal tiles: X[k][k'] - X[k'][k] on the upper triangle (which is all the
   // factorisation reads), exactly 0 on the diagonal; only the upper entries are written
@@ -2392,9 +2431,16 @@ static hipError_t launch_set(int which, const DevState& st, const int32_t* items
     // bond dimensions 33..64: R factors as below at 64 columns, the two-site SVD in k_svd_big
     switch (which) {
       case 1:
-        if constexpr (sizeof(CT) == sizeof(float2))
-          hipLaunchKernelGGL(k_absorb_gram<kMaxDBig>, dim3(count * 4), dim3(256), 0, stream, st, items, first);
-        else
+        if constexpr (sizeof(CT) == sizeof(float2)) {
+          if (st.gram_split) {
+            hipLaunchKernelGGL((k_absorb_gram<kMaxDBig, kGramPart>), dim3(count * 4 * kGramSplit), dim3(256), 0, stream, st,
+                               items, first);
+            hipLaunchKernelGGL((k_absorb_gram<kMaxDBig, kGramEnd>), dim3(count * 4), dim3(256), 0, stream, st, items,
+                               first);
+          } else {
+            hipLaunchKernelGGL(k_absorb_gram<kMaxDBig>, dim3(count * 4), dim3(256), 0, stream, st, items, first);
+          }
+        } else
           hipLaunchKernelGGL((k_absorb_qr<CT, kMaxDBig, 32>), dim3(count * 4), dim3(256), 0, stream, st, items, first);
         break;
       case 2:
