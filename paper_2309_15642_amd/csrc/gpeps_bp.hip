@@ -264,7 +264,7 @@ __global__ void k_bp_init(DevState st) {
 // Small bonds are bound by the launch: ten iterations and the readout of the 127-qubit graph take
 // 172 us at D = 2 in complex128 (226 with k_bp_norm at every D, 181 before the matrix cores), and
 // sixteen such instances at D = 3 470 us with kernels sized for D <= 8 (1129 with those for 16, 580).
-// Measured at D = 32 on the 288 directed edges of the 127-qubit graph: 185 us (5.4 GFLOP, 29 TFLOP/s)
+// Measured at D = 32 on the 288 directed edges of the 127-qubit graph: 180 us (5.4 GFLOP, 30 TFLOP/s)
 // with the senders of three legs first (bp_order), 307 us in edge order (some CUs got two of their
 // 150 us workgroups), 3860 us as vector dot products with one workgroup per directed edge.
 template <typename CT, int N>

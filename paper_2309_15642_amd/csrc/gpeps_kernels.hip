@@ -477,7 +477,7 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
 // below the complex64 storage rounding for every kept value (cutoff ~1e-6).
 //   complex128 (ACC = true, cutoffs down to 1e-12): quiet at |g|^2 <= 1e-16 al be, R from a
 // Householder QR of B with its columns sorted by norm, and the rotations accumulated in W, so that
-// the other set is Q W, accurate for every sigma.  D = 16, ten steps of the 127-qubit graph: 110 us
+// the other set is Q W, accurate for every sigma.  D = 16, ten steps of the 127-qubit graph: 104 us
 // per launch and 5.3 sweeps (9.3 at most 17 without the QR, through LDS: 192 us).  A square B of at
 // most kSmallB columns takes Q = I, R = B: the QR and the reflectors (3.5 us at two columns) cost
 // more than the sweep they save.
