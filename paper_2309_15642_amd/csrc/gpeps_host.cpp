@@ -527,9 +527,9 @@ gpeps_status enqueue_edge_kernel(gpeps_ctx* c, int which, int first, int count, 
 // chain (85 us for one instance at D = 16, one wave 150 us); one wave does the same with half the
 // float64 instructions and no barriers, and eight such workgroups fit a CU against five, so it wins
 // once the launches fill the chip: 127 qubits at D = 16, 20 steps, 256 / 64 threads: 16 instances
-// 12.9 / 15.7 ms, 32 (1728 items in the largest class) 21.7 / 20.6 ms, 128 72.7 / 61.9 ms; D = 12
-// x 32 19.6 / 17.8 ms.  At D <= 8 half of the four waves' work is gone already (64 instances at
-// D = 8 16.3 / 18.8 ms), and complex128 holds two matrices more (one wave a SIMD).  The choice
+// 12.7 / 15.0 ms, 32 (1728 items in the largest class) 21.2 / 19.7 ms, 128 72.3 / 62.0 ms; D = 12
+// x 32 19.3 / 17.1 ms.  At D <= 8 half of the four waves' work is gone already (64 instances at
+// D = 8 16.0 / 18.3 ms), and complex128 holds two matrices more (one wave a SIMD).  The choice
 // depends on the whole context, not on one launch: batched and plain mode give the same bits.
 int default_svd_threads(const gpeps_ctx* c) {
   constexpr int kCus = 256;
