@@ -467,15 +467,20 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
 // 2^-52 * eps^2 * ||B||_F^2 (eps = truncation cutoff): pairs below that are
 // made of columns far under the cutoff (rounding noise), whose rotation
 // cannot move a kept singular vector.  The sweep loop ends when a sweep
-// applies no rotation, or when every rotation of the sweep was quiet: by the quadratic convergence
-// of the sweeps the off-diagonal left is then about the square of the quiet level, relative.
-//   complex64 (ACC = false): quiet at |g|^2 <= 1e-8 al be (angles below 1e-4; what is left, 1e-8,
-// is under the 2^-24 rounding of the complex64 tensors the update writes), one Newton step, not
+// applies no rotation, or when every rotation of the sweep was quiet.
+//   complex64 (ACC = false): quiet at |g|^2 <= 1e-8 al be (what is left, 1e-8 between separated
+// values, is under the 2^-24 rounding of the complex64 tensors the update writes), one Newton step, not
 // two, for the reciprocal square roots (unitarity to ~1e-13 per rotation), R from a column-pivoted
 // Cholesky factorisation of B^H B, and the other set of singular vectors from the original Theta'
 // as U = Theta' V / sigma or V = Theta'^H U / sigma, accurate to ~2^-52 sigma_0 / sigma_k, well
 // below the complex64 storage rounding for every kept value (cutoff ~1e-6).
-//   complex128 (ACC = true, cutoffs down to 1e-12): quiet at |g|^2 <= 1e-16 al be, R from a
+//   complex128 (ACC = true, cutoffs down to 1e-12): quiet at |g|^2 <= 1e-16 al be and
+// tan^2 theta <= 1e-16: a later rotation of the sweep then puts at most the product of two such values
+// back into a pair already done, so what is left is under the rotation threshold.  The angle has to be
+// tested too: values closer to one another than |g| turn by large angles however small g is, and three
+// or more of them hand the couplings on undiminished (eight values 1e-9 apart: vectors orthogonal to
+// 1.4e-10 without the test of the angle, to 3.5e-15 with it, as after a sweep without rotations; the sweeps of
+// separated values are the same).  R from a
 // Householder QR of B with its columns sorted by norm, and the rotations accumulated in W, so that
 // the other set is Q W, accurate for every sigma.  D = 16, ten steps of the 127-qubit graph: 104 us
 // per launch and 5.3 sweeps (9.3 at most 17 without the QR, through LDS: 192 us).  A square B of at
@@ -486,7 +491,7 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
 // reverse sweep needs: every singular triplet (bU, bV, bS) and float64 T matrices (t64).
 constexpr double kJacobiQuietC64 = 1e-8;    // (1e-4)^2: relative size of a quiet rotation, complex64
 constexpr int kSmallB = 8;                  // largest square B that skips the QR, complex128
-constexpr double kJacobiQuietC128 = 1e-16;  // (1e-8)^2: the same for the complex128 path
+constexpr double kJacobiQuietC128 = 1e-16;  // (1e-8)^2: the same for the complex128 path, and of its tan^2 theta
 
 template <typename CT, int NT, int NMAX, bool ACC_, bool BWD = false>
 __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : ACC_ ? 1 : 2) void k_theta_svd(DevState st, const int32_t* __restrict__ items, int first) {
@@ -1241,12 +1246,13 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
             const double h2 = fmax(d * d + 4.0 * g2, 1e-300);
             const double rh = ACC ? rsq_nr(h2) : rsq_nr1(h2);  // 1 / h
             const double x = 0.5 + 0.5 * fabs(d) * rh;
-            double tg;  // tan theta |g|
+            double tg, t2 = 0.0;  // tan theta |g|, tan^2 theta
             if constexpr (kSpread) {
               const double rx = ACC ? rcp_nr(x) : rcp_nr1(x);  // 1 / x
               const double F = ok ? copysign(rh, d) * rx : 0.0;
               const double xx = ok ? x : 1.0;
               tg = g2 * F;
+              if constexpr (ACC) t2 = tg * F;
               const double fm = F * pm, fs = F * ps;
               const double2 tm = make_double2(gr * fm, gi * fm), ts = make_double2(gr * fs, gi * fs);
               auto turn = [&](double2& a, double2& b) {
@@ -1269,6 +1275,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
               const double cs = ok ? x * rc : 1.0;
               const double2 sph = make_double2(gr * f, gi * f);  // s e^{i phi}
               tg = g2 * f * rc;
+              if constexpr (ACC) t2 = tg * f * rc;
               auto turn = [&](double2& a, double2& b) {
                 const double2 a0 = a, b0 = b;
                 a = csub(cscale(a0, cs), cmulc(sph, b0));
@@ -1283,7 +1290,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
             ns = al - tg;
             nm = be + tg;
             rot |= ok;
-            big |= ok & (g2 > (ACC ? kJacobiQuietC128 : kJacobiQuietC64) * ab);
+            big |= ok & ((g2 > (ACC ? kJacobiQuietC128 : kJacobiQuietC64) * ab) | (ACC && t2 > kJacobiQuietC128));
           };
           // the moving column of this group in round t of the block
           auto mid = [&](int t) {
