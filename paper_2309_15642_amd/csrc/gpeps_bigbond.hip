@@ -505,15 +505,7 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
     if (cm_id < nB) sig[cm_id] = s_m;
   }
   __syncthreads();
-  for (int c = tid; c < nB; c += kBT) {
-    const double sv = sig[c];
-    int rank = 0;
-    for (int d2 = 0; d2 < nB; ++d2) {
-      const double sd = sig[d2];
-      rank += (sd > sv) || (sd == sv && d2 < c);
-    }
-    perm[rank] = c;
-  }
+  for (int c = tid; c < nB; c += kBT) perm[falling_rank(sig, nB, c)] = c;
   __syncthreads();
   if (tid == 0) {
     const double smax = sig[perm[0]];
@@ -540,11 +532,7 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
   // X[k'][colid[r]] = x[r] / sigma (rows < nB)
   auto stage = [&](const double2 (&x)[kBRPL], int c, double sv) {
     if (!gact || c >= nB) return;
-    int rank = 0;
-    for (int d2 = 0; d2 < nB; ++d2) {
-      const double sd = sig[d2];
-      rank += (sd > sv) || (sd == sv && d2 < c);
-    }
+    const int rank = falling_rank(sig, nB, c);
     if (rank >= chi) return;
     const double inv = sv > 0.0 ? 1.0 / sv : 0.0;
 #pragma unroll

@@ -11,6 +11,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace gpeps {
@@ -62,7 +63,6 @@ struct InstParam {
   double g_c, g_s;    // cos(theta_J / 2), sin(theta_J / 2): g(s,t) = g_c - i g_s z_s z_t
 };
 
-// Per work-item bookkeeping written by the SVD kernel for the re-absorb kernel.
 // Complex float64 entries of per-item adjoint scratch for bond dimension cap D.
 __host__ __device__ inline int64_t adj_scratch(int D) { return (int64_t)48 * D * D; }
 
@@ -74,6 +74,20 @@ __host__ __device__ constexpr int64_t big_scratch(int /*D*/) {
   return (int64_t)2 * (2 * kMaxDBig) * (2 * kMaxDBig) + (int64_t)2 * kMaxDBig * kMaxDBig;
 }
 
+// Position of entry i of `key` (entries >= 0) in their falling order, equal ones in index order.  NaN
+// counts as -1: plain comparisons with it are all false, and several entries would then take one
+// position and leave others, which the kernels use as indices, unset.
+__host__ __device__ inline int falling_rank(const double* key, int n, int i) {
+  const double ki = fmax(key[i], -1.0);
+  int rank = 0;
+  for (int d = 0; d < n; ++d) {
+    const double kd = fmax(key[d], -1.0);
+    rank += (kd > ki) || (kd == ki && d < i);
+  }
+  return rank;
+}
+
+// Per work-item bookkeeping written by the SVD kernel for the re-absorb kernel.
 struct SlotMeta {
   int32_t de_old;   // bond dimension of the edge before the update
   int32_t chi_new;  // bond dimension after truncation

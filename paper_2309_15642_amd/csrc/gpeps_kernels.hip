@@ -946,15 +946,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
       if (ql == 0) nrm[qc] = qc < nB ? s2 : -1.0;
     }
     __syncthreads();
-    if (tid < nB) {
-      const double sv = nrm[tid];
-      int pos = 0;
-      for (int d = 0; d < nB; ++d) {
-        const double sd = nrm[d];
-        pos += (sd > sv) || (sd == sv && d < tid);
-      }
-      colid[pos] = tid;
-    }
+    if (tid < nB) colid[falling_rank(nrm, nB, tid)] = tid;
     __syncthreads();
     double2 x[RQ];
 #pragma unroll
@@ -1393,15 +1385,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
     if (lane == 0 && c < nB) sig[c] = sqrt(s2);
   }
   __syncthreads();
-  for (int c = tid; c < nB; c += NT) {
-    const double sv = sig[c];
-    int rank = 0;
-    for (int d = 0; d < nB; ++d) {
-      const double sd = sig[d];
-      rank += (sd > sv) || (sd == sv && d < c);
-    }
-    perm[rank] = c;
-  }
+  for (int c = tid; c < nB; c += NT) perm[falling_rank(sig, nB, c)] = c;
   __syncthreads();
   // truncation (one wave; nB <= 64): chi = #{sigma > trunc_rel sigma_0} capped at D (at least
   // 1), and the norm of the kept values for lambda_e

@@ -1,16 +1,18 @@
 // Peak-rate probes of the GPU the library runs on (libgpeps_peaks.so, used by the benchmark to
 // quote measured peaks beside the datasheet ones): FP64 vector FMA throughput, FP64 matrix-core
-// throughput (v_mfma_f64_16x16x4f64) and device-memory copy bandwidth; and one testing aid that
-// fills the LDS of every CU with a chosen pattern.  Measurement and testing only; no step of the
+// throughput (v_mfma_f64_16x16x4f64) and device-memory copy bandwidth; and two testing aids, one that
+// fills the LDS of every CU with a chosen pattern and one that sorts as the SVD kernels do.  Measurement and testing only; no step of the
 // simple update runs here.
 //
-// Every entry point launches one kernel on the given stream and returns a hipError_t as int;
+// Every other entry point launches one kernel on the given stream and returns a hipError_t as int;
 // the caller times the launch with events on that stream.  `out` receives one double per
 // thread (FMA) or per lane (MFMA) so that the arithmetic cannot be removed; its contents carry
 // no meaning.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include "gpeps_internal.h"
 
 namespace {
 
@@ -98,6 +100,13 @@ int gpeps_peak_copy(const void* src, void* dst, int64_t bytes, int n_blocks, voi
   hipLaunchKernelGGL(k_peak_copy, dim3(n_blocks), dim3(256), 0, (hipStream_t)stream, (const float4*)src,
                      (float4*)dst, bytes / 16);
   return (int)hipGetLastError();
+}
+
+// The order the SVD kernels sort n keys into (testing aid, host only): perm[position] = index.
+int gpeps_probe_falling_order(const double* key, int n, int* perm) {
+  if (!key || !perm || n < 1) return (int)hipErrorInvalidValue;
+  for (int i = 0; i < n; ++i) perm[gpeps::falling_rank(key, n, i)] = i;
+  return (int)hipSuccess;
 }
 
 // LDS fill (testing aid): n_blocks workgroups of 256 threads, each with `lds_bytes` (a multiple
