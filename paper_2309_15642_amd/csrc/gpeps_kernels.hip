@@ -554,6 +554,11 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
 
   // stage the R factors of one end ([2][r][de], row stride DS) into an LDS region
   auto stage_r = [&](double2* dst, int side, int rows) {
+    if (NMAX == 64 && 2 * rows * de <= NT) {  // the first steps: one entry a thread
+      const int sl = tid / (rows * de), rem = tid - sl * rows * de, rr = rem / de, k = rem - rr * de;
+      if (sl < 2) dst[sl * DM * DS + rr * DS + k] = Rg[(side * 2 + sl) * D * D + rr * D + k];
+      return;
+    }
     constexpr int PT = 2 * DM * DM / NT;  // entries a thread, all in flight
     double2 v[PT];
 #pragma unroll
@@ -597,10 +602,14 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
       double w[KS];
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {  // valid entries only: the loads do not wait for one another
-        const int k = min(4 * kk + lk, de - 1);
-        x[kk] = Ra[k];
-        y[kk] = Rb[k];
-        w[kk] = lam_e[k];
+        x[kk] = y[kk] = make_double2(0.0, 0.0);
+        w[kk] = 0.0;
+        if (NMAX == 32 || kk < ksteps) {  // (uniform)
+          const int k = min(4 * kk + lk, de - 1);
+          x[kk] = Ra[k];
+          y[kk] = Rb[k];
+          w[kk] = lam_e[k];
+        }
       }
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
@@ -1080,9 +1089,6 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
     int K = 1;
     while ((1 << K) < nB) ++K;
     const bool gact = jgrp < (1 << (K - 1));
-    // a wave whose groups are all inactive takes part in the barriers only (uniform over the wave;
-    // at NMAX = 64 only the first steps have such waves, and the test costs the others 0.7 %)
-    const bool wact = NMAX == 64 || (__builtin_amdgcn_readfirstlane(tid) >> 6) * GW < (1 << (K - 1));
     auto ins = [](int g, int hb, int bit) { return ((g >> hb) << (hb + 1)) | (bit << hb) | (g & ((1 << hb) - 1)); };
     auto xrow = [&](int u) { return jlane + LJ * u; };
     auto group_total2 = [&](double& a, double& b) {
@@ -1111,6 +1117,9 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
     // RB row blocks of LJ rows: a matrix of at most half the rows leaves the upper half of them out
     auto sweeps = [&](auto row_blocks) {
       constexpr int RB = decltype(row_blocks)::value;
+      // a wave whose groups are all inactive takes part in the barriers only (uniform over the wave;
+      // with every row block at NMAX = 64 none is, and the test costs 0.7 %)
+      const bool wact = (NMAX == 64 && RB == RPL) || (__builtin_amdgcn_readfirstlane(tid) >> 6) * GW < (1 << (K - 1));
       double2 xs[RB], xm[RB];  // stationary and moving column of the group
       double2 us[ACC ? RB : 1], um[ACC ? RB : 1];  // and the columns of W that go with them
       double ns = 0.0, nm = 0.0;  // their tracked squared norms
@@ -1314,7 +1323,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
                   }
                   if (kSpread || sb < 3) move_blk(sb);
                 };
-                if constexpr (RB >= 8) {  // straight-line code of that length takes the compiler many minutes
+                if constexpr (RB >= 8 || NMAX == 64) {  // straight-line code of that length takes the compiler many minutes
 #pragma unroll 1
                   for (int sb = 0; sb < 4; ++sb) quarter(sb);
                 } else {
@@ -1347,9 +1356,17 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
         converged = (sh_flag[sweep % 3][0] == 0) || (sh_flag[sweep % 3][1] == 0);
       }
     };
-    constexpr int kHalf = NMAX == 32 ? RPL / 2 : RPL;
-    if (kHalf < RPL && nB <= LJ * kHalf) sweeps(std::integral_constant<int, kHalf>());
-    else sweeps(std::integral_constant<int, RPL>());
+    if constexpr (NMAX == 64 && ACC) {
+      // the first steps above D = 16 (one 24-qubit ring, D = 20, launch of 4 / 8 / 16 / 32 columns: all eight row
+      // blocks 33 / 91 / 155 / 262 us, these 21 / 43 / 98 / 198)
+      if (nB <= 2 * LJ) sweeps(std::integral_constant<int, 2>());
+      else if (nB <= 4 * LJ) sweeps(std::integral_constant<int, 4>());
+      else sweeps(std::integral_constant<int, RPL>());
+    } else {
+      constexpr int kHalf = NMAX == 32 ? RPL / 2 : RPL;
+      if (kHalf < RPL && nB <= LJ * kHalf) sweeps(std::integral_constant<int, kHalf>());
+      else sweeps(std::integral_constant<int, RPL>());
+    }
   }
   if (tid == 0) {
     atomicAdd(reinterpret_cast<unsigned long long*>(st.stats) + 0, (unsigned long long)sweep);
