@@ -947,6 +947,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
       __syncthreads();
     } else {
     const int qc = tid / LQ, ql = tid - (tid / LQ) * LQ;
+    const int qfirst = (__builtin_amdgcn_readfirstlane(tid) >> 6) * (64 / LQ);  // first column of this wave
     {
       double s2 = 0.0;
       if (qc < nB)
@@ -957,76 +958,88 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
     __syncthreads();
     if (tid < nB) colid[falling_rank(nrm, nB, tid)] = tid;
     __syncthreads();
-    double2 x[RQ];
+    // RQB row blocks of LQ rows: a matrix of fewer rows leaves the others out.  A wave without columns,
+    // or with none left, takes part in the barriers only.
+    auto qr = [&](auto row_blocks) {
+      constexpr int RQB = decltype(row_blocks)::value;
+      double2 x[RQB];
 #pragma unroll
-    for (int u = 0; u < RQ; ++u) {
-      const int rr = ql + LQ * u;
-      x[u] = (qc < nB && rr < mB) ? B[colid[qc < nB ? qc : 0]][rr] : make_double2(0.0, 0.0);
-    }
-    auto publish = [&](int j) {  // rows and the norm below row j of the column of position j
-      double s2 = 0.0;
-#pragma unroll
-      for (int u = 0; u < RQ; ++u) {
+      for (int u = 0; u < RQB; ++u) {
         const int rr = ql + LQ * u;
-        vb[j & 1][rr] = x[u];
-        if (rr > j) s2 += cabs2(x[u]);
+        x[u] = (qc < nB && rr < mB) ? B[colid[qc < nB ? qc : 0]][rr] : make_double2(0.0, 0.0);
       }
-      s2 = group_sum_dpp(s2, LQ);
-      if (ql == 0) vn[j & 1] = s2;
-    };
-    if (qc == 0) publish(0);
-    __syncthreads();
-    for (int j = 0; j < nB; ++j) {
-      const double2 alpha = vb[j & 1][j];
-      const double s2 = vn[j & 1];
-      double2 v[RQ];
+      auto publish = [&](int j) {  // rows and the norm below row j of the column of position j
+        double s2 = 0.0;
 #pragma unroll
-      for (int u = 0; u < RQ; ++u) v[u] = vb[j & 1][ql + LQ * u];
-      // reflector v = x - beta e_j, beta = -phase(x_j) ||x||, x = rows j.. of the column; an exactly
-      // zero lower part needs none
-      const bool any = s2 > 0.0;
-      const double aa2 = cabs2(alpha);
-      const double nu2 = any ? aa2 + s2 : 1.0;
-      const double nu = nu2 * rsq_nr(nu2);
-      const double2 ph = aa2 > 0.0 ? cscale(alpha, rsq_nr(aa2)) : make_double2(1.0, 0.0);
-      const double2 beta = any ? cscale(ph, -nu) : alpha;
-      const double2 v0 = csub(alpha, beta);
-      const double tau = any ? 2.0 * rcp_nr(cabs2(v0) + s2) : 0.0;
-#pragma unroll
-      for (int u = 0; u < RQ; ++u) {
-        const int rr = ql + LQ * u;
-        v[u] = rr == j ? v0 : rr > j ? v[u] : make_double2(0.0, 0.0);
-      }
-      if (qc > j && qc < nB) {
-        double wr = 0.0, wi = 0.0;
-#pragma unroll
-        for (int u = 0; u < RQ; ++u) {
-          const double2 t = cmulc(v[u], x[u]);
-          wr += t.x;
-          wi += t.y;
-        }
-        group_sum2_dpp(wr, wi, LQ);
-        const double2 f = make_double2(wr * tau, wi * tau);
-#pragma unroll
-        for (int u = 0; u < RQ; ++u) x[u] = csub(x[u], cmul(v[u], f));
-        if (qc == j + 1) publish(j + 1);
-      } else if (qc == j) {
-        const double rt = any ? tau * rsq_nr(tau) : 0.0;
-#pragma unroll
-        for (int u = 0; u < RQ; ++u) {
+        for (int u = 0; u < RQB; ++u) {
           const int rr = ql + LQ * u;
-          if (rr < mB) refl[j * mB + rr] = cscale(v[u], rt);
-          if (rr == j) x[u] = beta;
+          vb[j & 1][rr] = x[u];
+          if (rr > j) s2 += cabs2(x[u]);
         }
-      }
+        s2 = group_sum_dpp(s2, LQ);
+        if (ql == 0) vn[j & 1] = s2;
+      };
+      if (qc == 0) publish(0);
       __syncthreads();
-    }
-    // B <- R^H: X[c][r] = conj(R(c, r)), c <= r, from the registers of column r
+      for (int j = 0; j < nB; ++j) {
+        if (qfirst >= nB || qfirst + 64 / LQ <= j) {
+          __syncthreads();
+          continue;
+        }
+        const double2 alpha = vb[j & 1][j];
+        const double s2 = vn[j & 1];
+        double2 v[RQB];
 #pragma unroll
-    for (int u = 0; u < RQ; ++u) {
-      const int c = ql + LQ * u;
-      if (qc < nB && c < nB) B[c][qc] = c <= qc ? cconj(x[u]) : make_double2(0.0, 0.0);
-    }
+        for (int u = 0; u < RQB; ++u) v[u] = vb[j & 1][ql + LQ * u];
+        // reflector v = x - beta e_j, beta = -phase(x_j) ||x||, x = rows j.. of the column; an exactly
+        // zero lower part needs none
+        const bool any = s2 > 0.0;
+        const double aa2 = cabs2(alpha);
+        const double nu2 = any ? aa2 + s2 : 1.0;
+        const double nu = nu2 * rsq_nr(nu2);
+        const double2 ph = aa2 > 0.0 ? cscale(alpha, rsq_nr(aa2)) : make_double2(1.0, 0.0);
+        const double2 beta = any ? cscale(ph, -nu) : alpha;
+        const double2 v0 = csub(alpha, beta);
+        const double tau = any ? 2.0 * rcp_nr(cabs2(v0) + s2) : 0.0;
+#pragma unroll
+        for (int u = 0; u < RQB; ++u) {
+          const int rr = ql + LQ * u;
+          v[u] = rr == j ? v0 : rr > j ? v[u] : make_double2(0.0, 0.0);
+        }
+        if (qc > j && qc < nB) {
+          double wr = 0.0, wi = 0.0;
+#pragma unroll
+          for (int u = 0; u < RQB; ++u) {
+            const double2 t = cmulc(v[u], x[u]);
+            wr += t.x;
+            wi += t.y;
+          }
+          group_sum2_dpp(wr, wi, LQ);
+          const double2 f = make_double2(wr * tau, wi * tau);
+#pragma unroll
+          for (int u = 0; u < RQB; ++u) x[u] = csub(x[u], cmul(v[u], f));
+          if (qc == j + 1) publish(j + 1);
+        } else if (qc == j) {
+          const double rt = any ? tau * rsq_nr(tau) : 0.0;
+#pragma unroll
+          for (int u = 0; u < RQB; ++u) {
+            const int rr = ql + LQ * u;
+            if (rr < mB) refl[j * mB + rr] = cscale(v[u], rt);
+            if (rr == j) x[u] = beta;
+          }
+        }
+        __syncthreads();
+      }
+      // B <- R^H: X[c][r] = conj(R(c, r)), c <= r, from the registers of column r
+#pragma unroll
+      for (int u = 0; u < RQB; ++u) {
+        const int c = ql + LQ * u;
+        if (qc < nB && c < nB) B[c][qc] = c <= qc ? cconj(x[u]) : make_double2(0.0, 0.0);
+      }
+    };
+    if (mB <= LQ * RQ / 4) qr(std::integral_constant<int, RQ / 4>());
+    else if (mB <= LQ * RQ / 2) qr(std::integral_constant<int, RQ / 2>());
+    else qr(std::integral_constant<int, RQ>());
     __syncthreads();
     }
   }
@@ -1358,7 +1371,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
     };
     if constexpr (NMAX == 64 && ACC) {
       // the first steps above D = 16 (one 24-qubit ring, D = 20, launch of 4 / 8 / 16 / 32 columns: all eight row
-      // blocks 33 / 91 / 155 / 262 us, these 21 / 43 / 98 / 198)
+      // blocks 33 / 91 / 155 / 262 us, these 21 / 43 / 74 / 188)
       if (nB <= 2 * LJ) sweeps(std::integral_constant<int, 2>());
       else if (nB <= 4 * LJ) sweeps(std::integral_constant<int, 4>());
       else sweeps(std::integral_constant<int, RPL>());
@@ -1455,19 +1468,23 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
   double2 qw[ACC ? RC : 1];
   if constexpr (ACC) {
     const double2* const refl = reinterpret_cast<const double2*>(st.tbuf) + rbuf_off(st, slot, 0, 0);
-    for (int batch = BWD ? 1 : 0; batch >= 0; --batch) {
+#pragma unroll
+    for (int u = 0; u < RC; ++u) qw[u] = make_double2(0.0, 0.0);
+    const int kfirst = (__builtin_amdgcn_readfirstlane(tid) >> 6) * (64 / LC);  // first column of this wave
+    auto left = [&](auto row_blocks, int batch) {  // (row blocks as in the QR)
+      constexpr int RCB = decltype(row_blocks)::value;
       const int k = kc + batch * DM;
       const int col = perm[k < nB ? k : 0];
 #pragma unroll
-      for (int u = 0; u < RC; ++u) {
+      for (int u = 0; u < RCB; ++u) {
         const int rr = lc + LC * u;
         const double2 t = W[col][rr];
         qw[u] = (k < nB && rr < nB) ? t : make_double2(0.0, 0.0);
       }
-      double2 nv[RC];  // the next reflector, in flight
+      double2 nv[RCB];  // the next reflector, in flight
       auto fetch = [&](int j) {
 #pragma unroll
-        for (int u = 0; u < RC; ++u) {
+        for (int u = 0; u < RCB; ++u) {
           const int rr = lc + LC * u;
           nv[u] = rr < mB ? refl[j * mB + rr] : make_double2(0.0, 0.0);
         }
@@ -1475,13 +1492,13 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
       const int nr = small_sq ? 0 : nB;
       if (nr) fetch(nr - 1);
       for (int j = nr - 1; j >= 0; --j) {
-        double2 v[RC];
+        double2 v[RCB];
 #pragma unroll
-        for (int u = 0; u < RC; ++u) v[u] = nv[u];
+        for (int u = 0; u < RCB; ++u) v[u] = nv[u];
         if (j > 0) fetch(j - 1);
         double wr = 0.0, wi = 0.0;
 #pragma unroll
-        for (int u = 0; u < RC; ++u) {
+        for (int u = 0; u < RCB; ++u) {
           const double2 t = cmulc(v[u], qw[u]);
           wr += t.x;
           wi += t.y;
@@ -1489,17 +1506,22 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
         group_sum2_dpp(wr, wi, LC);
         const double2 f = make_double2(wr, wi);
 #pragma unroll
-        for (int u = 0; u < RC; ++u) qw[u] = csub(qw[u], cmul(v[u], f));
+        for (int u = 0; u < RCB; ++u) qw[u] = csub(qw[u], cmul(v[u], f));
       }
       if (BWD && k < nB) {
         const int ld = 2 * D;
         double2* Og = (trans ? st.bV : st.bU) + (int64_t)slot * ld * ld;
 #pragma unroll
-        for (int u = 0; u < RC; ++u) {
+        for (int u = 0; u < RCB; ++u) {
           const int rr = lc + LC * u;
           if (rr < mB) Og[rr * ld + k] = qw[u];
         }
       }
+    };
+    for (int batch = BWD ? 1 : 0; batch >= 0; --batch) {
+      if (kfirst + batch * DM >= (BWD ? nB : chi)) continue;
+      if (mB <= LC * RC / 2) left(std::integral_constant<int, RC / 2>(), batch);
+      else left(std::integral_constant<int, RC>(), batch);
     }
     __syncthreads();  // every reflector has been read
   }
