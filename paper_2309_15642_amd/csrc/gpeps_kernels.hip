@@ -533,7 +533,6 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
   const EdgeInfo& E = st.edges[e];
   const InstParam ip = st.inst[E.inst];
   const int D = st.D;
-  const int tid = threadIdx.x;
   const int de = st.chi[e];
   double* lam_e = st.lam + (int64_t)e * D;
 
@@ -549,6 +548,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
   const bool trans = n0 > m0;  // orthogonalise the shorter side
   const int mB = trans ? n0 : m0;
   const int nB = trans ? m0 : n0;
+  const int tid = threadIdx.x;
   const bool small_sq = ACC && nB <= kSmallB && mB == nB;
   const double2* Rg = st.rbuf + rbuf_off(st, slot, 0, 0);  // 4 consecutive [D][D] blocks: i0, i1, j0, j1
 
@@ -1104,9 +1104,9 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
     const bool gact = jgrp < (1 << (K - 1));
     auto ins = [](int g, int hb, int bit) { return ((g >> hb) << (hb + 1)) | (bit << hb) | (g & ((1 << hb) - 1)); };
     auto xrow = [&](int u) { return jlane + LJ * u; };
-    auto group_total2 = [&](double& a, double& b) {
+    auto group_total2 = [&](double& a, double& b, int rows) {
       if constexpr (!kSpread) {
-        group_sum2_dpp(a, b, LJ);
+        group_sum2_dpp(a, b, rows < LJ ? rows : LJ);
       } else {
         if constexpr (LJ == 8) {
           a = own * __builtin_amdgcn_mfma_f64_4x4x4f64(a, 1.0, 0.0, 0, 0, 0);  // sum over l / 16 of l % 4 = i, in D[i][j]
@@ -1127,9 +1127,18 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
     if (kSpread)
       for (int c = tid; c < NMAX; c += NT) scl[c] = 1.0;
     __syncthreads();
-    // RB row blocks of LJ rows: a matrix of at most half the rows leaves the upper half of them out
-    auto sweeps = [&](auto row_blocks) {
+    // RB row blocks of LJ rows: a matrix of at most half the rows leaves the upper half of them out.
+    // SOLO: at most 8 columns, LJ = 16 lanes a pair: one wave has them all, goes without barriers and sums over
+    // the lanes that have rows; the others wait for it.
+    auto sweeps = [&](auto row_blocks, auto solo) {
       constexpr int RB = decltype(row_blocks)::value;
+      constexpr bool SOLO = decltype(solo)::value;
+      constexpr int SR = SOLO ? 8 : 64;  // rows of a sum
+      auto barrier = [&]() {
+        if constexpr (SOLO) wave_lds_sync();
+        else __syncthreads();
+      };
+      if (SOLO && __builtin_amdgcn_readfirstlane(tid) >= 64) return;
       // a wave whose groups are all inactive takes part in the barriers only (uniform over the wave;
       // with every row block at NMAX = 64 none is, and the test costs 0.7 %)
       const bool wact = (NMAX == 64 && RB == RPL) || (__builtin_amdgcn_readfirstlane(tid) >> 6) * GW < (1 << (K - 1));
@@ -1197,7 +1206,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
           if (hb == 0) {
             ns = fold(xs, us, ps);
             nm = fold(xm, um, pm);
-            group_total2(ns, nm);
+            group_total2(ns, nm, SR);
           } else {
             ns = nrm[cs_id];
             nm = nrm[cm_id];
@@ -1251,7 +1260,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
               gr = g.x;
               gi = g.y;
             }
-            group_total2(gr, gi);
+            group_total2(gr, gi, SR);
             const double al = ns, be = nm;
             const double g2 = kSpread ? (gr * gr + gi * gi) * (ps * pm) : gr * gr + gi * gi;
             const double ab = al * be;
@@ -1346,7 +1355,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
               }
               if (t0 + GW < nt) {
                 store_col(xm, um, mid(kSpread ? t0 : t0 + GW - 1), nm, pm);
-                __syncthreads();
+                barrier();
                 load_col(xm, um, mid(t0 + GW));
                 nm = nrm[mid(t0 + GW)];
                 if (kSpread) pm = scl[mid(t0 + GW)];
@@ -1364,21 +1373,24 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
             rot = false;
             big = false;
           }
-          __syncthreads();
+          barrier();
         }
         converged = (sh_flag[sweep % 3][0] == 0) || (sh_flag[sweep % 3][1] == 0);
       }
     };
     if constexpr (NMAX == 64 && ACC) {
       // the first steps above D = 16 (one 24-qubit ring, D = 20, launch of 4 / 8 / 16 / 32 columns: all eight row
-      // blocks 33 / 91 / 155 / 262 us, these 21 / 43 / 74 / 188)
-      if (nB <= 2 * LJ) sweeps(std::integral_constant<int, 2>());
-      else if (nB <= 4 * LJ) sweeps(std::integral_constant<int, 4>());
-      else sweeps(std::integral_constant<int, RPL>());
+      // blocks 33 / 91 / 155 / 262 us, these 21 / 42 / 74 / 188)
+      if (nB <= 2 * LJ) sweeps(std::integral_constant<int, 2>(), std::false_type());
+      else if (nB <= 4 * LJ) sweeps(std::integral_constant<int, 4>(), std::false_type());
+      else sweeps(std::integral_constant<int, RPL>(), std::false_type());
     } else {
       constexpr int kHalf = NMAX == 32 ? RPL / 2 : RPL;
-      if (kHalf < RPL && nB <= LJ * kHalf) sweeps(std::integral_constant<int, kHalf>());
-      else sweeps(std::integral_constant<int, RPL>());
+      constexpr bool kSolo = ACC && LJ == 16;
+      if (kSolo && nB <= 8) sweeps(std::integral_constant<int, kHalf>(), std::integral_constant<bool, kSolo>());
+      else if (kHalf < RPL && nB <= LJ * kHalf) sweeps(std::integral_constant<int, kHalf>(), std::false_type());
+      else sweeps(std::integral_constant<int, RPL>(), std::false_type());
+      if (kSolo && nB <= 8) __syncthreads();
     }
   }
   if (tid == 0) {
