@@ -488,15 +488,7 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
     if (!converged) redistribute(0, K - 1);
   }
   fold();
-  if (tid == 0) {
-    atomicAdd(reinterpret_cast<unsigned long long*>(st.stats) + 0, (unsigned long long)sweep);
-    atomicAdd(reinterpret_cast<unsigned long long*>(st.stats) + 1, 1ull);
-    atomicMax(reinterpret_cast<unsigned long long*>(st.stats) + 2, (unsigned long long)sweep);
-    if (!converged) {
-      atomicAdd(reinterpret_cast<unsigned long long*>(st.stats) + 3, 1ull);
-      flag_status(st.status, kStatusNoConverge);
-    }
-  }
+  if (tid == 0) count_svd(st, sweep, converged);
 
   // singular values (norms of the held columns), stable descending order, truncation
   const double s_s = sqrt(ns), s_m = sqrt(nm);

@@ -236,6 +236,18 @@ __device__ __forceinline__ double2 gate_phase(const InstParam& ip, int s, int t)
 
 __device__ __forceinline__ void flag_status(int32_t* status, int bits) { atomicOr(status, bits); }
 
+// One SVD of `sweep` sweeps in the statistics (one thread of a workgroup).
+__device__ __forceinline__ void count_svd(const DevState& st, int sweep, bool converged) {
+  unsigned long long* s = reinterpret_cast<unsigned long long*>(st.stats) + (blockIdx.x % kStatLines) * kStatStride;
+  atomicAdd(s + 0, (unsigned long long)sweep);
+  atomicAdd(s + 1, 1ull);
+  atomicMax(s + 2, (unsigned long long)sweep);
+  if (!converged) {
+    atomicAdd(s + 3, 1ull);
+    flag_status(st.status, kStatusNoConverge);
+  }
+}
+
 // ------------------------------------------------------------------ site-matrix geometry
 
 // Active geometry of one end of an edge: rows run over the other legs

@@ -419,7 +419,7 @@ gpeps_status build_layout(const gpeps_graph* graphs, int32_t n_graphs, const int
   L.class_slots = slots;
   L.off_rbuf = take(ncl * slots * 4 * D * D * sizeof(double2));
   L.off_tbuf = take(slots * 4 * D * D * esize);
-  L.off_stats = take(4 * sizeof(int64_t));
+  L.off_stats = take((size_t)kStatLines * kStatStride * sizeof(int64_t));
   L.off_meta = take(ncl * slots * sizeof(SlotMeta));
   L.off_z = take((size_t)L.NV * sizeof(double));
   L.off_hist = take((size_t)cfg->max_steps * L.NV * sizeof(double));
@@ -1231,9 +1231,16 @@ extern "C" {
 
 gpeps_status gpeps_stats(gpeps_ctx* c, int64_t* out, int32_t n) {
   if (!c || !out || n < 0) return fail(c, GPEPS_ERR_ARG, "ctx and out are required, n >= 0");
-  int64_t v[4] = {0, 0, 0, 0};
-  HIP_TRY(c, hipMemcpyAsync(v, c->st.stats, sizeof(v), hipMemcpyDeviceToHost, c->stream));
+  int64_t lines[kStatLines][kStatStride];
+  HIP_TRY(c, hipMemcpyAsync(lines, c->st.stats, sizeof(lines), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
+  int64_t v[4] = {0, 0, 0, 0};
+  for (const auto& l : lines) {
+    v[0] += l[0];
+    v[1] += l[1];
+    v[2] = std::max(v[2], l[2]);
+    v[3] += l[3];
+  }
   for (int k = 0; k < n; ++k) out[k] = k < 4 ? v[k] : 0;
   return GPEPS_OK;
 }

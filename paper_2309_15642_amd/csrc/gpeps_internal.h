@@ -74,6 +74,12 @@ __host__ __device__ constexpr int64_t big_scratch(int /*D*/) {
   return (int64_t)2 * (2 * kMaxDBig) * (2 * kMaxDBig) + (int64_t)2 * kMaxDBig * kMaxDBig;
 }
 
+// The SVD statistics are counted on kStatLines lines of memory, workgroup b on line b % kStatLines, and
+// added up when they are asked for: on one line the atomics of a launch take 36 ns a workgroup,
+// one after the other.
+constexpr int kStatLines = 64;
+constexpr int kStatStride = 16;  // int64 entries a line of 128 bytes
+
 // Position of entry i of `key` (entries >= 0) in their falling order, equal ones in index order.  NaN
 // counts as -1: plain comparisons with it are all false, and several entries would then take one
 // position and leave others, which the kernels use as indices, unset.
@@ -104,7 +110,7 @@ struct DevState {
   const InstParam* inst;  // [n_inst]
   double2* rbuf;          // [slots][2 sides][2 slices][D][D] float64 R factors
   void* tbuf;             // [slots][2][2][D][D] re-absorb matrices (storage precision)
-  int64_t* stats;         // [4] Jacobi sweeps total, SVD count, max sweeps, non-converged count
+  int64_t* stats;         // [kStatLines][kStatStride] Jacobi sweeps total, SVD count, max sweeps, non-converged count
   // adjoint (reverse sweep) only
   double2* bU;            // [slots][2D][2D] all left singular vectors of Theta' (row stride 2D)
   double2* bV;            // [slots][2D][2D] all right singular vectors

@@ -1393,15 +1393,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
       if (kSolo && nB <= 8) __syncthreads();
     }
   }
-  if (tid == 0) {
-    atomicAdd(reinterpret_cast<unsigned long long*>(st.stats) + 0, (unsigned long long)sweep);
-    atomicAdd(reinterpret_cast<unsigned long long*>(st.stats) + 1, 1ull);
-    atomicMax(reinterpret_cast<unsigned long long*>(st.stats) + 2, (unsigned long long)sweep);
-    if (!converged) {
-      atomicAdd(reinterpret_cast<unsigned long long*>(st.stats) + 3, 1ull);
-      flag_status(st.status, kStatusNoConverge);
-    }
-  }
+  if (tid == 0) count_svd(st, sweep, converged);
 
   // singular values (column norms, two columns per pair group, the scales folded in), stable
   // descending order
@@ -2443,7 +2435,7 @@ __global__ __launch_bounds__(256) void k_reset(DevState st) {
     *st.step_ctr = 0;
     *st.status = 0;
   }
-  if (gid < 4) st.stats[gid] = 0;
+  if (gid < kStatLines * kStatStride) st.stats[gid] = 0;
 }
 
 // ------------------------------------------------------------------ host-side launchers
