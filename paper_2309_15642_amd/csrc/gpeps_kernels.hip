@@ -548,7 +548,12 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
   const bool trans = n0 > m0;  // orthogonalise the shorter side
   const int mB = trans ? n0 : m0;
   const int nB = trans ? m0 : n0;
-  const int tid = threadIdx.x;
+  // complex128: 9 to 16 columns keep two waves of the four busy.  Workgroups that share a CU have numbers
+  // a multiple of 256 (the CUs) apart and their first waves sit on successive SIMDs, so the second one's
+  // busy pair would overlap the first one's: it numbers its waves from the SIMD after.  127 qubits x 8
+  // at D = 5 70 -> 63 us, at D = 8 82 -> 71.  (One busy wave is placed best without.)
+  const int turn = ACC && NT == 256 && nB > 8 ? (0 - (int)(blockIdx.x >> 8)) & 3 : 0;
+  const int tid = (threadIdx.x + 64 * turn) & (NT - 1);
   const bool small_sq = ACC && nB <= kSmallB && mB == nB;
   const double2* Rg = st.rbuf + rbuf_off(st, slot, 0, 0);  // 4 consecutive [D][D] blocks: i0, i1, j0, j1
 
@@ -1140,8 +1145,16 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
       };
       if (SOLO && __builtin_amdgcn_readfirstlane(tid) >= 64) return;
       // a wave whose groups are all inactive takes part in the barriers only (uniform over the wave;
-      // with every row block at NMAX = 64 none is, and the test costs 0.7 %)
-      const bool wact = (NMAX == 64 && RB == RPL) || (__builtin_amdgcn_readfirstlane(tid) >> 6) * GW < (1 << (K - 1));
+      // with every row block at NMAX = 64 none is, and the test costs 0.7 %); complex128 up to D = 16 leaves
+      // out every GW rounds in which a wave has none of the nB columns to move, too: 18 columns run as
+      // 32, and with several workgroups a CU the rounds on padding cost what they issue (127 qubits x 16 at
+      // D = 9, 12 steps 9.90 -> 8.24 ms)
+      const int wgrp = (__builtin_amdgcn_readfirstlane(tid) >> 6) * GW;  // first group of this wave
+      const bool wact = (NMAX == 64 && RB == RPL) || wgrp < (1 << (K - 1));
+      auto moves = [&](int hb, int t0) {  // of rounds t0 .. t0 + GW - 1 of block hb
+        if constexpr (ACC && NMAX == 32) return ins(wgrp ^ ((t0 ^ (t0 >> 1)) & ~(GW - 1)), hb, 1) < nB;
+        else return wact;
+      };
       double2 xs[RB], xm[RB];  // stationary and moving column of the group
       double2 us[ACC ? RB : 1], um[ACC ? RB : 1];  // and the columns of W that go with them
       double ns = 0.0, nm = 0.0;  // their tracked squared norms
@@ -1326,7 +1339,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
             return ins((w * 4 + blk) << LB | low, hb, 1);
           };
           if (nt < GW) {
-            if (wact) {
+            if (moves(hb, 0)) {
               for (int t = 0; t < nt; ++t) {
                 round();
                 if (t + 1 < nt) move_xor(__builtin_ctz(t + 1));
@@ -1336,7 +1349,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
             // (spread lanes: blk turns once more than it has to, so that every trip is the same
             // straight line and the columns end where they began the GW rounds)
             for (int t0 = 0; t0 < nt; t0 += GW) {
-              if (wact) {
+              if (moves(hb, t0)) {
                 auto quarter = [&](int sb) {
 #pragma unroll
                   for (int r = 0; r < 1 << LB; ++r) {

@@ -39,3 +39,20 @@ def test_few_columns(d, threads):
     assert max(np.max(x) for x in s.bond_dims()) == d
     s.close()
     assert np.max(np.abs(h - su.evolve_graph(g, 0.8, TJ, d, steps, 1e-12).z)) < 1e-10
+
+
+@pytest.mark.parametrize("d,instances", [(5, 40), (5, 100), (9, 70)])
+def test_workgroups_that_share_a_cu_give_the_same_bits(d, instances):
+    """More workgroups a launch than CUs: from the 257th on a workgroup numbers its waves differently."""
+    _need_gpu()
+    from paper_2309_15642_amd.simulator import Simulator
+    g = heavy_hex(3, 7, False)
+    steps = 6
+    print(f"[gpu case] 25 qubits x {instances} D={d} c128, {steps} steps", flush=True)
+    s = Simulator([g], [0] * instances, [0.8] * instances, [TJ] * instances, d_max=d, precision="c128", trunc_rel=1e-12,
+                  max_steps=steps)
+    s.step(steps)
+    h = s.z_history()
+    s.close()
+    assert np.max(np.abs(h[0] - su.evolve_graph(g, 0.8, TJ, d, steps, 1e-12).z)) < 1e-10
+    assert all(np.array_equal(x, h[0]) for x in h[1:])
