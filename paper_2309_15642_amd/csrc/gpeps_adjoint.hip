@@ -181,7 +181,7 @@ __global__ __launch_bounds__(1024) void k_adj_readout(DevState st) {
     const int l = bin / D, k = bin - (bin / D) * D;
     const int sl = l == 0 ? s0 : l == 1 ? s1 : 1;  // stride of leg l
     double sacc = 0.0;
-    if (lw[l][k] != 0.0) {  // the tensor is zero past a leg's active indices
+    if (k < st.chi[V.leg[l]]) {  // the tensor is zero past a leg's active indices
 #pragma unroll 4
       for (int j = lane; j < inner; j += 64) {
         const int hi = j / sl, lo = j - (j / sl) * sl;  // digits above and below leg l

@@ -2357,26 +2357,23 @@ __global__ __launch_bounds__(NT) void k_expect_z(DevState st, int v_first, int r
   __syncthreads();
   // threads take the inner legs j (their weight computed once, loads coalesced across threads)
   // and loop over the active indices of the outermost leg a; with fewer inner indices than threads
-  // the threads form G groups of `inner`, group g taking a = g, g + G, ...  A weight is zero past
-  // the active indices of a leg, where the tensor is zero too: nothing is read there.
+  // the threads form G groups of `inner`, group g taking a = g, g + G, ...  Past the active indices
+  // of a leg the tensor is zero: nothing is read there.  (Told by the index, not by a weight of zero: where a
+  // tiny lambda squares to zero an infinite element has to end in the status.)
   int inner = 1;
   for (int l = 1; l < V.deg; ++l) inner *= D;
   const int na = V.deg >= 1 ? st.chi[V.leg[0]] : 1;
+  const int n1 = V.deg >= 2 ? st.chi[V.leg[1]] : 1, n2 = V.deg == 3 ? st.chi[V.leg[2]] : 1;
   const int ps = inner * (V.deg >= 1 ? D : 1);
   const CT* gam = reinterpret_cast<const CT*>(st.gamma) + V.goff;
-  auto weight = [&](int j) {
-    double w = 1.0;
-    if (V.deg == 3) w = lw[1][j / D] * lw[2][j - (j / D) * D];
-    else if (V.deg == 2) w = lw[1][j];
-    return w;
-  };
   double r0 = 0.0, r1 = 0.0;
   const int G = inner < NT ? NT / inner : 1;
   const int g = inner < NT ? tid / inner : 0;
   if (g < G) {
     for (int j = tid - g * inner; j < inner; j += NT) {
-      const double w = weight(j);
-      if (w == 0.0) continue;
+      const int j1 = V.deg == 3 ? j / D : j, j2 = V.deg == 3 ? j - (j / D) * D : 0;
+      if (j1 >= n1 || j2 >= n2) continue;
+      const double w = lw[1][j1] * lw[2][j2];  // (1 for a missing leg)
       for (int a0 = g; a0 < na; a0 += UA * G) {
         CT x0[UA], x1[UA];
 #pragma unroll

@@ -66,3 +66,30 @@ def test_nan_before_a_reverse_sweep(d, precision, threads):
         with pytest.raises(Exception, match="non-finite"):
             s.backward([np.full(g.n_nodes, 1.0 / g.n_nodes)])
         s.close()
+
+
+@pytest.mark.parametrize("d,precision", [(2, "c128"), (8, "c64"), (20, "c128")])
+def test_infinite_element_under_a_vanishing_weight(d, precision):
+    """An infinite element where lambda^2 is zero in float64 is no zero term: the readout reports it."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from heavyhex import ring
+    from paper_2309_15642_amd.simulator import Simulator
+    g = ring(12)
+    print(f"[gpu case] ring of 12 D={d} {precision}, infinity under lambda 1e-170", flush=True)
+    s = Simulator([g], [0], [0.8], [TJ], d_max=d, precision=precision, trunc_rel=0.0, max_steps=2)
+    s.step(2)
+    s.sync()
+    esize = 16 if precision == "c128" else 8
+    n_gamma = sum(2 * d ** int(k) for k in g.degrees())
+    off_lam = -(-n_gamma * esize // 256) * 256  # the weights [edge][d] follow the site tensors
+    lam = s.workspace[off_lam : off_lam + 8 * d * len(g.edges)].view(torch.float64).view(-1, d)
+    inner = max(e for e, (u, v) in enumerate(g.edges) if 0 in (u, v))  # the last leg of qubit 0
+    assert lam[inner, 1] > 0  # that leg has a second index
+    lam[inner, 1] = 1e-170
+    s.workspace[: 2 * esize].view(torch.float64 if precision == "c128" else torch.float32)[2] = float("inf")  # its element [0][0][1]
+    torch.cuda.synchronize()
+    with pytest.raises(Exception, match="non-finite"):
+        s.expect_z()
+    s.close()
