@@ -10,7 +10,9 @@ resident on the device before the timed region starts.
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME]
 
 Prints one JSON line.  value = gate updates per second of the batched path
-(instances x edges x T per evolution / seconds per evolution).
+(instances x edges x T per evolution / seconds per evolution).  The other
+workloads are in it with their figures alone; --report FILE keeps their kernel
+tables, work models and per-instance lists as well.
 """
 
 from __future__ import annotations
@@ -57,6 +59,35 @@ def measured_traffic(workload: str, kernel: str):
 
 def log(msg: str) -> None:
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
+
+
+LINE_LIMIT = 7000  # characters of the printed line: whoever reads the end of the output gets all of it
+
+
+def result_line(out: dict) -> str:
+    """The report as one line of at most LINE_LIMIT characters: the headline workload as it is, of every
+    other leg its figures and short texts (rounded to six digits), no tables or lists."""
+    whole = ("config", "tiles", "plain", "jacobi", "kernels", "roofline")
+
+    def figures(d: dict) -> dict:
+        kept = {}
+        for k, v in d.items():
+            if isinstance(v, float):
+                kept[k] = float(f"{v:.6g}")
+            elif isinstance(v, (bool, int)) or v is None or (isinstance(v, str) and len(v) <= 32):
+                kept[k] = v
+            elif k == "roofline":
+                kept["roofline_frac"] = float(f"{v['frac']:.4g}")
+        return kept
+
+    line = {k: figures(v) if isinstance(v, dict) and k not in whole else v for k, v in out.items() if not isinstance(v, list)}
+    text = json.dumps(line)
+    for k in reversed([k for k, v in line.items() if isinstance(v, dict) and k not in whole]):
+        if len(text) <= LINE_LIMIT:
+            break
+        del line[k]  # (what does not fit is in the report)
+        text = json.dumps(line)
+    return text
 
 
 # ----------------------------------------------------------------- algorithmic work model
@@ -322,6 +353,7 @@ def main() -> int:
     ap.add_argument("--no-autotune", action="store_true", help="keep the default tile shapes")
     ap.add_argument("--tiles", default=None, metavar="QR,RB,SV",
                     help="fixed tiles (QR rows per lane, re-absorb tiles per wave, SVD threads) instead of autotuning")
+    ap.add_argument("--report", default=None, metavar="FILE", help="also write the whole report, as JSON, to FILE")
     ap.add_argument("--calib-copy", type=int, default=0, metavar="MIB",
                     help="first run a plain device-to-device copy of MIB MiB (counter calibration)")
     args = ap.parse_args()
@@ -604,7 +636,10 @@ def main() -> int:
                 for v in d.values():
                     add_measured(v)
         add_measured(out)
-    print(json.dumps(out))
+    if args.report:
+        with open(args.report, "w") as f:
+            json.dump(out, f)
+    print(result_line(out))
     return 0
 
 
