@@ -1310,8 +1310,13 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
               const double f = ok ? copysign(rh, d) * rc : 0.0;
               const double cs = ok ? x * rc : 1.0;
               const double2 sph = make_double2(gr * f, gi * f);  // s e^{i phi}
-              tg = g2 * f * rc;
-              if constexpr (ACC) t2 = tg * f * rc;
+              if constexpr (ACC) {
+                const double F = f * rc;
+                tg = g2 * F;
+                t2 = tg * F;
+              } else {
+                tg = g2 * f * rc;
+              }
               auto turn = [&](double2& a, double2& b) {
                 const double2 a0 = a, b0 = b;
                 a = csub(cscale(a0, cs), cmulc(sph, b0));
@@ -1400,9 +1405,9 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
     } else {
       constexpr int kHalf = NMAX == 32 ? RPL / 2 : RPL;
       constexpr bool kSolo = ACC && LJ == 16;
-      if (kSolo && nB <= 8) sweeps(std::integral_constant<int, kHalf>(), std::integral_constant<bool, kSolo>());
-      else if (kHalf < RPL && nB <= LJ * kHalf) sweeps(std::integral_constant<int, kHalf>(), std::false_type());
-      else sweeps(std::integral_constant<int, RPL>(), std::false_type());
+      if (kHalf == RPL || nB > LJ * kHalf) sweeps(std::integral_constant<int, RPL>(), std::false_type());
+      else if (!kSolo || nB > 8) sweeps(std::integral_constant<int, kHalf>(), std::false_type());
+      else sweeps(std::integral_constant<int, kHalf>(), std::integral_constant<bool, kSolo>());
       if (kSolo && nB <= 8) __syncthreads();
     }
   }
