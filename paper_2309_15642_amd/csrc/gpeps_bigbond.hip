@@ -14,8 +14,9 @@
 //     and the moving columns pass between its eight groups by one DPP instruction a word, and
 //     across waves through an LDS exchange (64 columns, 130 KB); columns carry a scale, so a
 //     rotation takes 8 instead of 12 operations per pair of entries (as k_theta_svd at D = 32);
-//     between blocks every column goes to its new owner through LDS (column ids < 64) and
-//     the item's HBM scratch (ids >= 64);
+//     between blocks every column goes to its new owner through LDS, the two halves of the groups in
+//     turn; into and out of the last block at 128 columns the ids of 64 and more go through the
+//     item's HBM scratch;
 //   * B is first reduced by Householder QR with column pivoting, B P = Q R (columns in registers,
 //     4 lanes each; the pivot column goes through LDS every step), and the Jacobi iteration runs
 //     on X = R^H (nB x nB), whose orthogonalised columns are B's right singular vectors with rows
@@ -28,7 +29,7 @@
 //       T_i^(s)[k,k'] = lambda_k / sigma_k' sum_{t,b} g(s,t) R_j^(t)[b,k] V[(t,b),k'],
 //       T_j^(t)[k,k'] = lambda_k / sigma_k' sum_{s,a} g(s,t) conj(U[(s,a),k']) R_i^(s)[a,k].
 // A sweep ends the iteration when it rotates nothing, or (complex64 storage) when all its
-// rotations had |g|^2 <= 1e-8 al be, as in k_theta_svd.
+// rotations had |g|^2 <= 1e-8 al be, as in k_theta_svd; complex128 here has no quiet level.
 
 #include <hip/hip_runtime.h>
 #include <math.h>

@@ -74,7 +74,7 @@ __device__ __forceinline__ double2 bp_wmsg(const double2* M, int D, int n, const
 // Y is formed with b' on the rows, so the register that receives Y[4 r + l / 16][l % 16] is the
 // operand of k step r of the last product as it stands: only X goes through LDS (beside W1, which
 // the caller has put there, [b][b'] with row stride N + 1).  Lane l ends with m[a0 + l / 16 + 4 r][16 t + l % 16], this wave's share, in (mr[t][r], mi[t][r]).
-// Bound by the FP64 matrix cores at D = 32, where one workgroup fills a CU's LDS (131 KB) with two
+// Bound by the FP64 matrix cores at D = 32, where one workgroup fills a CU's LDS (149 KB) with two
 // waves per SIMD; at D <= 16 by the latency of the phases.  Every wave of the workgroup calls this.
 template <typename CT, int N, int NB = bp_tiles<N>()>
 __device__ __forceinline__ void bp_block(const CT* __restrict__ gam, const BpSite& g, const double2* W1,

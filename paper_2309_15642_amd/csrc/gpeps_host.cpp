@@ -527,10 +527,12 @@ gpeps_status enqueue_edge_kernel(gpeps_ctx* c, int which, int first, int count, 
 // chain (85 us for one instance at D = 16, one wave 150 us); one wave does the same with half the
 // float64 instructions and no barriers, and eight such workgroups fit a CU against five, so it wins
 // once the launches fill the chip: 127 qubits at D = 16, 20 steps, 256 / 64 threads: 16 instances
-// 12.7 / 15.0 ms, 32 (1728 items in the largest class) 21.2 / 19.7 ms, 128 72.3 / 62.0 ms; D = 12
-// x 32 19.3 / 17.1 ms.  At D <= 8 half of the four waves' work is gone already (64 instances at
-// D = 8 16.0 / 18.3 ms), and complex128 holds two matrices more (one wave a SIMD).  The choice
-// depends on the whole context, not on one launch: batched and plain mode give the same bits.
+// 12.7 / 14.8 ms, 24 16.6 / 17.4, 26 17.9 / 17.9, 32 (1728 items in the largest class) 20.8 / 19.3, 128
+// 71.7 / 60.4; D = 12 x 24 14.4 / 14.5, x 32 18.2 / 16.0.  At D <= 8 half of the four waves' work is gone
+// already and the two are close (D = 8 x 32 8.5 / 8.2, x 128 27.0 / 24.4; D = 4 x 64 8.7 / 9.0): four waves
+// stay.  complex128 holds two matrices more (one wave a SIMD): D = 8 x 64 26.3 / 33.9, D = 16 x 32
+// 42.5 / 55.9.  The choice depends on the whole context, not on one launch: batched and plain mode
+// give the same bits.
 int default_svd_threads(const gpeps_ctx* c) {
   constexpr int kCus = 256;
   return !c->c128 && c->D > 8 && c->D <= 16 && c->L.max_items >= 6 * kCus ? 64 : 256;
@@ -908,9 +910,10 @@ gpeps_status gpeps_init(gpeps_ctx** out, const gpeps_graph* graphs, int32_t n_gr
   st.max_steps = cfg->max_steps;
   st.trunc_rel = cfg->trunc_rel;
   // rows of an end over four workgroups (complex64, d_max > 32): pays while the ends of a class leave
-  // CUs idle and some end has rows to share (absorb of one class of 127 qubits, whole / split: one
-  // instance at D = 64 147 / 104 us, D = 33 58 / 53; four at D = 33 94 / 150; ring, two legs a
-  // vertex, 11.8 / 14.4)
+  // CUs idle and some end has rows to share (absorb of one class of 127 qubits, 48 edges an instance,
+  // whole / split, mean over eight steps: one instance at D = 64 166 / 115 us, D = 48 108 / 82, D = 33 67 / 59; two
+  // at D = 64 175 / 138, D = 48 110 / 100, D = 40 87 / 89, D = 33 70 / 82; three at D = 64 183 / 194, D = 48 114 / 137:
+  // the line lies where it pays at every bond; ring, two legs a vertex, 11.8 / 14.4)
   st.gram_split = c->D > kMaxD && L.max_items <= 64 &&
                   std::any_of(L.verts.begin(), L.verts.end(), [](const VertexInfo& v) { return v.deg == kMaxDeg; });
   st.tune_rb = default_rb_tiles(c);

@@ -482,10 +482,10 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
 // 1.4e-10 without the test of the angle, to 3.5e-15 with it, as after a sweep without rotations; the sweeps of
 // separated values are the same).  R from a
 // Householder QR of B with its columns sorted by norm, and the rotations accumulated in W, so that
-// the other set is Q W, accurate for every sigma.  D = 16, ten steps of the 127-qubit graph: 104 us
+// the other set is Q W, accurate for every sigma.  D = 16, ten steps of the 127-qubit graph: 106 us
 // per launch and 5.3 sweeps (9.3 at most 17 without the QR, through LDS: 192 us).  A square B of at
-// most kSmallB columns takes Q = I, R = B: the QR and the reflectors (3.5 us at two columns) cost
-// more than the sweep they save.
+// most kSmallB columns takes Q = I, R = B: there the QR and the reflectors cost more than the sweep
+// they save (with 10 columns, D = 5, a launch is 54.6 us with the QR and 57.1 without, with 16 they are even).
 // BWD: the forward update (the same path and arithmetic, so the truncation rank and the
 // gauge of the new tensors are the forward ones bit for bit) that also keeps what the
 // reverse sweep needs: every singular triplet (bU, bV, bS) and float64 T matrices (t64).
@@ -1134,7 +1134,7 @@ __global__ __launch_bounds__(NT, NMAX == 64 ? (ACC_ ? 1 : 2) : NT == 256 ? 4 : A
     __syncthreads();
     // RB row blocks of LJ rows: a matrix of at most half the rows leaves the upper half of them out.
     // SOLO: at most 8 columns, LJ = 16 lanes a pair: one wave has them all, goes without barriers and sums over
-    // the lanes that have rows; the others wait for it.
+    // the lanes that have rows; the others wait for it (24-qubit ring, 6 columns: 31 -> 29 us a launch).
     auto sweeps = [&](auto row_blocks, auto solo) {
       constexpr int RB = decltype(row_blocks)::value;
       constexpr bool SOLO = decltype(solo)::value;
