@@ -85,7 +85,7 @@ typedef struct {
 } gpeps_graph;
 
 typedef struct {
-  int32_t d_max;              /* bond dimension cap chi, 1..32 */
+  int32_t d_max;              /* bond dimension cap chi, 1..64 (adjoint and belief propagation: 1..32) */
   int32_t precision;          /* gpeps_precision */
   double trunc_rel;           /* keep singular values s_k > trunc_rel * s_0 (and at most d_max of them) */
   int32_t max_jacobi_sweeps;  /* cap on one-sided Jacobi sweeps per SVD (<= 0: 40) */
