@@ -307,236 +307,246 @@ __global__ __launch_bounds__(kBT) void k_svd_big(DevState st, const int32_t* __r
   while ((1 << K) < nB) ++K;
   const bool gact = pair_id < (1 << (K - 1));
   const double tol2 = (2.220446049250313e-16 * (double)nB) * (2.220446049250313e-16 * (double)nB);
-  double2 xs[kBRPL], xm[kBRPL];  // stationary and moving column of the group
-  double ns = 0.0, nm = 0.0;  // their tracked squared norms
-  double ps = 1.0, pm = 1.0;  // their squared scales: the column is sqrt(ps) xs
-  int cs_id = ins_bit(pair_id, 0, 0), cm_id = ins_bit(pair_id, 0, 1);
-  // both scales folded into the columns, their squared norms to ns, nm
-  auto fold = [&]() {
-    const double ds = ps * rsq_nr(ps), dm = pm * rsq_nr(pm);
-    ns = 0.0;
-    nm = 0.0;
+  // The iteration, the sort and the kept columns, with RB row blocks of kBLJ rows: a matrix of fewer rows leaves
+  // the others out, and the waves whose groups are all inactive take part in the barriers only.
+  auto iterate = [&](auto row_blocks) {
+    constexpr int RB = decltype(row_blocks)::value;
+    const bool wact = RB == kBRPL || (__builtin_amdgcn_readfirstlane(tid) >> 6) * 8 < (1 << (K - 1));
+    double2 xs[RB], xm[RB];  // stationary and moving column of the group
+    double ns = 0.0, nm = 0.0;  // their tracked squared norms
+    double ps = 1.0, pm = 1.0;  // their squared scales: the column is sqrt(ps) xs
+    int cs_id = ins_bit(pair_id, 0, 0), cm_id = ins_bit(pair_id, 0, 1);
+    // both scales folded into the columns, their squared norms to ns, nm
+    auto fold = [&]() {
+      const double ds = ps * rsq_nr(ps), dm = pm * rsq_nr(pm);
+      ns = 0.0;
+      nm = 0.0;
 #pragma unroll
-    for (int u = 0; u < kBRPL; ++u) {
-      xs[u] = cscale(xs[u], ds);
-      xm[u] = cscale(xm[u], dm);
-      ns += cabs2(xs[u]);
-      nm += cabs2(xm[u]);
-    }
-    ps = 1.0;
-    pm = 1.0;
-    total2(ns, nm);
-  };
-  // initial assignment (block hb = 0): group g holds columns 2g and 2g + 1
-#pragma unroll
-  for (int u = 0; u < kBRPL; ++u) {
-    const int rr = xrow(u);
-    xs[u] = (gact && cs_id < nB && rr < nB) ? x_at(cs_id, rr) : make_double2(0.0, 0.0);
-    xm[u] = (gact && cm_id < nB && rr < nB) ? x_at(cm_id, rr) : make_double2(0.0, 0.0);
-  }
-  const double floor2 = sh_floor * sh_floor;
-
-  // Every column to its owner under block hb.  Within the blocks hb < 6 the ids under 64 stay with
-  // the first half of the groups and the others with the second half, so the halves take turns with
-  // the LDS buffer; into and out of block 6 (two of the seven times a sweep at 128 columns) the ids
-  // of 64 and more go through the item's HBM scratch.  All through the two buffers at once: 26 k
-  // cycles a time.
-  auto redistribute = [&](int hb, int from) {
-    const bool turns = hb < 6 && from < 6;
-    auto put = [&](const double2 (&x)[kBRPL], int c, double n2, double p2) {
-      if (!gact || c >= nB) return;
-      double2* dst = turns ? &X[c & (kBGroups - 1)][0] : c < kBGroups ? &X[c][0] : Og + (int64_t)(c - kBGroups) * kBN;
-#pragma unroll
-      for (int u = 0; u < kBRPL; ++u) dst[xrow(u)] = x[u];
-      if (lane == 0) {
-        nrmx[c] = n2;
-        sclx[c] = p2;
+      for (int u = 0; u < RB; ++u) {
+        xs[u] = cscale(xs[u], ds);
+        xm[u] = cscale(xm[u], dm);
+        ns += cabs2(xs[u]);
+        nm += cabs2(xm[u]);
       }
+      ps = 1.0;
+      pm = 1.0;
+      total2(ns, nm);
     };
-    auto get = [&](double2 (&x)[kBRPL], int c, double& n2, double& p2) {
-      const bool ok = gact && c < nB;
-      const double2* src = turns ? &X[c & (kBGroups - 1)][0]
-                                 : c < kBGroups ? &X[c][0] : Og + (int64_t)(c - kBGroups) * kBN;
+    // initial assignment (block hb = 0): group g holds columns 2g and 2g + 1
 #pragma unroll
-      for (int u = 0; u < kBRPL; ++u) {
-        const double2 t = src[xrow(u)];
-        x[u] = ok ? t : make_double2(0.0, 0.0);
-      }
-      n2 = ok ? nrmx[c] : 0.0;
-      p2 = ok ? sclx[c] : 1.0;
-    };
-    const bool second = pair_id >= kBGroups / 2;
-    const int n_turns = turns && nB > kBGroups ? 2 : 1;
-    for (int turn = 0; turn < n_turns; ++turn) {
-      const bool mine = !turns || second == (turn == 1);
-      if (mine) {
-        put(xs, cs_id, ns, ps);
-        put(xm, cm_id, nm, pm);
-      }
-      __syncthreads();
-      if (mine) {
-        cs_id = ins_bit(pair_id, hb, 0);
-        cm_id = ins_bit(pair_id, hb, 1);
-        get(xs, cs_id, ns, ps);
-        get(xm, cm_id, nm, pm);
-      }
-      __syncthreads();
+    for (int u = 0; u < RB; ++u) {
+      const int rr = xrow(u);
+      xs[u] = (gact && cs_id < nB && rr < nB) ? x_at(cs_id, rr) : make_double2(0.0, 0.0);
+      xm[u] = (gact && cm_id < nB && rr < nB) ? x_at(cm_id, rr) : make_double2(0.0, 0.0);
     }
-  };
+    const double floor2 = sh_floor * sh_floor;
 
-  bool rot = false, big = false;
-  int sweep = 0;
-  bool converged = nB < 2;
-  for (; sweep < st.max_sweeps && !converged; ++sweep) {
-    for (int hb = 0; hb < K; ++hb) {
-      if (hb == 0) fold();
-      const int nt = 1 << hb;
-      // rotation of the pair (stationary xs, moving xm) by tan theta e^{i phi} = g F,
-      // F = sign(d) / (h x), x = cos^2 theta; branch-free: a pair that is not rotated takes F = 0 and
-      // x = 1, which leaves both columns and norms bit for bit
-      auto round = [&]() {
-        double gr, gi;
-        dot_rows<kBRPL>(xs, xm, gr, gi);
-        total2(gr, gi);
-        const double al = ns, be = nm;
-        const double g2 = (gr * gr + gi * gi) * (ps * pm);
-        const double ab = al * be;
-        // the columns of inactive groups and of ids past nB are exactly zero: g = 0
-        const bool ok = (g2 > tol2 * ab) & (g2 > floor2);
-        const double d = be - al;
-        const double h2 = fmax(d * d + 4.0 * g2, 1e-300);
-        const double rh = C64 ? rsq_nr1(h2) : rsq_nr(h2);  // 1 / h
-        const double x = 0.5 + 0.5 * fabs(d) * rh;
-        const double rx = C64 ? rcp_nr1(x) : rcp_nr(x);    // 1 / x
-        const double F = ok ? copysign(rh, d) * rx : 0.0;
-        const double xx = ok ? x : 1.0;
-        const double tg = g2 * F;  // tan theta |g|
-        const double fm = F * pm, fs = F * ps;
-        const double2 tm = make_double2(gr * fm, gi * fm), ts = make_double2(gr * fs, gi * fs);
+    // Every column to its owner under block hb.  Within the blocks hb < 6 the ids under 64 stay with
+    // the first half of the groups and the others with the second half, so the halves take turns with
+    // the LDS buffer; into and out of block 6 (two of the seven times a sweep at 128 columns) the ids
+    // of 64 and more go through the item's HBM scratch.  All through the two buffers at once: 26 k
+    // cycles a time.
+    auto redistribute = [&](int hb, int from) {
+      const bool turns = hb < 6 && from < 6;
+      auto put = [&](const double2 (&x)[RB], int c, double n2, double p2) {
+        if (!gact || c >= nB) return;
+        double2* dst = turns ? &X[c & (kBGroups - 1)][0] : c < kBGroups ? &X[c][0] : Og + (int64_t)(c - kBGroups) * kBN;
 #pragma unroll
-        for (int u = 0; u < kBRPL; ++u) {
-          const double2 a = xs[u], b = xm[u];
-          xs[u].x = fma(-tm.x, b.x, fma(-tm.y, b.y, a.x));
-          xs[u].y = fma(-tm.x, b.y, fma(tm.y, b.x, a.y));
-          xm[u].x = fma(ts.x, a.x, fma(-ts.y, a.y, b.x));
-          xm[u].y = fma(ts.x, a.y, fma(ts.y, a.x, b.y));
+        for (int u = 0; u < RB; ++u) dst[xrow(u)] = x[u];
+        if (lane == 0) {
+          nrmx[c] = n2;
+          sclx[c] = p2;
         }
-        ps *= xx;
-        pm *= xx;
-        ns = al - tg;
-        nm = be + tg;
-        rot = rot || ok;
-        big = big || (ok && g2 > kQuietBigC64 * ab);
       };
-      auto move = [&](auto perm) {  // the moving column, its norm and scale, through a lane permutation
+      auto get = [&](double2 (&x)[RB], int c, double& n2, double& p2) {
+        const bool ok = gact && c < nB;
+        const double2* src = turns ? &X[c & (kBGroups - 1)][0]
+                                   : c < kBGroups ? &X[c][0] : Og + (int64_t)(c - kBGroups) * kBN;
 #pragma unroll
-        for (int u = 0; u < kBRPL; ++u) xm[u] = make_double2(perm(xm[u].x), perm(xm[u].y));
-        nm = perm(nm);
-        pm = perm(pm);
+        for (int u = 0; u < RB; ++u) {
+          const double2 t = src[xrow(u)];
+          x[u] = ok ? t : make_double2(0.0, 0.0);
+        }
+        n2 = ok ? nrmx[c] : 0.0;
+        p2 = ok ? sclx[c] : 1.0;
       };
-      if (nt < 8) {
-        // fewer rounds than groups of a wave: group ^ 2^b, b the Gray-code bit
-        for (int t = 0; t < nt; ++t) {
-          round();
-          if (t + 1 < nt) {
-            if (__builtin_ctz(t + 1) == 0) move([](double v) { return dpp_d<0x4E>(v); });  // low: lane ^ 2
-            else move([](double v) { return lane_xor<4>(v); });                             // blk ^ 1
+      const bool second = pair_id >= kBGroups / 2;
+      const int n_turns = turns && nB > kBGroups ? 2 : 1;
+      for (int turn = 0; turn < n_turns; ++turn) {
+        const bool mine = !turns || second == (turn == 1);
+        if (mine) {
+          put(xs, cs_id, ns, ps);
+          put(xm, cm_id, nm, pm);
+        }
+        __syncthreads();
+        if (mine) {
+          cs_id = ins_bit(pair_id, hb, 0);
+          cm_id = ins_bit(pair_id, hb, 1);
+          get(xs, cs_id, ns, ps);
+          get(xm, cm_id, nm, pm);
+        }
+        __syncthreads();
+      }
+    };
+
+    bool rot = false, big = false;
+    int sweep = 0;
+    bool converged = nB < 2;
+    for (; sweep < st.max_sweeps && !converged; ++sweep) {
+      for (int hb = 0; hb < K; ++hb) {
+        if (hb == 0) fold();
+        const int nt = 1 << hb;
+        // rotation of the pair (stationary xs, moving xm) by tan theta e^{i phi} = g F,
+        // F = sign(d) / (h x), x = cos^2 theta; branch-free: a pair that is not rotated takes F = 0 and
+        // x = 1, which leaves both columns and norms bit for bit
+        auto round = [&]() {
+          double gr, gi;
+          dot_rows<RB>(xs, xm, gr, gi);
+          total2(gr, gi);
+          const double al = ns, be = nm;
+          const double g2 = (gr * gr + gi * gi) * (ps * pm);
+          const double ab = al * be;
+          // the columns of inactive groups and of ids past nB are exactly zero: g = 0
+          const bool ok = (g2 > tol2 * ab) & (g2 > floor2);
+          const double d = be - al;
+          const double h2 = fmax(d * d + 4.0 * g2, 1e-300);
+          const double rh = C64 ? rsq_nr1(h2) : rsq_nr(h2);  // 1 / h
+          const double x = 0.5 + 0.5 * fabs(d) * rh;
+          const double rx = C64 ? rcp_nr1(x) : rcp_nr(x);    // 1 / x
+          const double F = ok ? copysign(rh, d) * rx : 0.0;
+          const double xx = ok ? x : 1.0;
+          const double tg = g2 * F;  // tan theta |g|
+          const double fm = F * pm, fs = F * ps;
+          const double2 tm = make_double2(gr * fm, gi * fm), ts = make_double2(gr * fs, gi * fs);
+#pragma unroll
+          for (int u = 0; u < RB; ++u) {
+            const double2 a = xs[u], b = xm[u];
+            xs[u].x = fma(-tm.x, b.x, fma(-tm.y, b.y, a.x));
+            xs[u].y = fma(-tm.x, b.y, fma(tm.y, b.x, a.y));
+            xm[u].x = fma(ts.x, a.x, fma(-ts.y, a.y, b.x));
+            xm[u].y = fma(ts.x, a.y, fma(ts.y, a.x, b.y));
           }
-        }
-        cm_id = ins_bit(pair_id ^ ((nt - 1) ^ ((nt - 1) >> 1)), hb, 1);
-      } else {
-        int T = 0;
-        for (;; ++T) {
-          // blk turns once more than it has to, so that every trip is the same straight line (a
-          // condition on the last one costs copies and spills of the whole column) and the columns
-          // end where they began
+          ps *= xx;
+          pm *= xx;
+          ns = al - tg;
+          nm = be + tg;
+          rot = rot || ok;
+          big = big || (ok && g2 > kQuietBigC64 * ab);
+        };
+        auto move = [&](auto perm) {  // the moving column, its norm and scale, through a lane permutation
+#pragma unroll
+          for (int u = 0; u < RB; ++u) xm[u] = make_double2(perm(xm[u].x), perm(xm[u].y));
+          nm = perm(nm);
+          pm = perm(pm);
+        };
+        if (nt < 8) {
+          // fewer rounds than groups of a wave: group ^ 2^b, b the Gray-code bit
+          for (int t = 0; wact && t < nt; ++t) {
+            round();
+            if (t + 1 < nt) {
+              if (__builtin_ctz(t + 1) == 0) move([](double v) { return dpp_d<0x4E>(v); });  // low: lane ^ 2
+              else move([](double v) { return lane_xor<4>(v); });                             // blk ^ 1
+            }
+          }
+          cm_id = ins_bit(pair_id ^ ((nt - 1) ^ ((nt - 1) >> 1)), hb, 1);
+        } else {
+          int T = 0;
+          for (;; ++T) {
+            // blk turns once more than it has to, so that every trip is the same straight line (a
+            // condition on the last one costs copies and spills of the whole column) and the columns
+            // end where they began
 #pragma unroll 1
-          for (int sb = 0; sb < 4; ++sb) {
-            round();
-            move([](double v) { return dpp_d<0x4E>(v); });  // low ^ 1
-            round();
-            move([](double v) { return dpp_d<0x124>(v); });  // blk - 1 to blk
-          }
-          if (8 * (T + 1) >= nt) break;
-          // to the wave whose index differs in the next Gray-code bit, same group inside the wave
+            for (int sb = 0; wact && sb < 4; ++sb) {
+              round();
+              move([](double v) { return dpp_d<0x4E>(v); });  // low ^ 1
+              round();
+              move([](double v) { return dpp_d<0x124>(v); });  // blk - 1 to blk
+            }
+            if (8 * (T + 1) >= nt) break;
+            // to the wave whose index differs in the next Gray-code bit, same group inside the wave
 #pragma unroll
-          for (int u = 0; u < kBRPL; ++u) X[pair_id][xrow(u)] = xm[u];
-          if (lane == 0) {
-            nrmx[pair_id] = nm;
-            sclx[pair_id] = pm;
-          }
-          __syncthreads();
-          const int src = pair_id ^ (8 << __builtin_ctz(T + 1));
+            for (int u = 0; u < RB; ++u) X[pair_id][xrow(u)] = xm[u];
+            if (lane == 0) {
+              nrmx[pair_id] = nm;
+              sclx[pair_id] = pm;
+            }
+            __syncthreads();
+            const int src = pair_id ^ (8 << __builtin_ctz(T + 1));
 #pragma unroll
-          for (int u = 0; u < kBRPL; ++u) xm[u] = X[src][xrow(u)];
-          nm = nrmx[src];
-          pm = sclx[src];
-          __syncthreads();
+            for (int u = 0; u < RB; ++u) xm[u] = X[src][xrow(u)];
+            nm = nrmx[src];
+            pm = sclx[src];
+            __syncthreads();
+          }
+          cm_id = ins_bit(pair_id ^ ((T ^ (T >> 1)) << 3), hb, 1);
         }
-        cm_id = ins_bit(pair_id ^ ((T ^ (T >> 1)) << 3), hb, 1);
+        if (hb + 1 == K) {
+          if (rot && lane == 0) sh_flag[sweep % 3][0] = 1;
+          if (big && lane == 0) sh_flag[sweep % 3][1] = 1;
+          if (tid < 2) sh_flag[(sweep + 1) % 3][tid] = 0;
+          rot = false;
+          big = false;
+        }
+        if (hb + 1 < K) redistribute(hb + 1, hb);
       }
-      if (hb + 1 == K) {
-        if (rot && lane == 0) sh_flag[sweep % 3][0] = 1;
-        if (big && lane == 0) sh_flag[sweep % 3][1] = 1;
-        if (tid < 2) sh_flag[(sweep + 1) % 3][tid] = 0;
-        rot = false;
-        big = false;
-      }
-      if (hb + 1 < K) redistribute(hb + 1, hb);
+      __syncthreads();
+      converged = (sh_flag[sweep % 3][0] == 0) || (C64 && sh_flag[sweep % 3][1] == 0);
+      if (!converged) redistribute(0, K - 1);
+    }
+    fold();
+    if (tid == 0) count_svd(st, sweep, converged);
+
+    // singular values (norms of the held columns), stable descending order, truncation
+    const double s_s = sqrt(ns), s_m = sqrt(nm);
+    if (lane == 0 && gact) {
+      if (cs_id < nB) sig[cs_id] = s_s;
+      if (cm_id < nB) sig[cm_id] = s_m;
     }
     __syncthreads();
-    converged = (sh_flag[sweep % 3][0] == 0) || (C64 && sh_flag[sweep % 3][1] == 0);
-    if (!converged) redistribute(0, K - 1);
-  }
-  fold();
-  if (tid == 0) count_svd(st, sweep, converged);
-
-  // singular values (norms of the held columns), stable descending order, truncation
-  const double s_s = sqrt(ns), s_m = sqrt(nm);
-  if (lane == 0 && gact) {
-    if (cs_id < nB) sig[cs_id] = s_s;
-    if (cm_id < nB) sig[cm_id] = s_m;
-  }
-  __syncthreads();
-  for (int c = tid; c < nB; c += kBT) perm[falling_rank(sig, nB, c)] = c;
-  __syncthreads();
-  if (tid == 0) {
-    const double smax = sig[perm[0]];
-    int keep = 0;
-    for (int d2 = 0; d2 < nB; ++d2) keep += sig[d2] > st.trunc_rel * smax;
-    int chi = keep < D ? keep : D;
-    if (chi < 1) chi = 1;
-    double nr = 0.0;
-    for (int k = 0; k < chi; ++k) nr += sig[perm[k]] * sig[perm[k]];
-    nr = sqrt(nr);
-    if (!(smax > 0.0)) flag_status(st.status, kStatusZeroTheta);
-    if (!isfinite(nr)) flag_status(st.status, kStatusNonFinite);
-    sh_chi = chi;
-    sh_norm = nr;
-    st.meta[slot].de_old = de;
-    st.meta[slot].chi_new = chi;
-    st.chi[e] = chi;
-  }
-  __syncthreads();
-  const int chi = sh_chi;
-  for (int k = tid; k < D; k += kBT) lam_e[k] = k < chi ? sig[perm[k]] / sh_norm : 0.0;
-
-  // kept columns of X, normalised: B's right singular vectors with rows permuted by the pivoting,
-  // X[k'][colid[r]] = x[r] / sigma (rows < nB)
-  auto stage = [&](const double2 (&x)[kBRPL], int c, double sv) {
-    if (!gact || c >= nB) return;
-    const int rank = falling_rank(sig, nB, c);
-    if (rank >= chi) return;
-    const double inv = sv > 0.0 ? 1.0 / sv : 0.0;
-#pragma unroll
-    for (int u = 0; u < kBRPL; ++u) {
-      const int rr = xrow(u);
-      if (rr < nB) X[rank][colid_sh[rr]] = cscale(x[u], inv);
+    for (int c = tid; c < nB; c += kBT) perm[falling_rank(sig, nB, c)] = c;
+    __syncthreads();
+    if (tid == 0) {
+      const double smax = sig[perm[0]];
+      int keep = 0;
+      for (int d2 = 0; d2 < nB; ++d2) keep += sig[d2] > st.trunc_rel * smax;
+      int chi = keep < D ? keep : D;
+      if (chi < 1) chi = 1;
+      double nr = 0.0;
+      for (int k = 0; k < chi; ++k) nr += sig[perm[k]] * sig[perm[k]];
+      nr = sqrt(nr);
+      if (!(smax > 0.0)) flag_status(st.status, kStatusZeroTheta);
+      if (!isfinite(nr)) flag_status(st.status, kStatusNonFinite);
+      sh_chi = chi;
+      sh_norm = nr;
+      st.meta[slot].de_old = de;
+      st.meta[slot].chi_new = chi;
+      st.chi[e] = chi;
     }
+    __syncthreads();
+    const int chi = sh_chi;
+    for (int k = tid; k < D; k += kBT) lam_e[k] = k < chi ? sig[perm[k]] / sh_norm : 0.0;
+
+    // kept columns of X, normalised: B's right singular vectors with rows permuted by the pivoting,
+    // X[k'][colid[r]] = x[r] / sigma (rows < nB)
+    auto stage = [&](const double2 (&x)[RB], int c, double sv) {
+      if (!gact || c >= nB) return;
+      const int rank = falling_rank(sig, nB, c);
+      if (rank >= chi) return;
+      const double inv = sv > 0.0 ? 1.0 / sv : 0.0;
+#pragma unroll
+      for (int u = 0; u < RB; ++u) {
+        const int rr = xrow(u);
+        if (rr < nB) X[rank][colid_sh[rr]] = cscale(x[u], inv);
+      }
+    };
+    stage(xs, cs_id, sig[cs_id < nB ? cs_id : 0]);
+    stage(xm, cm_id, sig[cm_id < nB ? cm_id : 0]);
+    __syncthreads();
   };
-  stage(xs, cs_id, sig[cs_id < nB ? cs_id : 0]);
-  stage(xm, cm_id, sig[cm_id < nB ? cm_id : 0]);
-  __syncthreads();
+  if (nB <= 2 * kBLJ) iterate(std::integral_constant<int, 2>());
+  else if (nB <= 4 * kBLJ) iterate(std::integral_constant<int, 4>());
+  else iterate(std::integral_constant<int, kBRPL>());
+  const int chi = sh_chi;
 
   // B's right singular vectors are V of Theta' (B = Theta') or U of Theta' (B = Theta'^H); the
   // other set from the stored Theta': U = Theta' V / sigma or V = Theta'^H U / sigma, into
