@@ -193,9 +193,15 @@ __global__ __launch_bounds__(256) void k_absorb_qr(DevState st, const int32_t* _
 // CUs idle, and one CU's FP64 matrix cores need 250 us for one.  The first launch (kGramPart) leaves
 // the partial Gram matrices in the scratch of the SVD that follows, the second (kGramEnd) adds them in a
 // fixed order and factorises.  One 127-qubit instance at D = 64: 479 -> 217 + 85 us in the largest
-// class, 147 -> 104 us in the mean.
+// class, 147 -> 104 us in the mean.  Ends of at most kGramSplitRows rows are done whole by the first
+// launch, and only the tiles that the bond fills are written: while the bonds are small the partial
+// sums cost more than the rows.  One 127-qubit instance at D = 33, microseconds of the first eight steps:
+// 27 / 32 / 34 / 38 / 59 / 94 / 96 / 96 with every end split and every tile written,
+// 14 / 19 / 26 / 34 / 58 / 94 / 97 / 98 from 8 rows, 14 / 16 / 19 / 29 / 56 / 92 / 97 / 97 from 128,
+// 14 / 16 / 19 / 31 / 63 / 92 / 97 / 97 from 512.
 constexpr int kGramWhole = 0, kGramPart = 1, kGramEnd = 2;
 constexpr int kGramSplit = 4;
+constexpr int kGramSplitRows = 128;
 
 template <int NC, int MODE = kGramWhole>
 __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState st, const int32_t* __restrict__ items, int first) {
@@ -205,8 +211,11 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
   constexpr int UNR = NT16 >= 4 ? 2 : 4 / NT16;  // row steps (of 4 rows) per load batch in flight
   int slot, side, p;
   constexpr int SP = MODE == kGramPart ? kGramSplit : 1;
-  const int split = MODE == kGramPart ? (int)blockIdx.x % kGramSplit : 0;
-  end_task(st, blockIdx.x / SP, slot, side, p);
+  // the parts of an end lie a whole grid of ends apart: the ends done whole then stand in consecutive
+  // blocks, on all XCDs (block mod 8)
+  const int ends = (int)gridDim.x / SP;
+  const int split = (int)blockIdx.x / ends;
+  end_task(st, blockIdx.x - split * ends, slot, side, p);
   const int e = items[first + slot];
   const EdgeInfo& E = st.edges[e];
   const SideGeom G = side_geom(st, E.side[side]);
@@ -217,9 +226,10 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
   const int D = st.D;
   const int tid = threadIdx.x;
 
+  const bool whole = MODE == kGramWhole || M <= kGramSplitRows;
+  if ((MODE == kGramPart && whole && split > 0) || (MODE == kGramEnd && whole)) return;
   if (M <= n) {  // no reduction: R = A (M x n)
-    if (MODE == kGramEnd) return;
-    for (int idx = tid + split * 256; idx < M * n; idx += 256 * SP) {
+    for (int idx = tid; idx < M * n; idx += 256) {
       const int m = idx / n, k = idx - (idx / n) * n;
       R[m * D + k] = cscale(to_d2(gam[G.addr(p, m, k)]), G.env(m));
     }
@@ -232,7 +242,7 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
   constexpr int PART = NTILE * 4 * 64;
   constexpr int GSZ = NC * (NC + 1);
   static_assert(MODE == kGramWhole || 4 * kGramSplit * PART <= big_scratch(NC), "partial sums in st.big");
-  __shared__ double2 lds[PART + (GSZ > PART && MODE != kGramPart ? GSZ : PART)];
+  __shared__ double2 lds[PART + (GSZ > PART ? GSZ : PART)];
   __shared__ double dg[NC];           // squared column norms (diagonal of G)
   __shared__ double envs[2][NC];      // lambda weights of the other two legs (1 for a missing leg)
   double2* part0 = lds;
@@ -255,7 +265,7 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
     gr[t] = (d4){0.0, 0.0, 0.0, 0.0};
     gi[t] = (d4){0.0, 0.0, 0.0, 0.0};
   }
-  constexpr int WS = 4 * SP;  // waves that share the rows
+  const int WS = whole ? 4 : 4 * SP;  // waves that share the rows
   // Software pipelined: the complex64 elements of the next batch of rows (4 ks + l / 16, columns
   // 16 t + l % 16) are in flight while the products of the current batch run.  A row past the
   // end gets weight 0 (its load is clamped to the last row).
@@ -356,8 +366,11 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
           const double2 v = make_double2(gr[tile][r] + q.x, gi[tile][r] + q.y);
           // off the diagonal tiles k < k' always; a diagonal tile is stored whole (its lower
           // half holds X[k'][k] for the antisymmetrisation below)
-          if constexpr (MODE == kGramPart) gpar[split * PART + (tile * 4 + r) * 64 + l] = v;
-          else Gs(16 * ta + lk + 4 * r, 16 * tb + li) = v;
+          if (MODE == kGramPart && !whole) {
+            if (16 * tb < n) gpar[split * PART + (tile * 4 + r) * 64 + l] = v;
+          } else {
+            Gs(16 * ta + lk + 4 * r, 16 * tb + li) = v;
+          }
         }
         ++tile;
       }
@@ -368,7 +381,7 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
     for (int ta = 0; ta < NT16; ++ta)
 #pragma unroll
       for (int tb = ta; tb < NT16; ++tb) {
-        if ((tile & 3) == wv) {
+        if ((tile & 3) == wv && 16 * tb < n) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             double2 v = gpar[(tile * 4 + r) * 64 + l];
@@ -380,7 +393,7 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
         ++tile;
       }
   }
-  if constexpr (MODE == kGramPart) return;
+  if (MODE == kGramPart && !whole) return;
   __syncthreads();
   // Im G on the diagonal tiles: X[k][k'] - X[k'][k] on the upper triangle (which is all the
   // factorisation reads), exactly 0 on the diagonal; only the upper entries are written
