@@ -911,9 +911,10 @@ gpeps_status gpeps_init(gpeps_ctx** out, const gpeps_graph* graphs, int32_t n_gr
   st.trunc_rel = cfg->trunc_rel;
   // rows of an end over four workgroups (complex64, d_max > 32): pays while the ends of a class leave
   // CUs idle and some end has rows to share (absorb of one class of 127 qubits, 48 edges an instance,
-  // whole / split, mean over eight steps: one instance at D = 64 166 / 115 us, D = 48 108 / 82, D = 33 67 / 59; two
-  // at D = 64 175 / 138, D = 48 110 / 100, D = 40 87 / 89, D = 33 70 / 82; three at D = 64 183 / 194, D = 48 114 / 137:
-  // the line lies where it pays at every bond; ring, two legs a vertex, 11.8 / 14.4)
+  // whole / split, mean over eight steps: one instance at D = 64 166 / 110 us, D = 48 107 / 76, D = 33 67 / 53; two
+  // at D = 64 175 / 128, D = 48 110 / 89, D = 40 86 / 77, D = 33 70 / 68; three at D = 64 182 / 171, D = 48 115 / 115;
+  // four at D = 64 191 / 210, D = 33 85 / 104: the gain shrinks to nothing by three instances, the line lies
+  // at one; ring, two legs a vertex, 11.8 / 14.4)
   st.gram_split = c->D > kMaxD && L.max_items <= 64 &&
                   std::any_of(L.verts.begin(), L.verts.end(), [](const VertexInfo& v) { return v.deg == kMaxDeg; });
   st.tune_rb = default_rb_tiles(c);

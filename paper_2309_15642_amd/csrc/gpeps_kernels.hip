@@ -214,7 +214,7 @@ __global__ __launch_bounds__(256, NC == 32 ? 4 : 1) void k_absorb_gram(DevState 
   // the parts of an end lie a whole grid of ends apart: the ends done whole then stand in consecutive
   // blocks, on all XCDs (block mod 8)
   const int ends = (int)gridDim.x / SP;
-  const int split = (int)blockIdx.x / ends;
+  const int split = MODE == kGramPart ? (int)blockIdx.x / ends : 0;
   end_task(st, blockIdx.x - split * ends, slot, side, p);
   const int e = items[first + slot];
   const EdgeInfo& E = st.edges[e];
