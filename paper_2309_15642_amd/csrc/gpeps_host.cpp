@@ -369,6 +369,7 @@ gpeps_status build_layout(const gpeps_graph* graphs, int32_t n_graphs, const int
   // end lists of the absorb, the re-absorb and the edge adjoint: the ends of a class whose site
   // has at most one other leg need one block of rows per slice, the others up to
   // D^2 / rows-per-block; the light ends are stored first, the launches take the heavy ones first
+  L.rlist.reserve(4 * (size_t)L.NE);
   L.rl_begin.resize(L.n_classes);
   L.rl_light.resize(L.n_classes);
   L.rl_heavy.resize(L.n_classes);
@@ -390,10 +391,16 @@ gpeps_status build_layout(const gpeps_graph* graphs, int32_t n_graphs, const int
   // evenly
   L.bp_order = L.rlist.size();
   if (D <= kMaxD) {
-    std::vector<int32_t> by_deg[kMaxDeg + 1];
+    size_t at[kMaxDeg + 2] = {};  // at[deg]: where the senders of that degree begin
+    for (const EdgeInfo& E : L.edges) {
+      ++at[E.side[0].deg - 1];
+      ++at[E.side[1].deg - 1];
+    }
+    for (int deg = kMaxDeg - 1; deg >= 0; --deg) at[deg] += at[deg + 1];
+    L.rlist.resize(L.bp_order + at[0]);
+    int32_t* const order = L.rlist.data() + L.bp_order;
     for (int e = 0; e < L.NE; ++e)
-      for (int sd = 0; sd < 2; ++sd) by_deg[L.edges[e].side[sd].deg].push_back(2 * e + sd);
-    for (int deg = kMaxDeg; deg >= 1; --deg) L.rlist.insert(L.rlist.end(), by_deg[deg].begin(), by_deg[deg].end());
+      for (int sd = 0; sd < 2; ++sd) order[at[L.edges[e].side[sd].deg]++] = 2 * e + sd;
   }
   const size_t slots = std::max(L.max_items, 1);
   size_t off = 0;
